@@ -86,7 +86,9 @@ typedef int32_t lm_status;
 #define LM_GRAPH 0x10u       /* run the whole solve as one captured HIP graph launch: set-up,
                                 a fixed number of phases that do nothing once the tail kernel
                                 has taken over, and the tail kernel (no host round trip);
-                                ignored together with LM_PROFILE or LM_ASYNC; same results */
+                                ignored together with LM_PROFILE or LM_ASYNC, and by solves
+                                whose graphs one workgroup each solves (a few launches and no
+                                host round trip as they are); same results */
 #define LM_WEIGHT_SUM 0x20u  /* after the solve, set stats->matched_weight (needs stats) */
 #define LM_ASYNC 0x40u       /* stream-ordered: enqueue the whole solve on `stream` and return
                                 at once; mate holds the result when the stream reaches that
@@ -140,7 +142,8 @@ typedef struct {
   int32_t phases;         /* phases with at least one live edge */
   int32_t log_len;        /* records written to log (<= log_cap) */
   int64_t matched_edges;  /* |M| */
-  double device_ms;       /* stream time of the solve (events around it) */
+  double device_ms;       /* stream time of the solve (events around it; a graph solved by a single
+                             kernel: that kernel's time by the device's constant clock) */
   double bytes_alg;       /* algorithmic HBM bytes of all kernels, from the log */
   lm_phase_rec* log;      /* caller buffer for per-phase records, or NULL */
   int32_t log_cap;        /* its capacity in records */
@@ -220,7 +223,7 @@ typedef struct {
                               solves: LM_GRAPH, LM_ASYNC); a host-polled solve hands over one
                               phase after a live set of at most 4x this many (it keeps one phase
                               queued ahead). 0: host-polled solves never hand over (default
-                              2^20) */
+                              2^20), and no graph is solved by one workgroup */
 } lm_tuning;
 
 lm_status lm_get_tuning(lm_ctx* ctx, lm_tuning* out);

@@ -122,6 +122,7 @@ struct PhaseMirror {
   unsigned err;                // error flags so far
   int last_nonempty;           // last phase that had live rows
   int pad;
+  unsigned long long ticks;    // k_solo: the solve's time by the device's constant clock
   unsigned long long tag;      // (gen << 32) | t once the record is complete
 };
 constexpr int kMirrorSlots = 64;
@@ -307,6 +308,58 @@ struct TailArgs {
   PhaseMirror* final_rec;  // the solve's final record
   unsigned gen;
   unsigned long long spin_ticks;  // a barrier wait longer than this (device wall clock) aborts the solve
+};
+
+// Whole graphs solved by one workgroup each (k_solo).
+constexpr long long kSoloMaxN = 65536;     // vertices: candidates are 16-bit local ids in LDS
+// Entries up to which a single graph is solved by one workgroup: beyond them
+// the phase kernels and the tail kernel, spread over the chip, are faster.
+// Measured (us a call, one workgroup / spread): weighted ER of average degree
+// 16 with 131 K entries 156 / 243, with 262 K 279 / 276; weighted R-MAT with
+// 97 K 220 / 222, with 204 K 434 / 270; unweighted (every entry hashed) RGG
+// with 40 K 109 / 168, with 81 K 198 / 189; unweighted R-MAT with 46 K
+// 186 / 211, with 97 K 277 / 223. A batch has a workgroup for every graph
+// and is faster this way throughout (2 graphs of 2^15 to 2^16 vertices 874 /
+// 2313, 256 of them 2251 / 4821).
+constexpr long long kSoloEntries = 3 << 15;
+constexpr long long kSoloEntriesUnw = 1 << 16;
+constexpr int kSoloClasses = 3;            // size classes of a batch's graphs
+
+struct SoloArgs {
+  const long long* rp;  // row_ptr of the graph or the union
+  const int* col;
+  const float* w;       // nullptr: unweighted
+  int* mate;
+  long long N, nnz;     // vertices and entries of the union
+  int n;                // the graph's vertices (order == nullptr)
+  unsigned long long seed;  // its premixed seed
+  int renew;
+  const int* order;     // graph of workgroup b (a batch), or nullptr: one graph
+  const long long* vtx_off;
+  const unsigned long long* gseed;
+  int4* rows[2];        // live-row lists: N records each
+  int* ecol[2];         // live entries, each graph in its own input range
+  float* ew[2];
+  uint4* acc;           // a batch: the phase log's sums over its graphs
+  Totals* totals;
+  int check_err;        // totals->err was written by the input check
+  int* gphase;          // optional: phases per graph
+  LogRec* log;
+  int log_cap;
+  PhaseMirror* final_rec;
+  unsigned gen;
+};
+
+struct SoloOrder {
+  const long long* vtx_off;
+  const long long* rp;
+  int graphs;
+  long long cls_n[kSoloClasses];
+  int* order;
+  uint4* acc;
+  int acc_n;
+  int* gphase;
+  Totals* totals;  // cleared, or nullptr: the input check has written it
 };
 
 struct CheckArgs {

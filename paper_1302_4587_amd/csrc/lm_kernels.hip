@@ -475,6 +475,7 @@ __global__ __launch_bounds__(kPlanThreads) void k_plan(PlanArgs a) {
     m.err = tot.err;
     m.last_nonempty = tot.last_nonempty;
     m.pad = 0;
+    m.ticks = 0ull;
     m.tag = 0ull;
     PhaseMirror* slot = &a.mirror[m.t & (kMirrorSlots - 1)];
     *(volatile unsigned long long*)&slot->tag = 0ull;  // the slot is being rewritten

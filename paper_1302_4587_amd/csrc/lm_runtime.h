@@ -120,6 +120,8 @@ struct Solver {
   size_t t_pinned_cap = 0;
   hipEvent_t e0 = nullptr, e1 = nullptr;
   hipEvent_t e_order = nullptr;   // orders a captured solve after the legacy default stream
+  hipStream_t side = nullptr;     // a batch's smaller graphs, beside its largest (run_solo)
+  hipEvent_t e_fork = nullptr;    // orders side after the solve's stream, and back
   hipEvent_t e_tables = nullptr;  // after the last per-graph table upload
   std::vector<hipEvent_t> evpool;
 
@@ -128,8 +130,14 @@ struct Solver {
   lm_status prepare(int64_t N, int64_t nnz, int64_t G, bool want_gphase);
   Work pool_work() const;  // the pool's buffers, after prepare
   lm_status run(const Problem& p, const Work& wk, hipStream_t s, uint32_t flags, lm_stats* st);
+  // One workgroup per graph (lm_solo.hip): whether it takes this solve, and the solve.
+  bool solo_fits(int64_t N, int64_t nnz, int64_t G, const int64_t* vtx_off, bool unweighted) const;
+  lm_status run_solo(const Problem& p, const Work& wk, const int64_t* vtx_off, uint64_t seed, hipStream_t s,
+                     uint32_t flags, lm_stats* st);
   hipEvent_t event(size_t i);
 };
+
+lm_status solo_setup();  // raises the kernels' LDS limit on the current device
 
 // Matched weight (LM_WEIGHT_SUM): partial sums go to scratch[0, grid) and the
 // total to scratch[kWeightSumMaxGrid]; scratch holds kWeightSumMaxGrid + 1 doubles.

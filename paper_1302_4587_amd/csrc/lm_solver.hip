@@ -215,6 +215,7 @@ lm_status Solver::init_device(int device, size_t budget) {
   if (hipHostGetDevicePointer((void**)&d_mir, h_mir, 0) != hipSuccess) return LM_EDEVICE;
   if (hipHostGetDevicePointer((void**)&d_log, h_log, 0) != hipSuccess) return LM_EDEVICE;
   if (noalloc_setup(device) != LM_OK) return LM_EDEVICE;
+  if (solo_setup() != LM_OK) return LM_EDEVICE;
   bpc_stream = max_blocks_per_cu_stream(StreamKind::kCompact);
   bpc_first = max_blocks_per_cu_stream(StreamKind::kFirst);
   bpc_late = max_blocks_per_cu_stream(StreamKind::kLateCompact);
@@ -234,6 +235,7 @@ lm_status Solver::init_device(int device, size_t budget) {
 void Solver::shutdown() {
   if (dev >= 0) (void)hipSetDevice(dev);
   if (own) (void)hipStreamSynchronize(own);
+  if (side) (void)hipStreamSynchronize(side);
   if (e_async && async_pending) (void)hipEventSynchronize(e_async);
   async_pending = false;
   DevBuf* all[] = {&C,       &state,   &rows[0], &rows[1], &ecol[0], &ecol[1], &ew[0],   &ew[1],
@@ -263,6 +265,10 @@ void Solver::shutdown() {
 
   if (own) (void)hipStreamDestroy(own);
   own = nullptr;
+  if (side) (void)hipStreamDestroy(side);
+  side = nullptr;
+  if (e_fork) (void)hipEventDestroy(e_fork);
+  e_fork = nullptr;
   h_totals = nullptr;
   e0 = e1 = nullptr;
 }
@@ -873,7 +879,10 @@ static lm_status solve_common(lm_ctx* c, int64_t N, int64_t nnz, int64_t G, cons
   // after everything already queued there (for example the kernels that
   // produced device inputs). A captured graph needs a stream of its own, which
   // then waits for the default stream.
-  const bool own_stream = !stream && (flags & LM_GRAPH) && !(flags & LM_PROFILE);
+  // Graphs that one workgroup each solves take a few launches and no host
+  // round trip: nothing is captured.
+  const bool solo = N > 0 && S.solo_fits(N, nnz, G, h_vtx_off, w == nullptr);
+  const bool own_stream = !stream && (flags & LM_GRAPH) && !(flags & LM_PROFILE) && !solo;
   hipStream_t s = stream ? (hipStream_t)stream : (own_stream ? S.own : nullptr);
   if (own_stream) {
     if (hipEventRecord(S.e_order, nullptr) != hipSuccess || hipStreamWaitEvent(s, S.e_order, 0) != hipSuccess) {
@@ -935,7 +944,8 @@ static lm_status solve_common(lm_ctx* c, int64_t N, int64_t nnz, int64_t G, cons
     if ((rs = S.pool.reserve(S.out_mate, (size_t)N * 4)) != LM_OK) return rs;
     d_mate = (int32_t*)S.out_mate.p;
   }
-  // per-graph tables
+  // per-graph tables (one graph solved by one workgroup takes its seed as an argument)
+  const bool tables = !(solo && G == 1);
   std::vector<int32_t> hb((size_t)G);
   std::vector<uint64_t> hs((size_t)G);
   std::vector<int64_t> hv((size_t)G + 1);
@@ -947,8 +957,8 @@ static lm_status solve_common(lm_ctx* c, int64_t N, int64_t nnz, int64_t G, cons
   hv[(size_t)G] = h_vtx_off ? h_vtx_off[G] : N;
   // The tables live on the device between solves: upload only what changed
   // (repeated solves of one shape and seed upload nothing), from pinned memory.
-  if (hb != S.t_gbase || hs != S.t_gseed || hv != S.t_vtxoff || S.t_dev[0] != S.gbase.p ||
-      S.t_dev[1] != S.gseed.p || S.t_dev[2] != S.vtxoff.p) {
+  if (tables && (hb != S.t_gbase || hs != S.t_gseed || hv != S.t_vtxoff || S.t_dev[0] != S.gbase.p ||
+      S.t_dev[1] != S.gseed.p || S.t_dev[2] != S.vtxoff.p)) {
     const size_t bytes = (size_t)G * 4 + (size_t)G * 8 + (size_t)(G + 1) * 8 + 64;
     if (S.t_pinned_cap < bytes) {
       if (S.t_pinned) (void)hipHostFree(S.t_pinned);
@@ -996,7 +1006,8 @@ static lm_status solve_common(lm_ctx* c, int64_t N, int64_t nnz, int64_t G, cons
     rs = check_row_duplicates(S, N, nnz, p.row_ptr, p.col, s);
     if (rs != LM_OK) return rs;
   }
-  rs = S.run(p, S.pool_work(), s, flags, sp);
+  rs = solo ? S.run_solo(p, S.pool_work(), h_vtx_off, seeds ? seeds[0] : seed0, s, flags, sp)
+            : S.run(p, S.pool_work(), s, flags, sp);
   if (rs != LM_OK) return rs;
   if (flags & LM_ASYNC) return LM_OK;  // enqueued; the result lands in order on the stream
   double wsum = 0.0;
@@ -1017,7 +1028,8 @@ static lm_status solve_common(lm_ctx* c, int64_t N, int64_t nnz, int64_t G, cons
     if (hipMemcpyAsync(graph_phases, S.gphase.p, (size_t)G * 4, hipMemcpyDeviceToHost, s) != hipSuccess)
       return LM_EDEVICE;
   }
-  if (hipStreamSynchronize(s) != hipSuccess) return LM_EDEVICE;
+  // (a solve by whole workgroups has waited for its last kernel)
+  if (!(solo && !want_w && out_dev && !graph_phases) && hipStreamSynchronize(s) != hipSuccess) return LM_EDEVICE;
   if (want_w) st->matched_weight = wsum;
   return LM_OK;
 }

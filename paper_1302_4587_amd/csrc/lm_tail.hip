@@ -584,6 +584,7 @@ __global__ __launch_bounds__(kTailBlock) void k_tail(TailArgs a) {
     m.err = ld_u32(&tot->err);
     m.last_nonempty = last_nonempty;
     m.pad = c0;  // the live set the tail started from
+    m.ticks = 0ull;
     m.tag = 0ull;
     PhaseMirror* slot = a.final_rec;
     *(volatile unsigned long long*)&slot->tag = 0ull;
