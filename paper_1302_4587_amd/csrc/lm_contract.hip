@@ -10,18 +10,17 @@
 // merges (at most four in a simple graph) added in increasing order of the
 // fine edge (min end, max end), the same order from both sides.
 //
-// Work: (1) a scan over the fine vertices numbers the pairs (cmap); (2) every
-// coarse row whose bound deg(a) + deg(b) is at most kCS is merged in LDS: a
-// workgroup takes the coarse rows of a range of fine vertices in tiles of at
-// most kCT entries, maps each entry's neighbour through cmap, and groups the
-// entries of one coarse neighbour in the row's own slots of an LDS hash
-// table, with a list per slot; the first entry of a group (in row order)
-// keeps it with the group's sum, and the kept entries are written compacted
-// at the start of their fine row part. (3) Longer rows get a hash table of
-// their own in device memory and the same grouping over all their entries at
-// once. (4) A scan over the coarse rows gives their offsets and the kept
-// entries are copied out in order. The fine graph's entries are read once;
-// cmap is gathered once per entry.
+// Work: (1) a scan over the fine vertices numbers the pairs (cmap) and cuts the
+// vertices into ranges of equal cost. (2) Coarse rows by their bound deg(a) +
+// deg(b): up to kWS entries, several rows at once in a wave's tile; up to kCS,
+// a wave each; longer ones, a workgroup each or several (3). All find the
+// entries of one coarse neighbour in a hash set in LDS; the first of them in
+// row order keeps it with the sum, and the kept entries are written compacted
+// at the start of their fine row part (longer rows: in place, the others
+// marked as dropped). (4) A scan over the coarse rows gives their offsets and
+// the kept entries are copied out in order. The fine graph's entries are read
+// once; cmap is gathered once per entry, which is what bounds the skewed
+// graphs (R-MAT scale 24: about 100 G gathers a second).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -39,19 +38,17 @@ namespace {
 
 constexpr int kCV = 16;                 // fine vertices per lane in the numbering scans
 constexpr int kCBlockV = kBlock * kCV;  // fine vertices per scan block
-constexpr int kCT = 1024;               // tile capacity in entries
-constexpr int kCS = 512;                // largest coarse-row bound merged in LDS
-constexpr int kCStep = kCT - kCS;       // tiles take the rows that start in a window of this many entries
-constexpr int kCTI = kCT / kBlock;      // tile entries per lane
+constexpr int kCT = 1024;               // entries per workgroup a range is worth at least (twice this)
+constexpr int kCS = 512;                // largest coarse-row bound one wave merges
 constexpr int kCMaxDup = 4;             // fine edges one coarse edge merges at most in a simple graph
 constexpr int kCCost = 4;               // cost of a fine vertex when ranges are split (entries cost 1)
 constexpr int kCTopThreads = 1024;
-constexpr int kCPackGrid = 4096;
-constexpr unsigned long long kEmpty = ~0ull;
 constexpr int kLB = 512;      // average entries of a long row's bucket
-constexpr int kLBCap = 1024;  // entries a bucket may hold in LDS (more: the table path)
-constexpr int kLC = 8192;     // entries of a long row per counting / scatter chunk
-constexpr int kLHist = 4096;  // buckets a row may have for the chunks' LDS histograms
+constexpr int kLBCap = 1024;  // slots of a bucket's table in LDS (more neighbours: the table path)
+constexpr int kLSmall = 4;    // buckets of a long row that a workgroup of kBlock lanes merges
+constexpr int kLPart = 8;     // buckets a workgroup of kLBig lanes merges at once
+constexpr int kLBig = 1024;
+constexpr int kLC = 8192;     // entries of a long row per chunk of the mapping and the output
 
 constexpr unsigned kCErrMate = 1u;    // mate is not an involution with -1 for free vertices
 constexpr unsigned kCErrRowPtr = 2u;  // row_ptr is not a valid offset array
@@ -66,9 +63,8 @@ struct CTot {
   long long nlong;         // coarse rows merged through device-memory tables
   long long long_entries;  // the sum of their bounds
   long long long_slots;    // hash slots their tables take
-  long long long_buckets;  // LDS-sized buckets their entries are sorted into
+  long long long_items;    // low word: long rows of at most kLSmall buckets; high word: parts of kLPart buckets of the others
   long long long_chunks;   // row-aligned chunks of kLC entries
-  long long long_kept;     // their entries that are not the matched edge
   unsigned overflow;       // a bucket outgrew LDS: the long rows take the table path
   unsigned pad2;
 };
@@ -78,10 +74,10 @@ struct LongRow {
   int ub;     // deg(a) + deg(b)
   int tbits;  // table of 2^tbits slots
   int nb;     // buckets of the row (about kLB entries each)
-  int pad;
+  int np;     // parts of kLPart buckets; 0: at most kLSmall buckets
   long long eoff;  // first flat index of the row's entries among all long rows
   long long toff;  // first slot of its table
-  long long boff;  // first bucket of the row
+  int soff, boff;  // its place among the rows of at most kLSmall buckets; its first part
   long long coff;  // first chunk of the row (kLC entries each)
 };
 
@@ -97,21 +93,34 @@ struct CArgs {
   int* cnt;   // fine vertex -> coarse entries kept from its row part
   long long* cvw;  // nullptr: not wanted
   long long* bsum;
+  int* vstart;         // first vertex of each range of the kernels that walk vertices (nullptr: searched for)
+  long long per_wg;    // cost units of a range
+  int ranges;
   CTot* tot;
-  int2* scr;  // per fine entry: (coarse neighbour, summed weight bits) if kept, else (-1, 0)
-  int* next;  // per fine entry of a long row: the previous entry of its table slot's list
+  // The merged entries. Rows of bound <= kCS: the kept ones compacted at the
+  // start of their fine row part. Long rows: at their own fine entries, -1
+  // where dropped. dmap: the coarse neighbour, with kMerged if aux holds the
+  // summed weight; without it the weight is the fine entry's own (1 for an
+  // unweighted graph), which a compacted entry of a weighted graph has in aux.
+  // (While a long row is merged, aux links the fine edges of one coarse edge.)
+  int* dmap;
+  float* aux;
+  int* next;  // per fine entry of a long row: the previous entry of its table slot's list (table path)
   LongRow* lrows;
   long long lrow_cap;
   int2* table;  // (key, list head) per slot of the long rows' tables
-  long long* bstart;  // per bucket: entry count, then (scanned) first record
-  int* bfill;         // per bucket: records placed so far
-  int* rec;           // fine entry indices of the long rows, grouped by bucket
+  int* srow;   // long row of each row of at most kLSmall buckets
+  int* prow;   // long row of each part
+  int* crow;   // long row of each chunk
+  int* ccnt;   // kept entries of each chunk
   long long* crp;
   int* ccol;
   float* cw;
   int dup_limit;  // fine edges one coarse edge may merge (4; 1 for the duplicate check)
   int identity;   // every vertex free, cmap the identity (the duplicate check of LM_CHECK_GRAPH)
 };
+
+constexpr int kMerged = (int)0x80000000u;  // (coarse ids are below 2^31 - 1, so -1 stays apart)
 
 __device__ __forceinline__ unsigned long long tbl_hash(int d, int bits) {
   return (unsigned long long)(((unsigned)d * 0x9E3779B1u) >> (32 - bits));
@@ -135,25 +144,42 @@ __device__ __forceinline__ long long top_excl_sum(long long x, long long* sm, lo
 }
 
 // (1a) Checks mate and row_ptr and counts the pairs' smaller ends per block
-// (vertex base + i * kBlock + lane: coalesced).
+// (vertex base + i * kBlock + lane: coalesced). Finds the ranges' starts: the
+// first vertex whose cost prefix reaches r per_wg follows the one whose row
+// crosses it.
 __global__ __launch_bounds__(kBlock) void k_c_count(CArgs a) {
   __shared__ long long sm[kWaves];
   const long long base = (long long)blockIdx.x * kCBlockV;
   unsigned err = 0;
   long long reps = 0;
-  for (int i = 0; i < kCV; ++i) {
-    const long long v = base + (long long)i * kBlock + threadIdx.x;
-    if (v >= a.n) break;
-    const int m = a.identity ? -1 : a.mate[v];
-    if (m != -1) {
-      if (m < 0 || m >= a.n || m == v)
-        err |= kCErrMate;
-      else if (a.mate[m] != (int)v)
-        err |= kCErrMate;
+  constexpr int kI = kCV / 2;  // vertices a lane's loads are in flight for (all of them: 152 registers)
+#pragma unroll 1
+  for (int i0 = 0; i0 < kCV; i0 += kI) {
+    int m[kI], mm[kI];
+    long long r0[kI], r1[kI];
+    const long long v0 = base + (long long)i0 * kBlock + threadIdx.x;
+#pragma unroll
+    for (int i = 0; i < kI; ++i) {
+      const long long v = v0 + (long long)i * kBlock;
+      m[i] = v < a.n && !a.identity ? a.mate[v] : -1;
+      r0[i] = v < a.n ? a.rp[v] : 0;
+      r1[i] = v < a.n ? a.rp[v + 1] : 0;
     }
-    reps += (m == -1 || v < m) ? 1 : 0;
-    const long long r0 = a.rp[v], r1 = a.rp[v + 1];
-    if (r1 < r0 || (v == 0 && r0 != 0) || (v == a.n - 1 && r1 != a.nnz)) err |= kCErrRowPtr;
+#pragma unroll
+    for (int i = 0; i < kI; ++i) mm[i] = m[i] >= 0 && m[i] < a.n ? a.mate[m[i]] : -1;
+#pragma unroll
+    for (int i = 0; i < kI; ++i) {
+      const long long v = v0 + (long long)i * kBlock;
+      if (v >= a.n) break;
+      if (m[i] != -1 && (m[i] < 0 || m[i] >= a.n || m[i] == v || mm[i] != (int)v)) err |= kCErrMate;
+      reps += (m[i] == -1 || v < m[i]) ? 1 : 0;
+      if (r1[i] < r0[i] || (v == 0 && r0[i] != 0) || (v == a.n - 1 && r1[i] != a.nnz)) err |= kCErrRowPtr;
+      if (a.vstart && r0[i] >= 0 && r1[i] >= r0[i] && r1[i] <= a.nnz) {
+        const long long c0 = r0[i] + (long long)kCCost * v, c1 = r1[i] + (long long)kCCost * (v + 1);
+        for (long long r = c0 / a.per_wg + 1; r * a.per_wg <= c1 && r <= a.ranges; ++r) a.vstart[r] = (int)(v + 1);
+        if (v == 0) a.vstart[0] = 0;
+      }
+    }
   }
   long long total;
   (void)block_excl_sum<long long>(reps, sm, total);
@@ -175,42 +201,6 @@ __global__ __launch_bounds__(kCTopThreads) void k_c_scan_top(long long* v, long 
     carry += t;
   }
   if (threadIdx.x == 0) *total = carry;
-}
-
-// In-place exclusive scan of a long array in three steps: per-workgroup sums
-// of kSBlock consecutive values (k_c_scan_sums), the one-workgroup scan of
-// those sums (k_c_scan_top), and each workgroup's scan from its prefix
-// (k_c_scan_apply). A lane takes kSI consecutive values.
-constexpr int kSI = 8;
-constexpr int kSBlock = kBlock * kSI;
-
-__global__ __launch_bounds__(kBlock) void k_c_scan_sums(const long long* v, long long m, long long* bs) {
-  __shared__ long long sm[kWaves];
-  const long long i0 = (long long)blockIdx.x * kSBlock + (long long)threadIdx.x * kSI;
-  long long x = 0;
-#pragma unroll
-  for (int j = 0; j < kSI; ++j) x += i0 + j < m ? v[i0 + j] : 0ll;
-  long long tot;
-  (void)block_excl_sum<long long>(x, sm, tot);
-  if (threadIdx.x == 0) bs[blockIdx.x] = tot;
-}
-
-__global__ __launch_bounds__(kBlock) void k_c_scan_apply(long long* v, long long m, const long long* bs) {
-  __shared__ long long sm[kWaves];
-  const long long i0 = (long long)blockIdx.x * kSBlock + (long long)threadIdx.x * kSI;
-  long long x[kSI], s = 0;
-#pragma unroll
-  for (int j = 0; j < kSI; ++j) {
-    x[j] = i0 + j < m ? v[i0 + j] : 0ll;
-    s += x[j];
-  }
-  long long tot;
-  long long run = bs[blockIdx.x] + block_excl_sum<long long>(s, sm, tot);
-#pragma unroll
-  for (int j = 0; j < kSI; ++j) {
-    if (i0 + j < m) v[i0 + j] = run;
-    run += x[j];
-  }
 }
 
 // Exclusive prefix, in index order, of the kCBlockV values a block staged in
@@ -242,14 +232,13 @@ __global__ __launch_bounds__(kBlock) void k_c_map(CArgs a) {
 #pragma unroll
   for (int i = 0; i < kCV; ++i) {
     const long long v = base + (long long)i * kBlock + threadIdx.x;
-    int m = -2, f = 0;
-    if (v < a.n) {
-      m = a.mate[v];
-      f = (m == -1 || v < m) ? 1 : 0;
-      a.cnt[v] = 0;
-    }
-    mm[i] = m;
-    val[i * kBlock + threadIdx.x] = f;
+    mm[i] = v < a.n ? a.mate[v] : -2;
+  }
+#pragma unroll
+  for (int i = 0; i < kCV; ++i) {
+    const long long v = base + (long long)i * kBlock + threadIdx.x;
+    if (v < a.n) a.cnt[v] = 0;
+    val[i * kBlock + threadIdx.x] = v < a.n && (mm[i] == -1 || v < mm[i]) ? 1 : 0;
   }
   __syncthreads();
   (void)block_stage_scan(val, a.bsum[blockIdx.x], sm);
@@ -295,11 +284,16 @@ __device__ __forceinline__ RowHead row_head(const CArgs& a, long long v) {
 }
 
 // The fine vertices [vb, ve) of workgroup blockIdx.x: ranges split by
-// entries plus kCCost per vertex.
-__device__ __forceinline__ void wg_vertices(const CArgs& a, long long per_wg, long long& vb, long long& ve, int* lb) {
+// entries plus kCCost per vertex (starts past the last crossing: none left).
+__device__ __forceinline__ void wg_vertices(const CArgs& a, long long& vb, long long& ve, int* lb) {
   const long long C = a.nnz + (long long)kCCost * a.n;
-  const long long c0 = (long long)blockIdx.x * per_wg;
-  const long long c1 = c0 + per_wg;
+  const long long c0 = (long long)blockIdx.x * a.per_wg;
+  const long long c1 = c0 + a.per_wg;
+  if (a.vstart) {
+    vb = c0 > C ? a.n : a.vstart[blockIdx.x];
+    ve = c1 >= C ? a.n : a.vstart[blockIdx.x + 1];
+    return;
+  }
   vb = c0 >= C ? a.n
                : block_lower_bound(0, a.n + 1, [&](long long v) { return a.rp[v] + (long long)kCCost * v >= c0; },
                                    lb);
@@ -308,20 +302,11 @@ __device__ __forceinline__ void wg_vertices(const CArgs& a, long long per_wg, lo
                                    lb);
 }
 
-struct GroupSmem {
-  int skey[2 * kCT];      // coarse neighbour of the slot, -1 if free
-  int shead[2 * kCT];     // last tile position inserted into the slot's list
-  int erank[kCT + 1];     // coarse neighbour, then exclusive rank among the kept entries
-  short enext[kCT];
-  short eslot[kCT];
-  unsigned char erow[kCT];
-  int st[kBlock + 1];  // chunk-local start of each row's entries; st[kBlock] = chunk total
-  int ra[kBlock], rb[kBlock], rc[kBlock], rdega[kBlock], rut[kBlock];
-  long long rka[kBlock], rkb[kBlock];
-  int wcnt[kCTI * kWaves];
-  int smi[kWaves];
-  int lb[1];
-};
+// Vertices a wave takes at a time of a range of nv: about `turns` turns a wave,
+// so that the range's rows spread over its waves, however few and long.
+__device__ __forceinline__ int wave_rows(long long nv, int turns) {
+  return (int)min(64ll, max(4ll, (nv + kWaves * turns - 1) / (kWaves * turns)));
+}
 
 // Last row r of the chunk with st[r] <= pos (rows with no tile entries share
 // their start with the next row, so r is the row that holds pos).
@@ -336,21 +321,6 @@ __device__ __forceinline__ int row_of(const int* st, int pos) {
   }
   return lo;
 }
-// Start of the first row whose start is at least t (the chunk total if none).
-__device__ __forceinline__ int start_at(const int* st, int t) {
-  if (st[0] >= t) return st[0];
-  int lo = 0, hi = kBlock;  // st[lo] < t; smallest r in (lo, kBlock] with st[r] >= t
-  while (hi - lo > 1) {
-    const int mid = (lo + hi) >> 1;
-    if (st[mid] >= t)
-      hi = mid;
-    else
-      lo = mid;
-  }
-  return st[hi];
-}
-
-// Sums the fine edges of one group in increasing (min end, max end).
 // Sums the n <= 4 fine edges of one group in increasing (min end, max end):
 // slots n..3 hold ord = ~0 and sort last; a fixed sorting network keeps every
 // index static (no dynamic register indexing).
@@ -437,12 +407,12 @@ __device__ __forceinline__ int wrow_of(const int* st, int pos) {
 // workgroup's range, lays their rows out back to back and groups them in
 // wave tiles of at most kWT entries (the same grouping as k_c_group, in the
 // wave's own LDS); ranks in row order come from the tile's ballots.
-__global__ __launch_bounds__(kBlock) void k_c_group_wave(CArgs a, long long per_wg) {
+__global__ __launch_bounds__(kBlock) void k_c_group_wave(CArgs a) {
   __shared__ WaveSmem wsm[kWaves];
   __shared__ int lb[1];
   if (a.tot->err & (kCErrMate | kCErrRowPtr)) return;
   long long vb, ve;
-  wg_vertices(a, per_wg, vb, ve, lb);
+  wg_vertices(a, vb, ve, lb);
   WaveSmem& sm = wsm[wave_id()];
   const int l = lane_id();
   for (int i = l; i < 2 * kWT; i += 64) {
@@ -451,7 +421,8 @@ __global__ __launch_bounds__(kBlock) void k_c_group_wave(CArgs a, long long per_
   }
   wave_sync();
   unsigned err = 0;
-  for (long long cb = vb + (long long)wave_id() * 64; cb < ve; cb += kBlock) {
+  const int step = wave_rows(ve - vb, 2);
+  for (long long cb = vb + (long long)wave_id() * step; cb < ve; cb += kWaves * step) {
     const long long v = cb + l;
     RowHead h;
     h.rep = false;
@@ -459,7 +430,7 @@ __global__ __launch_bounds__(kBlock) void k_c_group_wave(CArgs a, long long per_
     h.m = -1;
     h.c = h.dega = h.ub = 0;
     h.ka = h.kb = 0;
-    if (v < ve) h = row_head(a, v);
+    if (l < step && v < ve) h = row_head(a, v);
     const int ut = (h.rep && !h.lng && h.ub <= kWS) ? h.ub : 0;
     const int incl = wave_incl_sum<int>(ut);
     const int U = __shfl(incl, 63);
@@ -537,13 +508,14 @@ __global__ __launch_bounds__(kBlock) void k_c_group_wave(CArgs a, long long per_
       }
       wave_sync();
       // 2: the first entry of every group keeps it, with the group's sum
-      bool keep[kWTI];
+      bool keep[kWTI], merged[kWTI];
       float sumr[kWTI];
       unsigned long long bal[kWTI];
 #pragma unroll
       for (int i = 0; i < kWTI; ++i) {
         const int q = i * 64 + l;
         keep[i] = false;
+        merged[i] = false;
         sumr[i] = 0.f;
         if (q < len && Dr[i] >= 0) {
           int lst[kCMaxDup + 1];
@@ -562,6 +534,7 @@ __global__ __launch_bounds__(kBlock) void k_c_group_wave(CArgs a, long long per_
           if (nl > a.dup_limit) err |= kCErrDup;
           if (first && nl <= a.dup_limit) {
             keep[i] = true;
+            merged[i] = nl > 1;
             const int r = rr[i];
             if (nl == 1) {
               sumr[i] = wr[i];
@@ -623,7 +596,7 @@ __global__ __launch_bounds__(kBlock) void k_c_group_wave(CArgs a, long long per_
         }
       }
       wave_sync();
-      if (a.scr) {
+      if (a.dmap) {
 #pragma unroll
         for (int i = 0; i < kWTI; ++i) {
           const int q = i * 64 + l;
@@ -632,8 +605,10 @@ __global__ __launch_bounds__(kBlock) void k_c_group_wave(CArgs a, long long per_
           const int off = lo + q - sm.st[r];
           const bool side = off >= sm.rdega[r];
           const int own = pre[i] + (int)__popcll(bal[i] & lanemask_lt());
-          a.scr[(side ? sm.rkb[r] : sm.rka[r]) + (own - sm.rrk[r][side ? 1 : 0])] =
-              make_int2(Dr[i], __float_as_int(sumr[i]));
+          const int at = (side ? sm.rkb[r] : sm.rka[r]) + (own - sm.rrk[r][side ? 1 : 0]);
+          const bool sum = a.w != nullptr || merged[i];
+          a.dmap[at] = sum ? Dr[i] | kMerged : Dr[i];
+          if (sum) a.aux[at] = sumr[i];
         }
       }
       for (int i = l; i < 2 * len; i += 64) {
@@ -647,232 +622,215 @@ __global__ __launch_bounds__(kBlock) void k_c_group_wave(CArgs a, long long per_
   if (err) atomicOr(&a.tot->err, err);
 }
 
-// (2b) Groups the entries of every medium coarse row (kWS < bound <= kCS) in LDS and
-// keeps, compacted in place at the start of each row part, the first entry of
-// every group with the group's sum; sets the parts' kept counts. Queues the
-// long rows.
-__global__ __launch_bounds__(kBlock) void k_c_group(CArgs a, long long per_wg) {
-  __shared__ GroupSmem sm;
-  if (a.tot->err & (kCErrMate | kCErrRowPtr)) return;
-  const int tid = threadIdx.x;
-  const int wv_id = wave_id();
-  long long vb, ve;
-  wg_vertices(a, per_wg, vb, ve, sm.lb);
-  for (int i = tid; i < 2 * kCT; i += kBlock) {
-    sm.skey[i] = -1;
-    sm.shead[i] = -1;
+// A slot of an LDS set of coarse neighbours: the neighbour in the low word; in
+// the high word the row position of its first entry in with kEnd, or, once
+// more entries named it, the position of the last of them (positions link
+// back to the one with kEnd). A group that was merged: the summed weight's
+// bits, and the first position in row order.
+constexpr unsigned long long kFree = ~0ull;
+constexpr unsigned kEnd = 0x80000000u;
+__device__ __forceinline__ unsigned long long set_slot(int D, unsigned pos) {
+  return ((unsigned long long)pos << 32) | (unsigned)D;
+}
+__device__ __forceinline__ unsigned* slot_pos(unsigned long long* slot) { return reinterpret_cast<unsigned*>(slot) + 1; }
+
+// The coarse edge whose fine edges are the row's entries at positions
+// lst[0..nl): the sum of their weights in edge order, and the first position.
+// Entry e < dega of the row is fine entry ka + e of vertex va, the others
+// kb + (e - dega) of vb.
+__device__ __forceinline__ float merge_group(const CArgs& a, const int* lst, int nl, int va, int vb, int dega, int ka,
+                                             int kb, int& first) {
+  unsigned long long ord[kCMaxDup];
+  float wg[kCMaxDup];
+  first = lst[0];
+#pragma unroll
+  for (int t = 0; t < kCMaxDup; ++t) {
+    ord[t] = ~0ull;
+    wg[t] = 0.f;
+    if (t >= nl) continue;
+    first = min(first, lst[t]);
+    const bool side = lst[t] >= dega;
+    const int k = side ? kb + (lst[t] - dega) : ka + lst[t];
+    ord[t] = edge_order(side ? vb : va, a.col[k]);
+    wg[t] = a.w ? a.w[k] : 1.0f;
   }
+  return group_sum(ord, wg, nl);
+}
+
+constexpr int kMSlots = 2 * kCS;
+constexpr int kMI = kCS / 64;  // entries per lane
+
+struct MidSmem {
+  unsigned long long tab[kMSlots];
+  unsigned short next[kCS];     // link of a position, with 0x8000 at the end
+  unsigned short grp[kCS / 2];  // slots with more than one entry
+  int ngrp;
+};
+
+// (2b) Merges every medium coarse row (kWS < bound <= kCS), one wave a row: an
+// entry enters its coarse neighbour into a set in LDS by one compare-and-swap,
+// which also tells whether it is the first; only neighbours named more than
+// once (few, in graphs with such rows) are linked, walked and summed. The
+// kept entries are compacted at the start of each row part. Queues the long
+// rows. What bounds it is the gather of cmap: eight of a lane's are in flight
+// at once, and nothing waits on a workgroup barrier.
+__global__ __launch_bounds__(kBlock) void k_c_group_mid(CArgs a) {
+  __shared__ MidSmem wsm[kWaves];
+  __shared__ int lb[1];
+  if (a.tot->err & (kCErrMate | kCErrRowPtr)) return;
+  long long vb, ve;
+  wg_vertices(a, vb, ve, lb);
+  MidSmem& sm = wsm[wave_id()];
+  const int l = lane_id();
+  for (int i = l; i < kMSlots; i += 64) sm.tab[i] = kFree;
+  if (l == 0) sm.ngrp = 0;
+  wave_sync();
   unsigned err = 0;
-  for (long long cb = vb; cb < ve; cb += kBlock) {
-    const long long v = cb + tid;
+  const int step = wave_rows(ve - vb, 4);
+  for (long long cb = vb + (long long)wave_id() * step; cb < ve; cb += kWaves * step) {
+    const long long v = cb + l;
     RowHead h;
     h.rep = false;
     h.lng = false;
     h.m = -1;
     h.c = h.dega = h.ub = 0;
     h.ka = h.kb = 0;
-    if (v < ve) {
-      h = row_head(a, v);
+    if (l < step && v < ve) h = row_head(a, v);
+    const unsigned long long lng = __ballot(h.rep && h.lng);
+    if (lng) {
+      unsigned long long base = 0;
+      if (l == 0) base = atomicAdd((unsigned long long*)&a.tot->nlong, (unsigned long long)__popcll(lng));
+      base = (unsigned long long)__shfl((long long)base, 0);
       if (h.rep && h.lng) {
-        const unsigned long long idx = atomicAdd((unsigned long long*)&a.tot->nlong, 1ull);
+        const unsigned long long idx = base + (unsigned long long)__popcll(lng & lanemask_lt());
         if ((long long)idx < a.lrow_cap) {
           LongRow L;
+          std::memset(&L, 0, sizeof(L));
           L.a = (int)v;
           L.b = h.m;
           L.c = h.c;
           L.dega = h.dega;
           L.ub = h.ub;
-          L.tbits = 0;
-          L.eoff = 0;
-          L.toff = 0;
           a.lrows[idx] = L;
         }
       }
     }
-    const int ut = (h.rep && !h.lng && h.ub > kWS) ? h.ub : 0;  // shorter rows: k_c_group_wave
-    int U;
-    const int st = block_excl_sum<int>(ut, sm.smi, U);
-    sm.st[tid] = st;
-    if (tid == 0) sm.st[kBlock] = U;
-    sm.ra[tid] = (int)v;
-    sm.rb[tid] = h.m;
-    sm.rc[tid] = h.c;
-    sm.rdega[tid] = h.dega;
-    sm.rut[tid] = ut;
-    sm.rka[tid] = h.ka;
-    sm.rkb[tid] = h.kb;
-    __syncthreads();
-    const int ntile = (U + kCStep - 1) / kCStep;
-    for (int j = 0; j < ntile; ++j) {
-      const int lo = start_at(sm.st, j * kCStep);
-      const int hi = start_at(sm.st, (j + 1) * kCStep);
-      const int len = hi - lo;
-      if (len <= 0) continue;  // uniform across the workgroup
-      int Dr[kCTI], xr[kCTI];
-      float wr[kCTI];
-      // 1: load every entry of the lane, then map them all, then insert (the
-      // loads of all rounds are in flight together)
-      int rr[kCTI];
-      long long kr[kCTI];
+    unsigned long long rows = __ballot(h.rep && !h.lng && h.ub > kWS);
+    while (rows) {
+      const int src = __ffsll((long long)rows) - 1;
+      rows &= rows - 1;
+      const int va = (int)(cb + src), vbm = __builtin_amdgcn_readlane(h.m, src);
+      const int c = __builtin_amdgcn_readlane(h.c, src), dega = __builtin_amdgcn_readlane(h.dega, src);
+      const int ub = __builtin_amdgcn_readlane(h.ub, src);
+      const int ka = __builtin_amdgcn_readlane((int)h.ka, src), kb = __builtin_amdgcn_readlane((int)h.kb, src);
+      int x[kMI], D[kMI], slot[kMI];
+      // every entry's neighbour, then its coarse one
 #pragma unroll
-      for (int i = 0; i < kCTI; ++i) {
-        const int q = i * kBlock + tid;
-        rr[i] = 0;
-        kr[i] = -1;
-        Dr[i] = -1;
-        xr[i] = 0;
-        wr[i] = 0.f;
-        if (q < len) {
-          const int pos = lo + q;
-          const int r = row_of(sm.st, pos);
-          const int off = pos - sm.st[r];
-          const bool side = off >= sm.rdega[r];
-          rr[i] = r;
-          kr[i] = side ? sm.rkb[r] + (off - sm.rdega[r]) : sm.rka[r] + off;
-          sm.erow[q] = (unsigned char)r;
+      for (int i = 0; i < kMI; ++i) {
+        x[i] = -1;
+        if (i * 64 < ub) {
+          const int e = i * 64 + l;
+          if (e < ub) x[i] = a.col[e < dega ? ka + e : kb + (e - dega)];
         }
       }
 #pragma unroll
-      for (int i = 0; i < kCTI; ++i) {
-        if (kr[i] < 0) continue;
-        xr[i] = a.col[kr[i]];
-        wr[i] = a.w ? a.w[kr[i]] : 1.0f;
+      for (int i = 0; i < kMI; ++i) {
+        D[i] = -1;
+        if (i * 64 < ub) {
+          const int e = i * 64 + l;
+          if (e < ub) {
+            if ((unsigned)x[i] >= (unsigned)a.n)
+              err |= kCErrCol;
+            else
+              D[i] = a.identity ? x[i] : a.cmap[x[i]];
+          }
+        }
       }
+      const int shift = ub <= 256 ? 23 : 22;  // 512 or 1024 slots: at most half of them taken
+      const unsigned mask = (1u << (32 - shift)) - 1u;
 #pragma unroll
-      for (int i = 0; i < kCTI; ++i) {
-        if (kr[i] < 0) continue;
-        if ((unsigned)xr[i] >= (unsigned)a.n)
-          err |= kCErrCol;
-        else
-          Dr[i] = a.identity ? xr[i] : a.cmap[xr[i]];
-      }
-#pragma unroll
-      for (int i = 0; i < kCTI; ++i) {
-        const int q = i * kBlock + tid;
-        const int r = rr[i];
-        if (kr[i] < 0) continue;
-        if (Dr[i] == sm.rc[r]) Dr[i] = -1;
-        const int D = Dr[i];
-        if (D >= 0) {
-          // the row's own slots: 2 * (its bound) of them from 2 * (its tile start)
-          const unsigned sb = 2u * (unsigned)(sm.st[r] - lo);
-          const unsigned range = 2u * (unsigned)sm.rut[r];
-          unsigned hh = (unsigned)(((unsigned long long)((unsigned)D * 0x9E3779B1u) * range) >> 32);
+      for (int i = 0; i < kMI; ++i) {
+        slot[i] = 0;
+        if (D[i] == c) D[i] = -1;
+        if (i * 64 < ub && D[i] >= 0) {
+          const unsigned e = (unsigned)(i * 64 + l);
+          unsigned hh = ((unsigned)D[i] * 0x9E3779B1u) >> shift;
           for (;;) {
-            const int old = atomicCAS(&sm.skey[sb + hh], -1, D);
-            if (old == -1 || old == D) break;
-            hh = hh + 1 == range ? 0u : hh + 1;
+            const unsigned long long old = atomicCAS(&sm.tab[hh], kFree, set_slot(D[i], e | kEnd));
+            if (old == kFree) break;
+            if ((int)(unsigned)old == D[i]) {
+              const unsigned prev = atomicExch(slot_pos(&sm.tab[hh]), e);
+              sm.next[e] = (unsigned short)((prev & 0x7fffu) | (prev >> 31 << 15));
+              if (prev & kEnd) sm.grp[atomicAdd(&sm.ngrp, 1)] = (unsigned short)hh;
+              break;
+            }
+            hh = (hh + 1u) & mask;
           }
-          sm.eslot[q] = (short)(sb + hh);
-          sm.enext[q] = (short)atomicExch(&sm.shead[sb + hh], q);
+          slot[i] = (int)hh;
         }
       }
-      __syncthreads();
-      // 2: the first entry of every group keeps it, with the group's sum
-      bool keep[kCTI];
-      float sumr[kCTI];
+      wave_sync();
+      const int ng = __builtin_amdgcn_readfirstlane(sm.ngrp);
+      for (int q = l; q < ng; q += 64) {
+        const int hs = sm.grp[q];
+        int lst[kCMaxDup];
+        int nl = 0;
+        unsigned p = (unsigned)(sm.tab[hs] >> 32);
 #pragma unroll
-      for (int i = 0; i < kCTI; ++i) {
-        const int q = i * kBlock + tid;
-        keep[i] = false;
-        sumr[i] = 0.f;
-        if (q < len && Dr[i] >= 0) {
-          int lst[kCMaxDup + 1];
-          int nl = 0;
-          int p = sm.shead[sm.eslot[q]];
-          bool first = true;
+        for (int t = 0; t < kCMaxDup; ++t) {  // static indices
+          if (p != ~0u) {
+            lst[t] = (int)(p & 0x7fffu);
+            nl = t + 1;
+            p = (p & 0x8000u) ? ~0u : sm.next[p & 0x7fffu];
+          }
+        }
+        if (p != ~0u || nl > a.dup_limit) err |= kCErrDup;
+        int first;
+        const float sum = merge_group(a, lst, nl, va, vbm, dega, ka, kb, first);
+        sm.tab[hs] = ((unsigned long long)(unsigned)first << 32) | __float_as_uint(sum);
+      }
+      wave_sync();
+      // ranks in row order, and the kept entries
+      int before = 0, acnt = 0;
 #pragma unroll
-          for (int t = 0; t <= kCMaxDup; ++t) {  // static indices: at most five nodes matter
-            if (p >= 0) {
-              lst[t] = p;
-              nl = t + 1;
-              first = first && p >= q;
-              p = sm.enext[p];
+      for (int i = 0; i < kMI; ++i) {
+        if (i * 64 < ub) {
+          const int e = i * 64 + l;
+          bool keep = D[i] >= 0, sum = false;
+          float wk = 1.0f;
+          if (keep && ng) {
+            const unsigned long long t = sm.tab[slot[i]];
+            if (!((unsigned)(t >> 32) & kEnd)) {
+              keep = (int)(t >> 32) == e;
+              sum = keep;
+              wk = __uint_as_float((unsigned)t);
             }
           }
-          if (nl > a.dup_limit) err |= kCErrDup;
-          if (first && nl <= a.dup_limit) {
-            keep[i] = true;
-            const int r = sm.erow[q];
-            if (nl == 1) {
-              sumr[i] = wr[i];
-            } else {
-              unsigned long long ord[kCMaxDup];
-              float wg[kCMaxDup];
-#pragma unroll
-              for (int t = 0; t < kCMaxDup; ++t) {
-                ord[t] = ~0ull;
-                wg[t] = 0.f;
-                if (t >= nl) continue;
-                const int pp = lst[t];
-                const int off = lo + pp - sm.st[r];
-                const bool side = off >= sm.rdega[r];
-                const int s = side ? sm.rb[r] : sm.ra[r];
-                int xp = xr[i];
-                float wp = wr[i];
-                if (pp != q) {
-                  const long long kp = side ? sm.rkb[r] + (off - sm.rdega[r]) : sm.rka[r] + off;
-                  xp = a.col[kp];
-                  wp = a.w ? a.w[kp] : 1.0f;
-                }
-                ord[t] = edge_order(s, xp);
-                wg[t] = wp;
-              }
-              sumr[i] = group_sum(ord, wg, nl);
-            }
+          const unsigned long long bal = __ballot(keep);
+          const int own = before + (int)__popcll(bal & lanemask_lt());
+          // kept entries of a's part in this round
+          const int split = dega - i * 64;
+          acnt += split >= 64 ? (int)__popcll(bal) : split > 0 ? (int)__popcll(bal & ((1ull << split) - 1ull)) : 0;
+          if (keep && a.dmap) {
+            const int at = e < dega ? ka + own : kb + (own - acnt);
+            if (a.w && !sum) wk = a.w[e < dega ? ka + e : kb + (e - dega)];
+            sum = sum || a.w;
+            a.dmap[at] = sum ? D[i] | kMerged : D[i];
+            if (sum) a.aux[at] = wk;
           }
+          before += (int)__popcll(bal);
         }
-        const unsigned long long bal = __ballot(keep[i]);
-        if (lane_id() == 0) sm.wcnt[i * kWaves + wv_id] = __popcll(bal);
-        sm.erank[q] = (int)__popcll(bal & lanemask_lt());  // rank inside the wave for now
       }
-      __syncthreads();
-      // 3: exclusive ranks in tile order: the kept counts of the (round, wave)
-      // groups are scanned across the wave's lanes, each lane takes its groups'
-      {
-        static_assert(kCTI * kWaves <= 64, "one lane per (round, wave) group");
-        const int l = lane_id();
-        const int cg = l < kCTI * kWaves ? sm.wcnt[l] : 0;
-        const int incl = wave_incl_sum<int>(cg);
-        const int excl = incl - cg;
-        const int tot = __shfl(incl, kCTI * kWaves - 1);
+      if (l == 0 && a.cnt) {
+        a.cnt[va] = acnt;
+        if (vbm >= 0) a.cnt[vbm] = before - acnt;
+      }
+      wave_sync();
 #pragma unroll
-        for (int i = 0; i < kCTI; ++i) {
-          const int q = i * kBlock + tid;
-          sm.erank[q] += __shfl(excl, i * kWaves + wv_id);
-        }
-        if (tid == 0) sm.erank[kCT] = tot;
-      }
-      __syncthreads();
-      // 4: write the kept entries at the start of their row part; part counts
-#pragma unroll
-      for (int i = 0; i < kCTI; ++i) {
-        const int q = i * kBlock + tid;
-        if (q >= len || !keep[i] || !a.scr) continue;
-        const int r = sm.erow[q];
-        const int off = lo + q - sm.st[r];
-        const bool side = off >= sm.rdega[r];
-        const int ps = sm.st[r] - lo + (side ? sm.rdega[r] : 0);
-        const int prank = sm.erank[q] - sm.erank[ps];
-        a.scr[(side ? sm.rkb[r] : sm.rka[r]) + prank] = make_int2(Dr[i], __float_as_int(sumr[i]));
-      }
-      {
-        const int r = tid;
-        const int s0 = sm.st[r] - lo;
-        if (a.cnt && sm.rut[r] > 0 && sm.st[r] >= lo && sm.st[r] < hi) {
-          const int pb = s0 + sm.rdega[r];
-          const int pe = s0 + sm.rut[r];
-          const int rb_ = pe < len ? sm.erank[pe] : sm.erank[kCT];
-          const int ra_ = pb < len ? sm.erank[pb] : sm.erank[kCT];
-          a.cnt[sm.ra[r]] = ra_ - sm.erank[s0];
-          if (sm.rb[r] >= 0) a.cnt[sm.rb[r]] = rb_ - ra_;
-        }
-      }
-      for (int i = tid; i < 2 * len; i += kBlock) {
-        sm.skey[i] = -1;
-        sm.shead[i] = -1;
-      }
-      __syncthreads();
+      for (int i = 0; i < kMI; ++i)
+        if (D[i] >= 0) sm.tab[slot[i]] = kFree;
+      if (l == 0) sm.ngrp = 0;
+      wave_sync();
     }
   }
   if (err) atomicOr(&a.tot->err, err);
@@ -880,7 +838,7 @@ __global__ __launch_bounds__(kBlock) void k_c_group(CArgs a, long long per_wg) {
 
 // (4d) Copies the kept entries of every short coarse row from the starts of
 // its two row parts to the output.
-__global__ __launch_bounds__(kBlock) void k_c_copy(CArgs a, long long per_wg) {
+__global__ __launch_bounds__(kBlock) void k_c_copy(CArgs a) {
   __shared__ int pre[kBlock + 1];
   __shared__ int sca[kBlock];
   __shared__ long long ska[kBlock], skb[kBlock], sd0[kBlock];
@@ -889,7 +847,7 @@ __global__ __launch_bounds__(kBlock) void k_c_copy(CArgs a, long long per_wg) {
   if (a.tot->err) return;
   const int tid = threadIdx.x;
   long long vb, ve;
-  wg_vertices(a, per_wg, vb, ve, lb);
+  wg_vertices(a, vb, ve, lb);
   for (long long cb = vb; cb < ve; cb += kBlock) {
     const long long v = cb + tid;
     int len = 0, ca = 0;
@@ -917,53 +875,75 @@ __global__ __launch_bounds__(kBlock) void k_c_copy(CArgs a, long long per_wg) {
       const int r = row_of(pre, q);
       const int off = q - pre[r];
       const long long src = off < sca[r] ? ska[r] + off : skb[r] + (off - sca[r]);
-      const int2 t = a.scr[src];
-      a.ccol[sd0[r] + off] = t.x;
-      a.cw[sd0[r] + off] = __int_as_float(t.y);
+      const int t = a.dmap[src];
+      a.ccol[sd0[r] + off] = t & ~kMerged;
+      a.cw[sd0[r] + off] = t < 0 ? a.aux[src] : 1.0f;
     }
     __syncthreads();
   }
 }
 
 // (3a') Sizes of the long rows: entries (their bound), table slots (the
-// power of two at least twice the bound), buckets and chunks, and the
-// offsets of each in row order. Workgroup g sums kLPRows rows
-// (k_c_long_sums), one scan over the workgroup sums per quantity gives the
-// totals (k_c_scan_top), and each workgroup writes its rows' offsets from its
-// prefix (k_c_long_offs). The grid covers the row capacity; workgroups past
-// the long rows counted write zero sums.
+// power of two at least twice the bound), whether one small workgroup merges
+// the row, parts and chunks, and the offsets of each in row order. Workgroup
+// g sums kLPRows rows (k_c_long_sums), one scan over the workgroup sums per
+// quantity gives the totals (k_c_scan_top), and each workgroup writes its
+// rows' offsets from its prefix (k_c_long_offs). The grid covers the row
+// capacity; workgroups past the long rows counted write zero sums.
 constexpr int kLP = 4;                 // long rows per lane in the prep kernels
 constexpr int kLPRows = kBlock * kLP;  // long rows per workgroup
+constexpr int kLQ = 4;                 // quantities
 
-__device__ __forceinline__ void long_row_sizes(long long ub, int& bits, long long v[4]) {
+__device__ __forceinline__ void long_row_sizes(long long ub, int& bits, int& nb, int& np, long long v[kLQ]) {
   const long long t = 2 * ub;
   bits = t <= 2 ? 1 : 64 - __clzll((unsigned long long)(t - 1));  // smallest bits >= 1 with 2^bits >= 2 ub
+  nb = (int)((ub + kLB - 1) / kLB);
+  np = nb <= kLSmall ? 0 : (nb + kLPart - 1) / kLPart;
   v[0] = ub;
   v[1] = 1ll << bits;
-  v[2] = (ub + kLB - 1) / kLB;
+  v[2] = np == 0 ? 1 : (long long)np << 32;  // (each sum is below 2^31)
   v[3] = (ub + kLC - 1) / kLC;
 }
 
 __global__ __launch_bounds__(kBlock) void k_c_long_sums(CArgs a, long long* lsum, long long nblk) {
   __shared__ long long sm[kWaves];
   const long long nl = a.tot->err ? 0 : (a.tot->nlong < a.lrow_cap ? a.tot->nlong : a.lrow_cap);
-  long long su[4] = {0, 0, 0, 0};
+  long long su[kLQ] = {0, 0, 0, 0};
   const long long i0 = (long long)blockIdx.x * kLPRows + (long long)threadIdx.x * kLP;
 #pragma unroll
   for (int j = 0; j < kLP; ++j) {
     if (i0 + j >= nl) continue;
-    int bits;
-    long long v[4];
-    long_row_sizes(a.lrows[i0 + j].ub, bits, v);
+    int bits, nb, np;
+    long long v[kLQ];
+    long_row_sizes(a.lrows[i0 + j].ub, bits, nb, np, v);
 #pragma unroll
-    for (int q = 0; q < 4; ++q) su[q] += v[q];
+    for (int q = 0; q < kLQ; ++q) su[q] += v[q];
   }
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
+  for (int q = 0; q < kLQ; ++q) {
     long long tot;
     (void)block_excl_sum<long long>(su[q], sm, tot);
     if (threadIdx.x == 0) lsum[q * nblk + blockIdx.x] = tot;
   }
+}
+
+// Exclusive scans of the kLQ arrays of workgroup sums, one workgroup each.
+__global__ __launch_bounds__(kCTopThreads) void k_c_long_top(long long* lsum, long long nblk, CTot* tot) {
+  __shared__ long long sm[kCTopThreads / 64];
+  long long* v = lsum + (long long)blockIdx.x * nblk;
+  long long carry = 0;
+  for (long long base = 0; base < nblk; base += kCTopThreads) {
+    const long long i = base + threadIdx.x;
+    const long long x = i < nblk ? v[i] : 0ll;
+    long long t;
+    const long long e = top_excl_sum(x, sm, t);
+    if (i < nblk) v[i] = carry + e;
+    carry += t;
+  }
+  long long* total[kLQ] = {&tot->long_entries, &tot->long_slots, &tot->long_items, &tot->long_chunks};
+#pragma unroll
+  for (int q = 0; q < kLQ; ++q)
+    if (threadIdx.x == 0 && blockIdx.x == q) *total[q] = carry;
 }
 
 __global__ __launch_bounds__(kBlock) void k_c_long_offs(CArgs a, const long long* lsum, long long nblk) {
@@ -972,21 +952,22 @@ __global__ __launch_bounds__(kBlock) void k_c_long_offs(CArgs a, const long long
   const long long nl = a.tot->nlong < a.lrow_cap ? a.tot->nlong : a.lrow_cap;
   if ((long long)blockIdx.x * kLPRows >= nl) return;  // (uniform)
   const long long i0 = (long long)blockIdx.x * kLPRows + (long long)threadIdx.x * kLP;
-  int bits[kLP];
-  long long v[kLP][4];
-  long long su[4] = {0, 0, 0, 0};
+  int bits[kLP], nb[kLP], np[kLP];
+  long long v[kLP][kLQ];
+  long long su[kLQ] = {0, 0, 0, 0};
 #pragma unroll
   for (int j = 0; j < kLP; ++j) {
     bits[j] = 1;
+    nb[j] = np[j] = 0;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) v[j][q] = 0;
-    if (i0 + j < nl) long_row_sizes(a.lrows[i0 + j].ub, bits[j], v[j]);
+    for (int q = 0; q < kLQ; ++q) v[j][q] = 0;
+    if (i0 + j < nl) long_row_sizes(a.lrows[i0 + j].ub, bits[j], nb[j], np[j], v[j]);
 #pragma unroll
-    for (int q = 0; q < 4; ++q) su[q] += v[j][q];
+    for (int q = 0; q < kLQ; ++q) su[q] += v[j][q];
   }
-  long long off[4];
+  long long off[kLQ];
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
+  for (int q = 0; q < kLQ; ++q) {
     long long tot;
     off[q] = lsum[q * nblk + blockIdx.x] + block_excl_sum<long long>(su[q], sm, tot);
   }
@@ -997,12 +978,25 @@ __global__ __launch_bounds__(kBlock) void k_c_long_offs(CArgs a, const long long
       L.eoff = off[0];
       L.toff = off[1];
       L.tbits = bits[j];
-      L.nb = (int)v[j][2];
-      L.boff = off[2];
+      L.nb = nb[j];
+      L.np = np[j];
+      L.soff = (int)(off[2] & 0x7fffffffll);
+      L.boff = (int)(off[2] >> 32);
       L.coff = off[3];
     }
 #pragma unroll
-    for (int q = 0; q < 4; ++q) off[q] += v[j][q];
+    for (int q = 0; q < kLQ; ++q) off[q] += v[j][q];
+  }
+}
+
+// The long row of every small row, part and chunk.
+__global__ __launch_bounds__(kBlock) void k_c_long_tables(CArgs a, long long nl) {
+  for (long long r = (long long)blockIdx.x * kBlock + threadIdx.x; r < nl; r += (long long)gridDim.x * kBlock) {
+    const LongRow L = a.lrows[r];
+    if (L.np == 0) a.srow[L.soff] = (int)r;
+    for (int p = 0; p < L.np; ++p) a.prow[L.boff + p] = (int)r;
+    const int nc = (L.ub + kLC - 1) / kLC;
+    for (int j = 0; j < nc; ++j) a.crow[L.coff + j] = (int)r;
   }
 }
 
@@ -1144,7 +1138,7 @@ __global__ __launch_bounds__(kBlock) void k_c_long_keep(CArgs a, long long nl, l
     for (int j = 0; j < kLI; ++j) {
       if (at[j].k < 0) continue;
       if (D[j] < 0) {
-        if (a.scr) a.scr[at[j].k] = make_int2(-1, 0);
+        if (a.dmap) a.dmap[at[j].k] = -1;
         continue;
       }
       const LongRow& L = a.lrows[at[j].r];
@@ -1168,9 +1162,9 @@ __global__ __launch_bounds__(kBlock) void k_c_long_keep(CArgs a, long long nl, l
         if (p >= 0 && t < kCMaxDup) pn = a.next[p];
       }
       if (nlst > a.dup_limit) err |= kCErrDup;
-      if (!a.scr) continue;
+      if (!a.dmap) continue;
       if (!first || nlst > a.dup_limit) {
-        a.scr[at[j].k] = make_int2(-1, 0);
+        a.dmap[at[j].k] = -1;
         continue;
       }
       float sum = wself[j];
@@ -1191,347 +1185,252 @@ __global__ __launch_bounds__(kBlock) void k_c_long_keep(CArgs a, long long nl, l
         }
         sum = group_sum(ord, wv, nlst);
       }
-      a.scr[at[j].k] = make_int2(D[j], __float_as_int(sum));
-      atomicAdd(&a.cnt[at[j].side ? L.b : L.a], 1);
+      a.dmap[at[j].k] = nlst > 1 ? D[j] | kMerged : D[j];
+      if (nlst > 1) a.aux[at[j].k] = sum;
+      atomicAdd(&a.cnt[L.a], 1);
+      atomicAdd(&a.ccnt[L.coff + at[j].off / kLC], 1);
     }
   }
   if (err) atomicOr(&a.tot->err, err);
 }
 
-// ---- long rows through LDS buckets: every entry of a long row goes to one
-// of the row's buckets by a hash of its coarse neighbour (so a group never
-// spans buckets), the entries are sorted by bucket (counts, scan, scatter of
-// fine entry indices), and one workgroup groups each bucket in LDS.
+// ---- long rows: the coarse neighbours of a row are split into buckets by a
+// hash, each with a set of kLBCap slots in LDS (a group never spans buckets).
+// A row of at most kLSmall buckets is merged by one workgroup of kBlock lanes,
+// one of at most kLPart by one of kLBig lanes, in one reading of its entries.
+// A longer row is mapped first (its coarse neighbours into dmap, by chunks), and
+// each part of kLPart buckets then streams the whole row's dmap, taking its
+// own: 4 bytes an entry and part from the caches instead of a sort by bucket.
 
-__device__ __forceinline__ long long bucket_of(const LongRow& L, int D) {
-  return L.boff + (long long)(((unsigned long long)((unsigned)D * 0x9E3779B1u) * (unsigned)L.nb) >> 32);
+__device__ __forceinline__ unsigned bucket_of(const LongRow& L, int D) {
+  return (unsigned)(((unsigned long long)((unsigned)D * 0x9E3779B1u) * (unsigned)L.nb) >> 32);
 }
 
-struct ChunkSmem {
-  int hist[kLHist];      // per bucket of the row: entries of the chunk, then their first record
-  unsigned erec[kLC];    // per chunk entry: bucket << 13 | rank in the bucket within the chunk
-  int row;
-  int lb;
-};
-static_assert(kLC <= (1 << 13) && kLHist <= (1 << 19), "bucket and rank fit the packed word");
-
-// Workgroup g of G takes the contiguous items [m g / G, m (g + 1) / G) (chunks
-// or buckets, in row order), so the row of each item is found by walking on
-// from the row of the one before (one step at most, mostly none); the first
-// item's row comes from one 256-way search over the long rows. Every lane
-// calls it.
-template <typename Off>
-__device__ __forceinline__ long long first_item_row(long long nl, long long c0, Off off, int* sm) {
-  return block_lower_bound(0, nl, [&](long long i) { return off(i) > c0; }, sm) - 1;  // largest off <= c0
-}
-
-// (3b') Maps every long-row entry (its coarse neighbour into next[k], -1 for
-// the matched edge, whose output is written as dropped now) and counts the
-// buckets. A workgroup takes a chunk of kLC entries of one row at a time and
-// counts in LDS, so each (chunk, bucket) costs one device atomic (rows with
-// more than kLHist buckets count straight in device memory).
-__global__ __launch_bounds__(kBlock) void k_c_lb_count(CArgs a, long long nl, long long nchunks) {
-  struct CountSmem {
-    int hist[kLHist];
-    int row;
-  };
-  __shared__ CountSmem sm;
+// Maps the rows of several parts: their coarse neighbours into dmap (-1 for
+// the matched edge), the kept counts of their chunks.
+__global__ __launch_bounds__(kBlock) void k_c_long_map(CArgs a) {
+  __shared__ int smi[kWaves];
   unsigned err = 0;
   const int tid = threadIdx.x;
-  // chunks taken in strides: those of rows counted in device memory come in
-  // runs, which contiguous ranges would leave to a few workgroups
-  for (long long c = blockIdx.x; c < nchunks; c += gridDim.x) {
-    if (tid == 0) {  // the row: largest coff <= c
-      long long lo = 0, hi = nl;
-      while (hi - lo > 1) {
-        const long long mid = (lo + hi) >> 1;
-        if (a.lrows[mid].coff <= c)
-          lo = mid;
-        else
-          hi = mid;
-      }
-      sm.row = (int)lo;
+  const long long c = blockIdx.x;
+  const LongRow L = a.lrows[a.crow[c]];
+  if (L.np <= 1) return;  // (uniform) mapped while it is merged
+  const int e0 = (int)(c - L.coff) * kLC;
+  const int ne = min(kLC, L.ub - e0);
+  const int ka = (int)a.rp[L.a], kb = L.b >= 0 ? (int)a.rp[L.b] : 0;
+  int kept = 0;
+  constexpr int kI = 8;
+  for (int q0 = 0; q0 < ne; q0 += kBlock * kI) {
+    int k[kI], x[kI];
+#pragma unroll
+    for (int j = 0; j < kI; ++j) {
+      const int q = q0 + j * kBlock + tid, e = e0 + q;
+      k[j] = q < ne ? (e < L.dega ? ka + e : kb + (e - L.dega)) : -1;
+      x[j] = k[j] >= 0 ? a.col[k[j]] : -1;
     }
-    __syncthreads();
-    const LongRow L = a.lrows[sm.row];
-    const bool lds = L.nb <= kLHist;
-    if (lds)
-      for (int i = tid; i < L.nb; i += kBlock) sm.hist[i] = 0;
-    __syncthreads();
-    const long long e0 = (c - L.coff) * kLC;
-    const int ne = (int)min((long long)kLC, (long long)L.ub - e0);
-    const long long ka = a.rp[L.a];
-    const long long kb = L.b >= 0 ? a.rp[L.b] : 0;
-    for (int q0 = 0; q0 < ne; q0 += kBlock * kLI) {
-      long long k[kLI];
-      int x[kLI];
 #pragma unroll
-      for (int j = 0; j < kLI; ++j) {
-        const int q = q0 + j * kBlock + tid;
-        const long long off = e0 + q;
-        k[j] = q < ne ? (off < L.dega ? ka + off : kb + (off - L.dega)) : -1;
-      }
+    for (int j = 0; j < kI; ++j) {
+      if (k[j] < 0) continue;
+      int D = -1;
+      if ((unsigned)x[j] >= (unsigned)a.n)
+        err |= kCErrCol;
+      else
+        D = a.cmap[x[j]];
+      x[j] = D == L.c ? -1 : D;
+    }
 #pragma unroll
-      for (int j = 0; j < kLI; ++j) x[j] = k[j] >= 0 ? a.col[k[j]] : -1;
+    for (int j = 0; j < kI; ++j) {
+      if (k[j] < 0) continue;
+      a.dmap[k[j]] = x[j];
+      kept += x[j] >= 0 ? 1 : 0;
+    }
+  }
+  int tot;
+  (void)block_excl_sum<int>(kept, smi, tot);
+  if (tid == 0) {
+    a.ccnt[c] = tot;
+    atomicAdd(&a.cnt[L.a], tot);
+  }
+  if (err) atomicOr(&a.tot->err, err);
+}
+
+// Merges a row (or one part of it), one workgroup each: LANES lanes, NB buckets.
+template <int LANES, int NB>
+struct LongSmem {
+  unsigned long long tab[NB * kLBCap];
+  unsigned short grp[NB * kLBCap / 2];  // slots with more than one entry
+  int ngrp, kept;
+};
+
+template <int LANES, int NB>
+__global__ __launch_bounds__(LANES, LANES == kLBig ? 8 : 4) void k_c_long_group(CArgs a, int np) {
+  __shared__ LongSmem<LANES, NB> sm;
+  constexpr int kI = LANES == kLBig ? 8 : 4;
+  constexpr int kGrp = NB * kLBCap / 2;
+  const int tid = threadIdx.x;
+  unsigned err = 0;
+  // (a launch of the wide workgroup may take the small rows too, after the parts)
+  const LongRow L = a.lrows[LANES == kLBig && (int)blockIdx.x < np ? a.prow[blockIdx.x] : a.srow[(int)blockIdx.x - np]];
+  const unsigned b0 = L.np > 0 ? (unsigned)((int)blockIdx.x - L.boff) * kLPart : 0u;
+  const int slots = min(L.nb - (int)b0, NB) * kLBCap;
+  for (int i = tid; i < slots; i += LANES) sm.tab[i] = kFree;
+  const bool mapped = L.np > 1;
+  const int ka = (int)a.rp[L.a], kb = L.b >= 0 ? (int)a.rp[L.b] : 0;
+  if (tid == 0) sm.ngrp = sm.kept = 0;
+  __syncthreads();
+  int kept = 0;
+  for (int q0 = 0; q0 < L.ub; q0 += LANES * kI) {
+    int k[kI], D[kI];
 #pragma unroll
-      for (int j = 0; j < kLI; ++j) {
+    for (int j = 0; j < kI; ++j) {
+      const int e = q0 + j * LANES + tid;
+      k[j] = e < L.ub ? (e < L.dega ? ka + e : kb + (e - L.dega)) : -1;
+      D[j] = k[j] < 0 ? -1 : mapped ? a.dmap[k[j]] : a.col[k[j]];
+    }
+    if (!mapped) {
+#pragma unroll
+      for (int j = 0; j < kI; ++j) {
         if (k[j] < 0) continue;
-        int D = -1;
-        if ((unsigned)x[j] >= (unsigned)a.n)
+        int d = -1;
+        if ((unsigned)D[j] >= (unsigned)a.n)
           err |= kCErrCol;
         else
-          D = a.identity ? x[j] : a.cmap[x[j]];
-        if (D == L.c) D = -1;
-        a.next[k[j]] = D;
-        if (D < 0) {
-          a.scr[k[j]] = make_int2(-1, 0);
-          continue;
-        }
-        const long long bb = bucket_of(L, D);
-        if (lds)
-          atomicAdd(&sm.hist[bb - L.boff], 1);
-        else
-          atomicAdd((unsigned long long*)&a.bstart[bb], 1ull);
+          d = a.cmap[D[j]];
+        D[j] = d == L.c ? -1 : d;
+      }
+#pragma unroll
+      for (int j = 0; j < kI; ++j) {
+        if (k[j] < 0) continue;
+        a.dmap[k[j]] = D[j];
+        kept += D[j] >= 0 ? 1 : 0;
       }
     }
-    __syncthreads();
-    if (lds)
-      for (int i = tid; i < L.nb; i += kBlock)
-        if (sm.hist[i]) atomicAdd((unsigned long long*)&a.bstart[L.boff + i], (unsigned long long)sm.hist[i]);
-    __syncthreads();
+    // Its own entries (another part of the row may have merged its groups by
+    // now): every lane enters them one after the other, one probe a step, so a
+    // wave takes as many steps as its busiest lane has probes, however few of
+    // the entries are this part's.
+    unsigned todo = 0u;
+#pragma unroll
+    for (int j = 0; j < kI; ++j) {
+      const bool live = D[j] != -1;
+      D[j] &= ~kMerged;
+      todo |= live && bucket_of(L, D[j]) - b0 < (unsigned)NB ? 1u << j : 0u;
+    }
+    int cur = -1, d = 0, probe = 0;
+    unsigned tb = 0u, hh = 0u;
+    for (;;) {
+      if (cur < 0 && todo) {
+        cur = __ffs((int)todo) - 1;
+        todo &= todo - 1u;
+#pragma unroll
+        for (int j = 0; j < kI; ++j) d = cur == j ? D[j] : d;
+        tb = (bucket_of(L, d) - b0) * kLBCap;
+        const unsigned h0 = (unsigned)d * 0x85EBCA77u;
+        hh = (h0 ^ (h0 >> 15)) & (kLBCap - 1u);
+        probe = 0;
+      }
+      if (__ballot(cur >= 0) == 0ull) break;
+      if (cur >= 0) {
+        const int e = q0 + cur * LANES + tid;
+        const unsigned long long old = atomicCAS(&sm.tab[tb + hh], kFree, set_slot(d, (unsigned)e | kEnd));
+        bool done = old == kFree;
+        if (!done && (int)(unsigned)old == d) {
+          const unsigned prev = atomicExch(slot_pos(&sm.tab[tb + hh]), (unsigned)e);
+          a.aux[e < L.dega ? ka + e : kb + (e - L.dega)] = __uint_as_float(prev);
+          if (prev & kEnd) {
+            const int g = atomicAdd(&sm.ngrp, 1);
+            if (g < kGrp) sm.grp[g] = (unsigned short)(tb + hh);
+          }
+          done = true;
+        }
+        if (!done && ++probe == kLBCap) {  // a full bucket
+          atomicOr(&a.tot->overflow, 1u);
+          done = true;
+        }
+        cur = done ? -1 : cur;
+        hh = (hh + 1u) & (kLBCap - 1u);
+      }
+    }
+  }
+  __syncthreads();
+  const int ng = min(sm.ngrp, kGrp);
+  if (tid == 0 && sm.ngrp > kGrp) atomicOr(&a.tot->overflow, 1u);
+  for (int q = tid; q < ng; q += LANES) {
+    const unsigned long long t = sm.tab[sm.grp[q]];
+    const int d = (int)(unsigned)t;
+    int lst[kCMaxDup];
+    int nl = 0;
+    unsigned p = (unsigned)(t >> 32);
+    bool more = true;
+#pragma unroll
+    for (int i = 0; i < kCMaxDup; ++i) {  // static indices
+      if (more) {
+        const int e = (int)(p & ~kEnd);
+        lst[i] = e;
+        nl = i + 1;
+        more = !(p & kEnd);
+        if (more) p = __float_as_uint(a.aux[e < L.dega ? ka + e : kb + (e - L.dega)]);
+      }
+    }
+    if (more || nl > a.dup_limit) err |= kCErrDup;
+    int first;
+    const float sum = merge_group(a, lst, nl, L.a, L.b, L.dega, ka, kb, first);
+#pragma unroll
+    for (int i = 0; i < kCMaxDup; ++i) {
+      if (i >= nl) continue;
+      const int e = lst[i], k = e < L.dega ? ka + e : kb + (e - L.dega);
+      a.dmap[k] = e == first ? d | kMerged : -1;
+      if (e == first) a.aux[k] = sum;
+      else if (mapped) atomicSub(&a.ccnt[L.coff + e / kLC], 1);
+    }
+    kept -= nl - 1;
+  }
+  kept = wave_incl_sum<int>(kept);
+  if (lane_id() == 63 && kept) atomicAdd(&sm.kept, kept);
+  __syncthreads();
+  if (tid == 0) {
+    if (sm.kept) atomicAdd(&a.cnt[L.a], sm.kept);
+    if (!mapped) a.ccnt[L.coff] = sm.kept;
   }
   if (err) atomicOr(&a.tot->err, err);
 }
 
-// (3c') Places every mapped long-row entry's index in its bucket: per chunk,
-// ranks within (chunk, bucket) from LDS atomics, one device atomic per
-// (chunk, bucket) for the range, then the writes.
-__global__ __launch_bounds__(kBlock) void k_c_lb_scatter(CArgs a, long long nl, long long nchunks) {
-  __shared__ ChunkSmem sm;
-  const int tid = threadIdx.x;
-  const long long c0 = nchunks * blockIdx.x / gridDim.x, c1 = nchunks * (blockIdx.x + 1) / gridDim.x;
-  if (c0 >= c1) return;  // (uniform)
-  long long row = first_item_row(nl, c0, [&](long long i) { return a.lrows[i].coff; }, &sm.lb);
-  for (long long c = c0; c < c1; ++c) {
-    if (tid == 0) {
-      while (row + 1 < nl && a.lrows[row + 1].coff <= c) ++row;
-      sm.row = (int)row;
-    }
-    __syncthreads();
-    const LongRow L = a.lrows[sm.row];
-    const bool lds = L.nb <= kLHist;
-    if (lds)
-      for (int i = tid; i < L.nb; i += kBlock) sm.hist[i] = 0;
-    __syncthreads();
-    const long long e0 = (c - L.coff) * kLC;
-    const int ne = (int)min((long long)kLC, (long long)L.ub - e0);
-    const long long ka = a.rp[L.a];
-    const long long kb = L.b >= 0 ? a.rp[L.b] : 0;
-    auto kof = [&](int q) {
-      const long long off = e0 + q;
-      return off < L.dega ? ka + off : kb + (off - L.dega);
-    };
-    for (int q0 = 0; q0 < ne; q0 += kBlock * kLI) {
-      int D[kLI];
-#pragma unroll
-      for (int j = 0; j < kLI; ++j) {
-        const int q = q0 + j * kBlock + tid;
-        D[j] = q < ne ? a.next[kof(q)] : -1;
-      }
-#pragma unroll
-      for (int j = 0; j < kLI; ++j) {
-        const int q = q0 + j * kBlock + tid;
-        if (D[j] < 0) {
-          if (lds && q < ne) sm.erec[q] = ~0u;  // the matched edge: no record
-          continue;
-        }
-        const long long bb = bucket_of(L, D[j]);
-        if (lds) {
-          const int lb = (int)(bb - L.boff);
-          sm.erec[q] = ((unsigned)lb << 13) | (unsigned)atomicAdd(&sm.hist[lb], 1);
-        } else {
-          a.rec[a.bstart[bb] + atomicAdd(&a.bfill[bb], 1)] = (int)kof(q);
-        }
-      }
-    }
-    if (lds) {
-      __syncthreads();
-      for (int i = tid; i < L.nb; i += kBlock) {
-        const int h = sm.hist[i];
-        if (h) sm.hist[i] = (int)(a.bstart[L.boff + i] + atomicAdd(&a.bfill[L.boff + i], h));
-      }
-      __syncthreads();
-      for (int q = tid; q < ne; q += kBlock) {
-        const unsigned r = sm.erec[q];
-        if (r == ~0u) continue;
-        a.rec[sm.hist[r >> 13] + (int)(r & 8191u)] = (int)kof(q);
-      }
-    }
-    __syncthreads();
-  }
-}
-
-// (an entry's index is not kept: it follows from its position in the row
-// and the row's two offsets, which keeps five workgroups resident per CU)
-struct BucketSmem {
-  int skey[2 * kLBCap];
-  int shead[2 * kLBCap];
-  int epos[kLBCap];
-  int eD[kLBCap];
-  short enext[kLBCap];
-  short eslot[kLBCap];
-  int kept[2];
-  int row;
-  int lb;
-};
-
-// (3d') Groups every bucket in LDS, one workgroup per bucket at a time: the
-// first entry of a group in row order keeps it with the group's sum (written
-// at its fine entry), the others are written as dropped; the parts' kept
-// counts grow by the bucket's. A bucket above kLBCap entries sets overflow.
-__global__ __launch_bounds__(kBlock) void k_c_lb_group(CArgs a, long long nl, long long nbk) {
-  __shared__ BucketSmem sm;
-  const int tid = threadIdx.x;
-  for (int i = tid; i < 2 * kLBCap; i += kBlock) {
-    sm.skey[i] = -1;
-    sm.shead[i] = -1;
-  }
-  unsigned err = 0;
-  const long long b0 = nbk * blockIdx.x / gridDim.x, b1 = nbk * (blockIdx.x + 1) / gridDim.x;
-  long long row = b0 < b1 ? first_item_row(nl, b0, [&](long long i) { return a.lrows[i].boff; }, &sm.lb) : 0;
-  // Consecutive buckets mostly share a row: its record and row offsets are
-  // reloaded only when the row changes, the next row's first bucket only when
-  // it is passed (thread 0), and a bucket's start is the previous one's end.
-  long long next_boff = row + 1 < nl ? a.lrows[row + 1].boff : nbk;
-  int cur = -1;
-  LongRow L;
-  long long ka = 0, kb = 0;
-  long long s1n = b0 < b1 ? a.bstart[b0] : 0;
-  for (long long b = b0; b < b1; ++b) {
-    const long long s0 = s1n, s1 = a.bstart[b + 1];
-    s1n = s1;
-    const int ne = (int)(s1 - s0);
-    if (ne == 0) continue;  // uniform
-    if (ne > kLBCap) {
-      if (tid == 0) atomicOr(&a.tot->overflow, 1u);
-      continue;
-    }
-    if (tid == 0) {  // the row: largest boff <= b
-      while (next_boff <= b) {
-        ++row;
-        next_boff = row + 1 < nl ? a.lrows[row + 1].boff : nbk;
-      }
-      sm.row = (int)row;
-      sm.kept[0] = sm.kept[1] = 0;
-    }
-    __syncthreads();
-    if (sm.row != cur) {  // (uniform)
-      cur = sm.row;
-      L = a.lrows[cur];
-      ka = a.rp[L.a];
-      kb = L.b >= 0 ? a.rp[L.b] : 0;
-    }
-    for (int q = tid; q < ne; q += kBlock) {
-      const int k = a.rec[s0 + q];
-      const int D = a.next[k];
-      const bool pa = (long long)k >= ka && (long long)k < ka + L.dega;
-      sm.epos[q] = pa ? (int)(k - ka) : L.dega + (int)(k - kb);
-      sm.eD[q] = D;
-      const unsigned h0 = (unsigned)D * 0x85EBCA77u;
-      unsigned hh = (h0 ^ (h0 >> 15)) & (2u * kLBCap - 1u);
-      for (;;) {
-        const int old = atomicCAS(&sm.skey[hh], -1, D);
-        if (old == -1 || old == D) break;
-        hh = (hh + 1) & (2u * kLBCap - 1u);
-      }
-      sm.eslot[q] = (short)hh;
-      sm.enext[q] = (short)atomicExch(&sm.shead[hh], q);
-    }
-    __syncthreads();
-    auto entry_of = [&](int pos) { return (int)(pos < L.dega ? ka + pos : kb + (pos - L.dega)); };
-    for (int q = tid; q < ne; q += kBlock) {
-      const int my = sm.epos[q];
-      const int k = entry_of(my);
-      int lst[kCMaxDup + 1];
-      int nlst = 0;
-      int p = sm.shead[sm.eslot[q]];
-      bool first = true;
-#pragma unroll
-      for (int t = 0; t <= kCMaxDup; ++t) {
-        if (p >= 0) {
-          lst[t] = p;
-          nlst = t + 1;
-          first = first && sm.epos[p] >= my;
-          p = sm.enext[p];
-        }
-      }
-      if (nlst > a.dup_limit) err |= kCErrDup;
-      if (!first || nlst > a.dup_limit) {
-        a.scr[k] = make_int2(-1, 0);
-        continue;
-      }
-      float sum;
-      if (nlst == 1) {
-        sum = a.w ? a.w[k] : 1.0f;
-      } else {
-        unsigned long long ord[kCMaxDup];
-        float wv[kCMaxDup];
-#pragma unroll
-        for (int t = 0; t < kCMaxDup; ++t) {
-          ord[t] = ~0ull;
-          wv[t] = 0.f;
-          if (t >= nlst) continue;
-          const int pp = lst[t];
-          const int kp = entry_of(sm.epos[pp]);
-          const int sp = sm.epos[pp] < L.dega ? L.a : L.b;
-          ord[t] = edge_order(sp, a.col[kp]);
-          wv[t] = a.w ? a.w[kp] : 1.0f;
-        }
-        sum = group_sum(ord, wv, nlst);
-      }
-      a.scr[k] = make_int2(sm.eD[q], __float_as_int(sum));
-      atomicAdd(&sm.kept[my < L.dega ? 0 : 1], 1);
-    }
-    __syncthreads();
-    if (tid == 0) {
-      if (sm.kept[0]) atomicAdd(&a.cnt[L.a], sm.kept[0]);
-      if (sm.kept[1]) atomicAdd(&a.cnt[L.b], sm.kept[1]);
-    }
-    for (int q = tid; q < ne; q += kBlock) {
-      sm.skey[sm.eslot[q]] = -1;
-      sm.shead[sm.eslot[q]] = -1;
-    }
-    __syncthreads();
-  }
-  if (err) atomicOr(&a.tot->err, err);
-}
-
-// Clears the kept counts of the long rows' parts (before the table path
-// redoes them after a bucket overflow).
-__global__ __launch_bounds__(kBlock) void k_c_long_clear_cnt(CArgs a, long long nl) {
-  for (long long r = (long long)blockIdx.x * kBlock + threadIdx.x; r < nl; r += (long long)gridDim.x * kBlock) {
+// Clears the kept counts of the long rows and their chunks (before the table
+// path redoes them after a bucket overflow).
+__global__ __launch_bounds__(kBlock) void k_c_long_clear_cnt(CArgs a, long long nl, long long nchunks) {
+  for (long long r = (long long)blockIdx.x * kBlock + threadIdx.x; r < nl; r += (long long)gridDim.x * kBlock)
     a.cnt[a.lrows[r].a] = 0;
-    if (a.lrows[r].b >= 0) a.cnt[a.lrows[r].b] = 0;
-  }
+  for (long long c = (long long)blockIdx.x * kBlock + threadIdx.x; c < nchunks; c += (long long)gridDim.x * kBlock)
+    a.ccnt[c] = 0;
 }
 
-__device__ __forceinline__ long long coarse_deg(const CArgs& a, long long c) {
-  const int r = a.crep[c];
-  const int m = a.mate[r];
-  return (long long)a.cnt[r] + (m >= 0 ? a.cnt[m] : 0);
+// Lengths of the coarse rows base + i * kBlock + lane, all loads of a step in
+// flight together.
+__device__ __forceinline__ void coarse_degs(const CArgs& a, long long base, long long nc, int (&deg)[kCV]) {
+  int r[kCV], m[kCV];
+#pragma unroll
+  for (int i = 0; i < kCV; ++i) {
+    const long long c = base + (long long)i * kBlock + threadIdx.x;
+    r[i] = c < nc ? a.crep[c] : -1;
+  }
+#pragma unroll
+  for (int i = 0; i < kCV; ++i) {
+    m[i] = r[i] >= 0 ? a.mate[r[i]] : -1;
+    deg[i] = r[i] >= 0 ? a.cnt[r[i]] : 0;
+  }
+#pragma unroll
+  for (int i = 0; i < kCV; ++i) deg[i] += m[i] >= 0 ? a.cnt[m[i]] : 0;
 }
 
 // (4a) Coarse row lengths, summed per block (coalesced).
 __global__ __launch_bounds__(kBlock) void k_c_deg_count(CArgs a, long long nc) {
   __shared__ long long sm[kWaves];
   if (a.tot->err) return;
-  const long long base = (long long)blockIdx.x * kCBlockV;
+  int deg[kCV];
+  coarse_degs(a, (long long)blockIdx.x * kCBlockV, nc, deg);
   long long s = 0;
-  for (int i = 0; i < kCV; ++i) {
-    const long long c = base + (long long)i * kBlock + threadIdx.x;
-    if (c >= nc) break;
-    s += coarse_deg(a, c);
-  }
+#pragma unroll
+  for (int i = 0; i < kCV; ++i) s += deg[i];
   long long total;
   (void)block_excl_sum<long long>(s, sm, total);
   if (threadIdx.x == 0) a.bsum[blockIdx.x] = total;
@@ -1543,11 +1442,10 @@ __global__ __launch_bounds__(kBlock) void k_c_deg_write(CArgs a, long long nc) {
   __shared__ long long sm[kWaves];
   if (a.tot->err) return;
   const long long base = (long long)blockIdx.x * kCBlockV;
+  int deg[kCV];
+  coarse_degs(a, base, nc, deg);
 #pragma unroll
-  for (int i = 0; i < kCV; ++i) {
-    const long long c = base + (long long)i * kBlock + threadIdx.x;
-    val[i * kBlock + threadIdx.x] = c < nc ? coarse_deg(a, c) : 0ll;
-  }
+  for (int i = 0; i < kCV; ++i) val[i * kBlock + threadIdx.x] = deg[i];
   __syncthreads();
   (void)block_stage_scan(val, a.bsum[blockIdx.x], sm);
 #pragma unroll
@@ -1558,96 +1456,97 @@ __global__ __launch_bounds__(kBlock) void k_c_deg_write(CArgs a, long long nc) {
   if (blockIdx.x == 0 && threadIdx.x == 0) a.crp[nc] = a.tot->nnz_c;
 }
 
-// (4d) Packs the kept entries of every long row part in order, one
-// workgroup per part at a time.
-__global__ __launch_bounds__(kBlock) void k_c_long_pack(CArgs a, long long nl) {
+// (4e) Writes the kept entries of the long rows in order, one workgroup a
+// chunk: its place in the output row is the sum of the counts of the chunks
+// before it, its entries stay in registers between counting and writing.
+__global__ __launch_bounds__(kBlock) void k_c_long_out(CArgs a) {
   __shared__ int smi[kWaves];
+  constexpr int kI = kLC / kBlock;  // entries per lane
   if (a.tot->err) return;
-  for (long long pi = blockIdx.x; pi < 2 * nl; pi += gridDim.x) {
-    const LongRow L = a.lrows[pi >> 1];
-    const bool side = (pi & 1) != 0;
-    if (side && L.b < 0) continue;
-    const int s = side ? L.b : L.a;
-    const long long k0 = a.rp[s];
-    const long long len = a.rp[s + 1] - k0;
-    long long dest = a.crp[L.c] + (side ? a.cnt[L.a] : 0);
-    for (long long base = 0; base < len; base += kBlock) {
-      const long long j = base + threadIdx.x;
-      int2 t = make_int2(-1, 0);
-      if (j < len) t = a.scr[k0 + j];
-      const int f = t.x >= 0 ? 1 : 0;
-      int tot;
-      const int e = block_excl_sum<int>(f, smi, tot);
-      if (f) {
-        a.ccol[dest + e] = t.x;
-        a.cw[dest + e] = __int_as_float(t.y);
+  const int tid = threadIdx.x, l = lane_id(), wv = wave_id();
+  const long long c = blockIdx.x;
+  const LongRow L = a.lrows[a.crow[c]];
+  const int e0 = (int)(c - L.coff) * kLC;
+  const int ne = min(kLC, L.ub - e0);
+  const int ka = (int)a.rp[L.a], kb = L.b >= 0 ? (int)a.rp[L.b] : 0;
+  // wave w takes positions [w step, (w + 1) step) of the chunk
+  const int step = ((ne + kBlock - 1) / kBlock) * 64;
+  int d[kI];
+  int mine = 0;
+#pragma unroll
+  for (int i = 0; i < kI; ++i) {
+    d[i] = -1;
+    if (i * 64 < step) {
+      const int q = wv * step + i * 64 + l, e = e0 + q;
+      if (q < ne) d[i] = a.dmap[e < L.dega ? ka + e : kb + (e - L.dega)];
+    }
+  }
+  int before = 0;
+  for (int j = tid; j < (int)(c - L.coff); j += kBlock) before += a.ccnt[L.coff + j];
+#pragma unroll
+  for (int i = 0; i < kI; ++i)
+    if (i * 64 < step) mine += (int)__popcll(__ballot(d[i] != -1));
+  int pre;
+  (void)block_excl_sum<int>(before, smi, pre);
+  if (l == 0) smi[wv] = mine;
+  __syncthreads();
+  long long dest = a.crp[L.c] + pre;
+  for (int w = 0; w < wv; ++w) dest += smi[w];
+#pragma unroll
+  for (int i = 0; i < kI; ++i) {
+    if (i * 64 < step) {
+      const unsigned long long bal = __ballot(d[i] != -1);
+      if (d[i] != -1) {
+        const int e = e0 + wv * step + i * 64 + l;
+        const int k = e < L.dega ? ka + e : kb + (e - L.dega);
+        const long long at = dest + (long long)__popcll(bal & lanemask_lt());
+        a.ccol[at] = d[i] & ~kMerged;
+        a.cw[at] = d[i] < 0 ? a.aux[k] : (a.w ? a.w[k] : 1.0f);
       }
-      dest += tot;
+      dest += (long long)__popcll(bal);
     }
   }
 }
 
-int lb_group_blocks_per_cu() {
-  static int cached = 0;
-  if (cached) return cached;
-  int nb = 1;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_c_lb_group, kBlock, 0) != hipSuccess || nb < 1) nb = 1;
-  cached = nb;
-  return nb;
-}
-
-int wave_blocks_per_cu() {
-  static int cached = 0;
-  if (cached) return cached;
-  int nb = 1;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_c_group_wave, kBlock, 0) != hipSuccess || nb < 1) nb = 1;
-  cached = nb;
-  return nb;
-}
-
-int tile_blocks_per_cu() {
-  static int cached = 0;
-  if (cached) return cached;
-  int nb = 1;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_c_group, kBlock, 0) != hipSuccess || nb < 1) nb = 1;
-  cached = nb;
-  return nb;
-}
-
 size_t a256(size_t b) { return (b + 255) & ~(size_t)255; }
+
+// Ranges of the kernels that walk the fine vertices (wg_vertices). Each
+// merges the rows of its own kind only, so a range's work is anything between
+// none and its cost: ranges of kCRange units, many more than fit the chip at
+// once, even that out (R-MAT scale 24, against one range per resident
+// workgroup: short rows 3.75 -> 1.3 ms, medium 6.3 -> 2.4, copy 3.7 -> 1.1).
+// k_c_count finds their starts as it reads row_ptr anyway.
+constexpr long long kCRange = 8192;
+
+void set_ranges(CArgs& a, Pool& P, DevBuf& buf, int num_cus) {
+  const long long cost = a.nnz + (long long)kCCost * a.n;
+  // small graphs: ranges down to 2 kCT units, so that every CU has some
+  const long long want = std::max<long long>((cost + kCRange - 1) / kCRange, (long long)num_cus * 4);
+  long long grid = std::max<long long>(1, std::min<long long>(want, (cost + 2 * kCT - 1) / (2 * kCT)));
+  a.vstart = nullptr;
+  if (P.reserve(buf, a256(sizeof(int) * (size_t)(grid + 2))) == LM_OK)
+    a.vstart = (int*)buf.p;
+  else  // no room: few ranges, whose starts the workgroups search for
+    grid = std::min<long long>(grid, (long long)num_cus * 4);
+  a.ranges = (int)grid;
+  a.per_wg = (cost + grid - 1) / grid;
+}
 
 }  // namespace
 
-// The long rows' sizes and offsets (k_c_long_sums, four top scans, k_c_long_offs)
-// over a grid that covers lrow_cap rows; lsum holds 4 * long_prep_blocks(lrow_cap).
+// The long rows' sizes and offsets (k_c_long_sums, k_c_long_top, k_c_long_offs)
+// over a grid that covers lrow_cap rows; lsum holds kLQ * long_prep_blocks(lrow_cap).
 static long long long_prep_blocks(long long lrow_cap) { return std::max<long long>(1, (lrow_cap + kLPRows - 1) / kLPRows); }
 static void launch_long_prep(const CArgs& a, long long* lsum, hipStream_t s) {
   const long long nblk = long_prep_blocks(a.lrow_cap);
   hipLaunchKernelGGL(k_c_long_sums, dim3((unsigned)nblk), dim3(kBlock), 0, s, a, lsum, nblk);
-  long long* totals[4] = {&a.tot->long_entries, &a.tot->long_slots, &a.tot->long_buckets, &a.tot->long_chunks};
-  for (int q = 0; q < 4; ++q)
-    hipLaunchKernelGGL(k_c_scan_top, dim3(1), dim3(kCTopThreads), 0, s, lsum + q * nblk, nblk, totals[q]);
+  hipLaunchKernelGGL(k_c_long_top, dim3(kLQ), dim3(kCTopThreads), 0, s, lsum, nblk, a.tot);
   hipLaunchKernelGGL(k_c_long_offs, dim3((unsigned)nblk), dim3(kBlock), 0, s, a, (const long long*)lsum, nblk);
-}
-
-// Exclusive scan of v[0, m) in place, its total to *total. Arrays above one
-// top-scan round's worth take the three-step scan, with the workgroup sums
-// in tmp (tmp_cap values; the one-workgroup scan when they would not fit).
-static void launch_scan(long long* v, long long m, long long* total, long long* tmp, long long tmp_cap,
-                        hipStream_t s) {
-  const long long nb = (m + kSBlock - 1) / kSBlock;
-  if (m <= 8 * kCTopThreads || nb > tmp_cap) {
-    hipLaunchKernelGGL(k_c_scan_top, dim3(1), dim3(kCTopThreads), 0, s, v, m, total);
-    return;
-  }
-  hipLaunchKernelGGL(k_c_scan_sums, dim3((unsigned)nb), dim3(kBlock), 0, s, (const long long*)v, m, tmp);
-  hipLaunchKernelGGL(k_c_scan_top, dim3(1), dim3(kCTopThreads), 0, s, tmp, nb, total);
-  hipLaunchKernelGGL(k_c_scan_apply, dim3((unsigned)nb), dim3(kBlock), 0, s, v, m, (const long long*)tmp);
 }
 
 // Buffers of the contraction, kept in the context between calls.
 struct ContractState {
-  DevBuf bsum, tot, crep, cnt, scr, next, lrows, table, bstart, bfill, rec, lsum;
+  DevBuf bsum, tot, crep, cnt, scr, next, lrows, table, ltab, lsum, ranges;
   DevBuf in_rp, in_col, in_w, in_mate, in_vw, o_cmap, o_crp, o_ccol, o_cw, o_cvw;
   CTot* h_tot = nullptr;
 };
@@ -1656,9 +1555,9 @@ void contract_release(Solver& S) {
   ContractState* cs = S.contract;
   if (!cs) return;
   DevBuf* all[] = {&cs->bsum,  &cs->tot,    &cs->crep,  &cs->cnt,  &cs->scr,     &cs->next,  &cs->lrows,
-                   &cs->table, &cs->bstart, &cs->bfill, &cs->rec,  &cs->in_rp,   &cs->in_col, &cs->in_w,
+                   &cs->table, &cs->ltab,   &cs->in_rp, &cs->in_col, &cs->in_w,
                    &cs->in_mate, &cs->in_vw, &cs->o_cmap, &cs->o_crp, &cs->o_ccol, &cs->o_cw, &cs->o_cvw,
-                   &cs->lsum};
+                   &cs->lsum, &cs->ranges};
   for (DevBuf* b : all) S.pool.release(*b);
   if (cs->h_tot) (void)hipHostFree(cs->h_tot);
   delete cs;
@@ -1686,7 +1585,7 @@ lm_status check_row_duplicates(Solver& S, int64_t n, int64_t nnz, const long lon
   if ((rs = P.reserve(cs.bsum, a256(sizeof(long long) * (size_t)(nb_v + 1)))) != LM_OK) return rs;
   if ((rs = P.reserve(cs.tot, a256(sizeof(CTot)))) != LM_OK) return rs;
   if ((rs = P.reserve(cs.lrows, a256(sizeof(LongRow) * (size_t)lrow_cap))) != LM_OK) return rs;
-  if ((rs = P.reserve(cs.lsum, a256(sizeof(long long) * 4 * (size_t)long_prep_blocks(lrow_cap)))) != LM_OK) return rs;
+  if ((rs = P.reserve(cs.lsum, a256(sizeof(long long) * kLQ * (size_t)long_prep_blocks(lrow_cap)))) != LM_OK) return rs;
   CArgs a;
   std::memset(&a, 0, sizeof(a));
   a.n = n;
@@ -1700,15 +1599,10 @@ lm_status check_row_duplicates(Solver& S, int64_t n, int64_t nnz, const long lon
   a.dup_limit = 1;
   a.identity = 1;
   if (hipMemsetAsync(a.tot, 0, sizeof(CTot), s) != hipSuccess) return LM_EDEVICE;
+  set_ranges(a, P, cs.ranges, S.num_cus);
   hipLaunchKernelGGL(k_c_count, dim3((unsigned)nb_v), dim3(kBlock), 0, s, a);
-  const long long cost = nnz + (long long)kCCost * n;
-  long long grid = (long long)S.num_cus * tile_blocks_per_cu();
-  grid = std::max<long long>(1, std::min<long long>(grid, (cost + 2 * kCT - 1) / (2 * kCT)));
-  // (each grouping kernel takes its own resident count of workgroups)
-  const long long gw = std::max<long long>(
-      1, std::min<long long>((long long)S.num_cus * wave_blocks_per_cu(), (cost + 2 * kCT - 1) / (2 * kCT)));
-  hipLaunchKernelGGL(k_c_group_wave, dim3((unsigned)gw), dim3(kBlock), 0, s, a, (cost + gw - 1) / gw);
-  hipLaunchKernelGGL(k_c_group, dim3((unsigned)grid), dim3(kBlock), 0, s, a, (cost + grid - 1) / grid);
+  hipLaunchKernelGGL(k_c_group_wave, dim3((unsigned)a.ranges), dim3(kBlock), 0, s, a);
+  hipLaunchKernelGGL(k_c_group_mid, dim3((unsigned)a.ranges), dim3(kBlock), 0, s, a);
   launch_long_prep(a, (long long*)cs.lsum.p, s);
   if (hipGetLastError() != hipSuccess) return LM_EDEVICE;
   if (hipMemcpyAsync(cs.h_tot, a.tot, sizeof(CTot), hipMemcpyDeviceToHost, s) != hipSuccess ||
@@ -1798,7 +1692,7 @@ lm_status lm_contract(lm_ctx* ctx, const lm_csr* g, const int32_t* mate, const i
   LMC_TRY(P.reserve(cs.cnt, a256(sizeof(int) * (size_t)n)));
   LMC_TRY(P.reserve(cs.scr, a256(sizeof(int2) * (size_t)(nnz > 0 ? nnz : 1))));
   LMC_TRY(P.reserve(cs.lrows, a256(sizeof(LongRow) * (size_t)lrow_cap)));
-  LMC_TRY(P.reserve(cs.lsum, a256(sizeof(long long) * 4 * (size_t)long_prep_blocks(lrow_cap))));
+  LMC_TRY(P.reserve(cs.lsum, a256(sizeof(long long) * kLQ * (size_t)long_prep_blocks(lrow_cap))));
 
   CArgs a;
   std::memset(&a, 0, sizeof(a));
@@ -1858,27 +1752,21 @@ lm_status lm_contract(lm_ctx* ctx, const lm_csr* g, const int32_t* mate, const i
   a.cnt = (int*)cs.cnt.p;
   a.bsum = (long long*)cs.bsum.p;
   a.tot = (CTot*)cs.tot.p;
-  a.scr = (int2*)cs.scr.p;
+  a.dmap = (int*)cs.scr.p;
+  a.aux = (float*)cs.scr.p + nnz;
   a.lrows = (LongRow*)cs.lrows.p;
   a.lrow_cap = lrow_cap;
   a.dup_limit = kCMaxDup;
   a.identity = 0;
+  set_ranges(a, P, cs.ranges, S.num_cus);
 
   LMC_HIP(hipEventRecord(S.e0, s));
   LMC_HIP(hipMemsetAsync(a.tot, 0, sizeof(CTot), s));
   hipLaunchKernelGGL(k_c_count, dim3((unsigned)nb_v), dim3(kBlock), 0, s, a);
   hipLaunchKernelGGL(k_c_scan_top, dim3(1), dim3(kCTopThreads), 0, s, a.bsum, nb_v, &a.tot->nc);
   hipLaunchKernelGGL(k_c_map, dim3((unsigned)nb_v), dim3(kBlock), 0, s, a);
-  const long long cost = nnz + (long long)kCCost * n;
-  long long grid = (long long)S.num_cus * tile_blocks_per_cu();
-  const long long by_cost = (cost + 2 * kCT - 1) / (2 * kCT);
-  if (grid > by_cost) grid = by_cost;
-  if (grid < 1) grid = 1;
-  const long long per_wg = (cost + grid - 1) / grid;
-  // (each grouping kernel takes its own resident count of workgroups)
-  const long long gw = std::max<long long>(1, std::min<long long>((long long)S.num_cus * wave_blocks_per_cu(), by_cost));
-  hipLaunchKernelGGL(k_c_group_wave, dim3((unsigned)gw), dim3(kBlock), 0, s, a, (cost + gw - 1) / gw);
-  hipLaunchKernelGGL(k_c_group, dim3((unsigned)grid), dim3(kBlock), 0, s, a, per_wg);
+  hipLaunchKernelGGL(k_c_group_wave, dim3((unsigned)a.ranges), dim3(kBlock), 0, s, a);
+  hipLaunchKernelGGL(k_c_group_mid, dim3((unsigned)a.ranges), dim3(kBlock), 0, s, a);
   launch_long_prep(a, (long long*)cs.lsum.p, s);
   LMC_HIP(hipGetLastError());
   LMC_HIP(hipMemcpyAsync(cs.h_tot, a.tot, sizeof(CTot), hipMemcpyDeviceToHost, s));
@@ -1891,29 +1779,23 @@ lm_status lm_contract(lm_ctx* ctx, const lm_csr* g, const int32_t* mate, const i
   if (nl > lrow_cap) return LM_EDEVICE;  // cannot happen: the bounds of the rows sum to nnz
   long long overflow_rows = 0;
   if (nl > 0) {
-    // long rows: entries sorted into LDS-sized buckets by a hash of their
-    // coarse neighbour, each bucket grouped in LDS by one workgroup
-    const long long nbk = t1.long_buckets;
-    LMC_TRY(P.reserve(cs.next, a256(sizeof(int) * (size_t)nnz)));
-    LMC_TRY(P.reserve(cs.bstart, a256(sizeof(long long) * (size_t)(nbk + 1))));
-    LMC_TRY(P.reserve(cs.bfill, a256(sizeof(int) * (size_t)nbk)));
-    LMC_TRY(P.reserve(cs.rec, a256(sizeof(int) * (size_t)t1.long_entries)));
-    a.next = (int*)cs.next.p;
-    a.bstart = (long long*)cs.bstart.p;
-    a.bfill = (int*)cs.bfill.p;
-    a.rec = (int*)cs.rec.p;
-    LMC_HIP(hipMemsetAsync(a.bstart, 0, sizeof(long long) * (size_t)(nbk + 1), s));
-    LMC_HIP(hipMemsetAsync(a.bfill, 0, sizeof(int) * (size_t)nbk, s));
-    const long long lg = std::min<long long>((t1.long_entries + kBlock * kLI - 1) / (kBlock * kLI), 16384);
-    const long long nch = t1.long_chunks;
-    const long long cgd = std::max<long long>(1, std::min<long long>(nch, (long long)S.num_cus * 8));
-    hipLaunchKernelGGL(k_c_lb_count, dim3((unsigned)cgd), dim3(kBlock), 0, s, a, nl, nch);
-    // (lsum is free again: the long rows' offsets are written)
-    launch_scan(a.bstart, nbk + 1, &a.tot->long_kept, (long long*)cs.lsum.p, 4 * long_prep_blocks(lrow_cap), s);
-    hipLaunchKernelGGL(k_c_lb_scatter, dim3((unsigned)cgd), dim3(kBlock), 0, s, a, nl, nch);
-    // every workgroup resident: each takes one contiguous range of buckets
-    const long long gg = std::max<long long>(1, std::min<long long>(nbk, (long long)S.num_cus * lb_group_blocks_per_cu()));
-    hipLaunchKernelGGL(k_c_lb_group, dim3((unsigned)gg), dim3(kBlock), 0, s, a, nl, nbk);
+    const long long np = t1.long_items >> 32, nsm = t1.long_items & 0x7fffffffll, nch = t1.long_chunks;
+    LMC_TRY(P.reserve(cs.ltab, a256(sizeof(int) * (size_t)(nsm + np + 2 * nch))));
+    a.srow = (int*)cs.ltab.p;
+    a.prow = a.srow + nsm;
+    a.crow = a.prow + np;
+    a.ccnt = a.crow + nch;
+    hipLaunchKernelGGL(k_c_long_tables, dim3((unsigned)std::min<long long>((nl + kBlock - 1) / kBlock, 4096)),
+                       dim3(kBlock), 0, s, a, nl);
+    // a workgroup per chunk, part and row: they differ in work, and are
+    // handed out as workgroups end
+    if (np > 0) hipLaunchKernelGGL(k_c_long_map, dim3((unsigned)nch), dim3(kBlock), 0, s, a);
+    const bool one = np > 0 && np + nsm <= 2 * S.num_cus;  // few of both: one launch
+    if (np > 0)
+      hipLaunchKernelGGL((k_c_long_group<kLBig, kLPart>), dim3((unsigned)(np + (one ? nsm : 0))), dim3(kLBig), 0, s, a,
+                         (int)np);
+    if (nsm > 0 && !one)
+      hipLaunchKernelGGL((k_c_long_group<kBlock, kLSmall>), dim3((unsigned)nsm), dim3(kBlock), 0, s, a, 0);
     LMC_HIP(hipGetLastError());
     LMC_HIP(hipMemcpyAsync(cs.h_tot, a.tot, sizeof(CTot), hipMemcpyDeviceToHost, s));
     LMC_HIP(hipStreamSynchronize(s));
@@ -1921,10 +1803,13 @@ lm_status lm_contract(lm_ctx* ctx, const lm_csr* g, const int32_t* mate, const i
     if (cs.h_tot->err) return LM_EGRAPH;
     if (cs.h_tot->overflow) {  // a bucket outgrew LDS: every long row through per-row tables
       overflow_rows = nl;
+      LMC_TRY(P.reserve(cs.next, a256(sizeof(int) * (size_t)nnz)));
       LMC_TRY(P.reserve(cs.table, a256(sizeof(int2) * (size_t)t1.long_slots)));
+      a.next = (int*)cs.next.p;
       a.table = (int2*)cs.table.p;
+      const long long lg = std::min<long long>((t1.long_entries + kBlock * kLI - 1) / (kBlock * kLI), 16384);
       const long long cg = std::min<long long>((nl + kBlock - 1) / kBlock, 4096);
-      hipLaunchKernelGGL(k_c_long_clear_cnt, dim3((unsigned)cg), dim3(kBlock), 0, s, a, nl);
+      hipLaunchKernelGGL(k_c_long_clear_cnt, dim3((unsigned)cg), dim3(kBlock), 0, s, a, nl, nch);
       const long long fill_grid = std::min<long long>((t1.long_slots + kBlock - 1) / kBlock, 8192);
       hipLaunchKernelGGL(k_c_fill, dim3((unsigned)fill_grid), dim3(kBlock), 0, s, a.table, t1.long_slots);
       hipLaunchKernelGGL(k_c_long_insert, dim3((unsigned)lg), dim3(kBlock), 0, s, a, nl, t1.long_entries);
@@ -1937,11 +1822,8 @@ lm_status lm_contract(lm_ctx* ctx, const lm_csr* g, const int32_t* mate, const i
     hipLaunchKernelGGL(k_c_scan_top, dim3(1), dim3(kCTopThreads), 0, s, a.bsum, nb_c, &a.tot->nnz_c);
     hipLaunchKernelGGL(k_c_deg_write, dim3((unsigned)nb_c), dim3(kBlock), 0, s, a, nc);
   }
-  hipLaunchKernelGGL(k_c_copy, dim3((unsigned)grid), dim3(kBlock), 0, s, a, per_wg);
-  if (nl > 0) {
-    const long long pg = std::min<long long>(2 * nl, kCPackGrid);
-    hipLaunchKernelGGL(k_c_long_pack, dim3((unsigned)pg), dim3(kBlock), 0, s, a, nl);
-  }
+  hipLaunchKernelGGL(k_c_copy, dim3((unsigned)a.ranges), dim3(kBlock), 0, s, a);
+  if (nl > 0) hipLaunchKernelGGL(k_c_long_out, dim3((unsigned)t1.long_chunks), dim3(kBlock), 0, s, a);
   LMC_HIP(hipGetLastError());
   LMC_HIP(hipEventRecord(S.e1, s));
   LMC_HIP(hipMemcpyAsync(cs.h_tot, a.tot, sizeof(CTot), hipMemcpyDeviceToHost, s));
