@@ -407,7 +407,9 @@ lm_status Solver::run(const Problem& p, const Work& wk, hipStream_t s, uint32_t 
       const int grid = (int)std::min<int64_t>(pmcap, (p.N + kBlock - 1) / kBlock + 1);
       ENQ(launch_check(ca, grid, s));
     }
-    const int pi = (int)std::max<int64_t>(1, std::min<int64_t>(pcap, (p.N + 16383) / 16384));
+    // (a workgroup per 16384 vertices took 30 us for 60 K and 36 for 1 M
+    // vertices, one per round of kCap 5 and 10)
+    const int pi = (int)std::max<int64_t>(1, std::min<int64_t>(pcap, (p.N + kCap - 1) / kCap));
     InitArgs ia;
     ia.c = c;
     ia.row_ptr = p.row_ptr;
@@ -533,8 +535,10 @@ lm_status Solver::run(const Problem& p, const Work& wk, hipStream_t s, uint32_t 
     ta.final_rec = d_mir + kMirrorSlots;
     ta.gen = gen;
     ta.spin_ticks = clock_khz * 2000ull;  // 2 s
-    // workgroups (1024 lanes each): about one per 16384 live entries
-    const long long want = L_hint < 0 ? tail_cap : (L_hint + 16383) / 16384;
+    // workgroups (1024 lanes each): about one per 4096 live entries (per 16384:
+    // the first phase of 600 K entries 23 us; 320 K unweighted ER entries solved
+    // in 237 us against 211)
+    const long long want = L_hint < 0 ? tail_cap : (L_hint + 4095) / 4096;
     const int grid = (int)std::max<long long>(1, std::min<long long>(tail_cap, want));
     ENQ(launch_tail(ta, grid, s, timing(LM_K_TAIL)));
     return hipSuccess;
