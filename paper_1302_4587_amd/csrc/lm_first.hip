@@ -19,9 +19,12 @@
 // kernels do.
 #include <hip/hip_ext.h>
 
+#include <algorithm>
+
 #include "lm_device.h"
 #include "lm_internal.h"
 #include "lm_key.h"
+#include "lm_rows.h"
 
 namespace lm {
 
@@ -755,6 +758,155 @@ hipError_t launch_first_csr(const StreamArgs& a, int grid, hipStream_t s, bool u
   const bool multi = a.c.graphs > 1;
   if (unweighted) return multi ? launch_first_csr_t<true, true>(a, grid, s, ev) : launch_first_csr_t<true, false>(a, grid, s, ev);
   return multi ? launch_first_csr_t<false, true>(a, grid, s, ev) : launch_first_csr_t<false, false>(a, grid, s, ev);
+}
+
+// First argmax of one weighted graph, whole rows: a wave takes 64 consecutive
+// rows, and lane groups hold those of at most kRI << lg entries (two steps'
+// loads in flight); longer ones, where there are more than a few, are listed
+// for k_first_long, which gives each a wave, or a workgroup above kRHub entries (skewed graphs have their
+// long rows next to each other: a wave that took those of its 64 rows one
+// after the other made R-MAT 14 50 us slower). No row is cut, nothing waits on
+// a workgroup barrier. Bound by HBM: RGG 2^24 415 us, 3.6 TB/s (in tiles with
+// workgroup barriers 487 us), RGG of 1 M vertices 44 us (69).
+constexpr int kRI = 8;
+constexpr int kRHub = 2048;
+constexpr int kRFew = 2;  // long rows a wave takes itself rather than list them (two atomics on shared words)
+
+__global__ __launch_bounds__(kBlock, 5) void k_first_rows(FirstRowsArgs a) {
+  if (a.totals->err) return;
+  const int lane = lane_id();
+  const long long nblk = ((long long)a.n + 63) / 64;
+  const long long nw = (long long)gridDim.x * kWaves;
+  const int lg = a.lg, sub = lane & ((1 << lg) - 1), grp = lane >> lg, per = 64 >> lg, thr = kRI << lg;
+  const unsigned long long gm = group_mask(lg);
+  const int lim = (int)a.nnz;
+  long long b = (long long)blockIdx.x * kWaves + uni(wave_id());
+  auto offs = [&](long long blk, int& o0, int& o1) {
+    const long long v = blk * 64 + lane;
+    o0 = v < a.n ? (int)a.rp[v] : 0;
+    o1 = v < a.n ? (int)a.rp[v + 1] : 0;
+  };
+  int n0 = 0, n1 = 0;
+  if (b < nblk) offs(b, n0, n1);
+  for (; b < nblk; b += nw) {
+    int v = (int)(b * 64) + lane, off = n0, len = n1 - n0;
+    if (b + nw < nblk) offs(b + nw, n0, n1);  // the next block's rows
+    unsigned long long lng = __ballot(len > thr);
+    if (lng) {
+      const unsigned long long hub = __ballot(len > kRHub);
+      if (!hub && __popcll(lng) <= kRFew) {
+        while (lng) {
+          const int src = __ffsll((long long)lng) - 1;
+          lng &= lng - 1;
+          const int rv = __builtin_amdgcn_readlane(v, src), ro = __builtin_amdgcn_readlane(off, src);
+          unsigned bw = 0u;
+          int bu = 0;
+          row_best<kRI, 64>(a.col, a.w, ro, __builtin_amdgcn_readlane(len, src), lane, lim, a.n, (unsigned)rv, a.S, bw,
+                            bu);
+          if (lane == 0 && bw != 0u) a.C[rv] = bu;
+        }
+      } else {  // waves' rows from the list's front, hubs from its back
+        lng &= ~hub;
+        unsigned al = 0u, ah = 0u;
+        if (lane == 0) {
+          if (lng) al = atomicAdd(&a.totals->longs, (unsigned)__popcll(lng));
+          if (hub) ah = atomicAdd(&a.totals->hubs, (unsigned)__popcll(hub));
+        }
+        al = uni(al);
+        ah = uni(ah);
+        const unsigned long long lt = lanemask_lt();
+        if (len > kRHub) a.list[a.n - 1 - (int)(ah + (unsigned)__popcll(hub & lt))] = v;
+        else if (len > thr) a.list[al + (unsigned)__popcll(lng & lt)] = v;
+      }
+    }
+    if (len > thr) len = 0;
+    const unsigned long long bal = __ballot(len > 0);
+    const int na = (int)__popcll(bal);
+    if (na < 64) {  // rows with work to the front
+      const int rank = (int)__popcll(bal & lanemask_lt());
+      const int to = 4 * (len > 0 ? rank : na + lane - rank);
+      v = __builtin_amdgcn_ds_permute(to, v);
+      off = __builtin_amdgcn_ds_permute(to, off);
+      len = __builtin_amdgcn_ds_permute(to, len);
+    }
+    for (int i = 0; i < na; i += 2 * per) {
+      int vv[2], ll[2], cv[2][kRI];
+      unsigned wv[2][kRI];
+#pragma unroll
+      for (int p = 0; p < 2; ++p) {
+        const int src = min(i + p * per + grp, 63);
+        vv[p] = __shfl(v, src, 64);
+        const int o = __shfl(off, src, 64), l = __shfl(len, src, 64);
+        ll[p] = i + p * per + grp < 64 ? l : 0;
+        load_row<true>(a.col, a.w, o + kRI * sub, lim, kRI * sub < ll[p], cv[p], wv[p]);
+      }
+#pragma unroll
+      for (int p = 0; p < 2; ++p) {
+        const int rem = ll[p] - kRI * sub;
+        bool ok[kRI];
+#pragma unroll
+        for (int q = 0; q < kRI; ++q) ok[q] = q < rem && (unsigned)cv[p][q] < (unsigned)a.n;
+        int u = 0;
+        unsigned m;
+        if (group_winner<kKeyWeight>(ok, cv[p], wv[p], rem > 0, lg, gm, (unsigned)vv[p], a.S, u, m)) a.C[vv[p]] = u;
+      }
+    }
+  }
+}
+
+// The listed rows: hubs a workgroup each, then the others a wave each.
+constexpr int kHubLanes = 1024;
+__global__ __launch_bounds__(kHubLanes) void k_first_long(FirstRowsArgs a) {
+  __shared__ unsigned sw[kHubLanes / 64];
+  __shared__ int su[kHubLanes / 64];
+  if (a.totals->err) return;
+  const int tid = threadIdx.x, wv = uni(wave_id());
+  const int hubs = (int)a.totals->hubs, longs = (int)a.totals->longs;
+  for (int h = blockIdx.x; h < hubs; h += gridDim.x) {
+    const int v = uni(a.list[a.n - 1 - h]);
+    const int off = uni((int)a.rp[v]), len = uni((int)a.rp[v + 1]) - off;
+    unsigned bw = 0u;
+    int bu = 0;
+    row_best<kRI, kHubLanes>(a.col, a.w, off, len, tid, (int)a.nnz, a.n, (unsigned)v, a.S, bw, bu);
+    if (lane_id() == 0) {
+      sw[wv] = bw;
+      su[wv] = bu;
+    }
+    __syncthreads();
+    if (tid == 0) {
+      for (int i = 1; i < kHubLanes / 64; ++i) best_pair(bw, bu, sw[i], su[i], (unsigned)v, a.S);
+      if (bw != 0u) a.C[v] = bu;
+    }
+    __syncthreads();
+  }
+  for (int j = (int)blockIdx.x * (kHubLanes / 64) + wv; j < longs; j += (int)gridDim.x * (kHubLanes / 64)) {
+    const int v = uni(a.list[j]);
+    const int off = uni((int)a.rp[v]), len = uni((int)a.rp[v + 1]) - off;
+    unsigned bw = 0u;
+    int bu = 0;
+    row_best<kRI, 64>(a.col, a.w, off, len, lane_id(), (int)a.nnz, a.n, (unsigned)v, a.S, bw, bu);
+    if (lane_id() == 0 && bw != 0u) a.C[v] = bu;
+  }
+}
+
+// A step holds a row of twice the average: at one and a half times 3 % of an
+// RGG's rows are longer.
+int first_rows_lg(long long nnz, long long n) {
+  int lg = 1;
+  while (lg < 4 && ((long long)kRI << lg) * n < 2 * nnz) ++lg;
+  return lg;
+}
+
+hipError_t launch_first_rows(const FirstRowsArgs& a, int num_cus, hipStream_t s, hipEvent_t* ev) {
+  const long long blocks = (((long long)a.n + 63) / 64 + kWaves - 1) / kWaves;
+  const int grid = (int)std::max<long long>(1, std::min<long long>(blocks, (long long)num_cus * 64));
+  if (ev) hipExtLaunchKernelGGL(k_first_rows, dim3(grid), dim3(kBlock), 0, s, ev[0], ev[1], 0, a);
+  else hipLaunchKernelGGL(k_first_rows, dim3(grid), dim3(kBlock), 0, s, a);
+  if (hipGetLastError() != hipSuccess) return hipErrorUnknown;
+  hipLaunchKernelGGL(k_first_long, dim3((unsigned)std::min<long long>(2 * num_cus, (a.nnz + 8191) / 8192)),
+                     dim3(kHubLanes), 0, s, a);
+  if (hipGetLastError() != hipSuccess) return hipErrorUnknown;
+  return hipSuccess;
 }
 
 // A failed solve, or a guarded launch whose phases the device tail took over.

@@ -93,6 +93,7 @@ struct Totals {
   int t;    // current phase (1-based): read by the mutual check, advanced by the plan kernel
   int tail_from;  // guarded phases: the live set R_t the tail kernel takes over (0 = none yet)
   unsigned long long fp[2];  // LM_CHECK_GRAPH: fingerprints of the entries and of their mirrors
+  unsigned hubs, longs;      // rows left to k_first_long
   unsigned far, samp;        // sampled first entries of R_1 whose neighbour id is far from the row's
 };
 
@@ -350,6 +351,20 @@ struct SoloArgs {
   unsigned gen;
 };
 
+// First argmax of one weighted graph by whole rows (k_first_rows).
+struct FirstRowsArgs {
+  const long long* rp;
+  const int* col;
+  const float* w;
+  int* C;
+  int n;
+  long long nnz;
+  unsigned long long S;  // the seed of the candidates of phase 1
+  int lg;                // lanes per row (log2)
+  int* list;             // n words: the rows left to k_first_long
+  Totals* totals;
+};
+
 struct SoloOrder {
   const long long* vtx_off;
   const long long* rp;
@@ -391,6 +406,8 @@ hipError_t launch_first_argmax(const StreamArgs& a, int grid, hipStream_t s, boo
                                hipEvent_t* ev = nullptr, long long nnz = 0);
 hipError_t launch_compact(const StreamArgs& a, int grid, hipStream_t s, bool late = false, bool unweighted = false,
                           hipEvent_t* ev = nullptr);
+hipError_t launch_first_rows(const FirstRowsArgs& a, int num_cus, hipStream_t s, hipEvent_t* ev = nullptr);
+int first_rows_lg(long long nnz, long long n);
 // First argmax of R_1 of one graph read from its CSR (a.in.csr_rp set).
 hipError_t launch_first_csr(const StreamArgs& a, int grid, hipStream_t s, bool unweighted, hipEvent_t* ev = nullptr);
 int first_csr_blocks_per_cu(bool unweighted);

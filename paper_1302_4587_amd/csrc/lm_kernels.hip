@@ -51,6 +51,8 @@ __global__ void k_zero(Ctl* ctl, int nctl, Totals* totals, TailCtl* tc) {
     totals->tail_from = 0;
     totals->fp[0] = 0;
     totals->fp[1] = 0;
+    totals->hubs = 0;
+    totals->longs = 0;
     totals->far = 0;
     totals->samp = 0;
   }

@@ -114,6 +114,7 @@ extern "C" lm_status lm_match_noalloc(lm_ctx* c, const lm_csr* g, uint64_t seed,
   p.vtx_off = wk.vtxoff;
   p.mate = mate;
   p.gphase = nullptr;
+  p.seed = premix_seed(seed);
   lm_stats local;
   std::memset(&local, 0, sizeof(local));
   lm_stats* sp = st ? st : &local;

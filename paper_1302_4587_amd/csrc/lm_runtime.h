@@ -71,6 +71,7 @@ struct Problem {
   const long long* vtx_off = nullptr;  // device, G+1
   int* mate = nullptr;
   int* gphase = nullptr;  // optional per-graph phase counts
+  uint64_t seed = 0;      // G = 1: the graph's premixed seed
 };
 
 struct ContractState;  // buffers of lm_contract (lm_contract.hip)

@@ -442,6 +442,21 @@ lm_status Solver::run(const Problem& p, const Work& wk, hipStream_t s, uint32_t 
     pa.ctl_new = dctl + 0;
     pa.heads_of_runs = csr1 ? wk.bstat : nullptr;
     ENQ(launch_plan(pa, s, timing(LM_K_PLAN)));
+    if (csr1 && !unweighted) {  // whole rows: nothing to stitch afterwards
+      FirstRowsArgs fa;
+      fa.rp = p.row_ptr;
+      fa.col = p.col;
+      fa.w = p.w;
+      fa.C = wk.C;
+      fa.n = (int)p.N;
+      fa.nnz = p.nnz;
+      fa.S = cand_seed(p.seed, c.renew != 0, 1);
+      fa.lg = first_rows_lg(p.nnz, p.N);
+      fa.list = reinterpret_cast<int*>(wk.rows[0]);  // (R_1 has no piece records)
+      fa.totals = dtot;
+      ENQ(launch_first_rows(fa, num_cus, s, timing(LM_K_ARGMAX)));
+      return hipSuccess;
+    }
     StreamArgs sa;
     std::memset(&sa, 0, sizeof(sa));
     sa.c = c;
@@ -1003,6 +1018,7 @@ static lm_status solve_common(lm_ctx* c, int64_t N, int64_t nnz, int64_t G, cons
   p.vtx_off = (const long long*)S.vtxoff.p;
   p.mate = d_mate;
   p.gphase = graph_phases ? (int*)S.gphase.p : nullptr;
+  p.seed = premix_seed(seeds ? seeds[0] : seed0);
   lm_stats local;
   std::memset(&local, 0, sizeof(local));
   lm_stats* sp = st ? st : &local;
