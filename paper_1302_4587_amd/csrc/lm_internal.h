@@ -107,6 +107,16 @@ __host__ __device__ __forceinline__ bool bits_on(const Totals* t) {
   return t->samp > 0 && 4ull * t->far > 3ull * t->samp;
 }
 
+// The first compaction of one weighted graph takes whole rows (k_compact_rows)
+// when the first argmax listed no row for a whole workgroup and at most one for a
+// wave in 64 vertices: a wave takes such a row alone, two times over. ER with
+// 2^20 vertices of degree 10 beside rows of 1000 (2000) entries, whole solve by
+// piece windows -> by rows: none 386 -> 339 us, one in 100 vertices 577 -> 533,
+// one in 70 677 -> 659 (920 -> 917): the line is where the gain ends.
+__host__ __device__ __forceinline__ bool compact_by_rows(const Totals* t, int n) {
+  return t->hubs == 0u && 64ull * t->longs <= (unsigned long long)(unsigned)n;
+}
+
 // What the host loop needs after each plan, written by the plan kernel into
 // mapped coherent pinned host memory: the record is stored, made visible to
 // the system, and only then tagged (tag = gen << 32 | t), so the host polls the
@@ -177,6 +187,7 @@ struct StreamArgs {
   Common c;
   LiveSet in;
   int cand_phase;    // the phase whose candidates this launch computes (renewed keys)
+  int rows_first = 0;  // k_compact_rows was enqueued: do nothing where it took the launch
   // outputs (compaction only)
   Run* runs_out;
   int4* rows_out;
@@ -417,6 +428,11 @@ int first_csr_blocks_per_cu(bool unweighted);
 hipError_t launch_first_unw(const StreamArgs& a, int grid, hipStream_t s, bool vec_ok, hipEvent_t* ev = nullptr);
 int first_unw_ranges_per_cu();
 int first_unw_min_entries();
+// First compaction of one weighted graph (a.in.csr_rp set), if
+// compact_by_rows(); launch_compact with a.rows_first takes it otherwise.
+hipError_t launch_compact_rows(const StreamArgs& a, int grid, int lg, long long nnz, hipStream_t s,
+                               hipEvent_t* ev = nullptr);
+int compact_rows_per_cu();
 hipError_t launch_mutual(const MutualArgs& a, int grid, hipStream_t s, hipEvent_t* ev = nullptr);
 // grid must not exceed tail_blocks_per_cu() * CUs (every workgroup resident)
 hipError_t launch_tail(const TailArgs& a, int grid, hipStream_t s, hipEvent_t* ev = nullptr);

@@ -1520,6 +1520,7 @@ __global__ __launch_bounds__(kBlock, UNW ? (PPL > 1 ? 4 : 6) : (FIRST ? 4 : (PPL
   __shared__ StreamSmem<kBlock * PPL, stream_items<FIRST, UNW>()> sm;
   __shared__ unsigned s_err;
   if (block_failed(a.c, &s_err)) return;
+  if (VIEW == kViewCsr && !FIRST && !UNW && a.rows_first && compact_by_rows(a.c.totals, a.c.n)) return;
   Ctl ctl = *a.in.ctl;
   if (FIRST && ctl.Pf > 0) ctl.P = ctl.Pf;  // the first argmax's own split of R_1
   const unsigned long long seed0 = cand_seed(a.c.gseed[0], a.c.renew, a.cand_phase);

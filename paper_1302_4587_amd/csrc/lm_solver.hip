@@ -224,6 +224,7 @@ lm_status Solver::init_device(int device, size_t budget) {
   bpc_late_u = max_blocks_per_cu_stream(StreamKind::kLateCompact, true);
   bpc_tail = tail_blocks_per_cu();
   bpc_first_csr = first_csr_blocks_per_cu(false);
+  bpc_compact_rows = compact_rows_per_cu();
   bpc_first_unw = first_unw_ranges_per_cu();
   tun.block_entries = kCap;  // one batch: small phases still spread over every CU
   tun.grid_per_cu = 16;  // at most: the resident count of each kernel caps it
@@ -506,6 +507,10 @@ lm_status Solver::run(const Problem& p, const Work& wk, hipStream_t s, uint32_t 
         1, std::min<int64_t>(late ? pcap_late : pcap,
                              std::max<int64_t>(est_L / std::max(kCap, tun.block_entries),
                                                est_V / (kBlock * (late ? late_ppl(unweighted) : 1))) + 1));
+    if (t == 1 && csr1 && !unweighted) {
+      sa.rows_first = 1;
+      ENQ(launch_compact_rows(sa, std::min(gx, num_cus * bpc_compact_rows), first_rows_lg(p.nnz, p.N), p.nnz, s, timing(LM_K_COMPACT)));
+    }
     ENQ(launch_compact(sa, gx, s, late, unweighted, timing(LM_K_COMPACT)));
     PlanArgs pa = plan_base();  // sizes the next compaction, a late one
     pa.pcap = pcap_late;
