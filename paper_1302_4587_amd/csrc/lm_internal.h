@@ -281,7 +281,6 @@ struct InitArgs {
 // one entry buffer and writes the survivors to the same offset of the other.
 constexpr int kTailBlock = 1024;
 constexpr int kTailMaxBlocks = 128;
-constexpr int kTailArrive = 16;  // barrier arrival counters (workgroup b uses b % kTailArrive)
 constexpr int kTailShort = 16;
 
 struct TailSeg {
@@ -289,13 +288,11 @@ struct TailSeg {
   int ns, nl;                // short rows at [base, base + ns), long rows at [base + cap - nl, base + cap)
   long long kept;            // live entries of those rows
   long long md;              // entries of the rows this workgroup dropped as matched
-  unsigned long long mv;     // vertices this workgroup matched
+  unsigned long long mv;     // low word: vertices this workgroup matched; high word: closed rows it left in the list
 };
 
 struct TailCtl {
-  unsigned arrive[kTailArrive][32];  // one counter per 128-byte line
-  unsigned top[32];
-  unsigned gen[32];
+  unsigned tag[kTailMaxBlocks];      // exchanges workgroup b has reached
   unsigned abort[32];
   TailSeg seg[2][kTailMaxBlocks];    // segment table of the list phase t writes: seg[t & 1]
 };

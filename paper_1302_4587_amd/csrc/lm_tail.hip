@@ -6,22 +6,32 @@
 // inputs for this reason). k_tail takes the live set R_c the phase kernels
 // left behind and runs every remaining phase in one persistent launch:
 //
-//   mutual   every live vertex v with C[C[v]] = v is matched (mate, state);
-//   -------- grid barrier
-//   compact  every live row of an unmatched vertex keeps the entries whose
-//            neighbour is unmatched, writes them to the same offset of the
-//            other entry buffer and computes its new candidate C[v];
-//   -------- grid barrier
+//   phase    every live vertex v with C[C[v]] = v is matched (mate); every other
+//            live row keeps the entries whose neighbour u is not (C[C[u]] != u),
+//            writes them to the same offset of the other entry buffer and
+//            computes its new candidate;
+//   -------- exchange: the counts of the next list and a grid barrier in one
 //   log      the phase record (L_t, V_t, matched_t, matched entries_t).
+//
+// The candidates of two phases have to be there at once, since a neighbour's
+// partner is looked up while the next candidates are written: C holds one
+// phase's, mate the next one's (a vertex's own word until its row ends).
 //
 // Nothing is counted through a shared global counter (atomics on one address
 // serialise across the dies): workgroup b owns a segment of the next row list
 // and reports its counts in a table (TailCtl::seg) that every workgroup reads
-// after the barrier; within a workgroup rows are placed with LDS atomics. The
+// after the exchange; within a workgroup rows are placed with LDS atomics. The
 // row order is irrelevant to the result (the key order is strict, so every
 // vertex has one candidate whatever the order of its entries). Once a live
-// set is at most kTailSolo entries, workgroup 0 finishes alone and the grid
-// barriers become workgroup barriers.
+// set is at most kTailSolo entries, workgroup 0 finishes alone and the exchange
+// is a workgroup barrier.
+//
+// Bound by latency: a phase is a chain of four to five dependent loads across
+// the dies (3 to 5 us) and an exchange (7 to 9 us, the slowest workgroup's lag
+// included). With a mutual check and a compaction of their own, three barriers
+// and tables read apart, a phase took 16 to 20 us: RGG with 60 K vertices, all
+// phases here, 92 -> 79 us, the tail of R-MAT 20 (renewed keys) 110 -> 89, of
+// R-MAT 24 148 -> 115.
 #include <hip/hip_ext.h>
 
 #include "lm_device.h"
@@ -32,12 +42,12 @@ namespace lm {
 
 namespace {
 
-// Live entries workgroup 0 handles alone. A grid phase costs about 16 us down to
-// the smallest live set (two barriers of 3.5 to 4 us, the segment table, two
-// dependent round trips); alone, 14 K entries take 43 us, 8 K of R-MAT 43, 2 K
-// 15 and a hundred 6.
+// Live entries workgroup 0 handles alone. A grid phase costs about 12 us down to
+// the smallest live set; alone, 14 K entries took 43 us, 2 K take 11 and a
+// hundred 4.
 constexpr long long kTailSolo = 2048;
 constexpr int kTW = kTailBlock / 64;    // waves per workgroup
+constexpr int kLongStep = 4;            // entries per lane and step of a long row
 constexpr int kRunCache = kMaxBlocks + 1;
 
 __device__ __forceinline__ unsigned ld_u32(const unsigned* p) {
@@ -48,88 +58,107 @@ struct TailSmem {
   int pre_s[kTailMaxBlocks + 1];  // short rows of the current list before segment b
   int pre_l[kTailMaxBlocks + 1];  // long rows before segment b
   int sbase[kTailMaxBlocks], scap[kTailMaxBlocks];
-  long long red[3][kTW];
-  long long sum[3];
+  long long kept, md;           // the current list: its live entries, the entries matched on the way to it
+  unsigned long long mv;        // low word: vertices matched on the way to it; high word: its closed rows
+  long long kept_b, md_b;       // the same of this workgroup and the next list
+  unsigned long long mv_b;
   int cnt_s, cnt_l;  // rows this workgroup has placed in its segment
   unsigned ok;
   int rp[kRunCache];  // conversion: piece prefix of R_c's runs
 };
 
-// Barrier over the whole grid (every workgroup is resident: the host sizes
-// the grid from the occupancy of this kernel). Workgroup b arrives at counter
-// b % kTailArrive; the last arrival there arrives at the top counter, whose
-// last arrival resets it and advances the generation. The workgroup barrier
-// first waits for every lane's stores; lane 0 then makes them visible to the
-// other dies (release) before it arrives, polls the generation with plain
-// device-scope loads (an acquire per poll would invalidate the L2 under the
-// workgroups still working) and invalidates its caches once (acquire) when the
-// generation moves. A wait longer than `limit` ticks of the constant wall
-// clock, or another workgroup's abort, makes every workgroup give up (false).
-__device__ bool grid_sync(TailCtl* tc, unsigned nb, unsigned& gen, unsigned long long limit, Totals* tot,
-                          TailSmem& sm) {
+// Ends a phase: this workgroup's segment of the next list (base, cap, and the
+// counts in sm) goes to tab[b], and every workgroup's comes back as the
+// prefixes and sums in sm. This is also the barrier of the grid (every
+// workgroup is resident: the host sizes the grid from the occupancy of this
+// kernel): a workgroup stores the number `g` of the exchange behind its segment
+// and its first wave polls the others' numbers, two a lane, until all are
+// there. That is one store and one load across the dies, where counters took
+// two atomics, a store and a load. The workgroup barrier first waits
+// for every lane's stores; lane 0 then makes them visible to the other dies
+// (release) before it stores its number; the polls are plain device-scope loads
+// (an acquire per poll would invalidate the L2 under the workgroups still
+// working), and the caches are invalidated once (acquire) when all have come. A
+// wait longer than `limit` ticks of the constant wall clock, or another
+// workgroup's abort, makes every workgroup give up (false).
+__device__ bool exchange(TailCtl* tc, TailSeg* tab, int base, int cap, int nb, unsigned g, bool alone,
+                         unsigned long long limit, Totals* tot, TailSmem& sm) {
+  __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
-  if (threadIdx.x == 0) {
-    unsigned ok = 1u;
-    const unsigned g = gen;
-    const unsigned b = blockIdx.x;
-    const unsigned k = b % kTailArrive;
-    const unsigned members = nb / kTailArrive + (k < nb % kTailArrive ? 1u : 0u);
-    const unsigned groups = nb < (unsigned)kTailArrive ? nb : (unsigned)kTailArrive;
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");  // this die's stores reach the others
-    bool last = false;
-    if (__hip_atomic_fetch_add(&tc->arrive[k][0], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == members - 1) {
-      __hip_atomic_store(&tc->arrive[k][0], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      last = __hip_atomic_fetch_add(&tc->top[0], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == groups - 1;
+  if (wave_id() == 0) {
+    const int lane = lane_id();
+    const int b = (int)blockIdx.x;
+    bool ok = true;
+    TailSeg s0{}, s1{};
+    if (lane == 0) {
+      s0.base = base;
+      s0.cap = cap;
+      s0.ns = sm.cnt_s;
+      s0.nl = sm.cnt_l;
+      s0.kept = sm.kept_b;
+      s0.md = sm.md_b;
+      s0.mv = sm.mv_b;
+      sm.cnt_s = sm.cnt_l = 0;
+      sm.kept_b = sm.md_b = 0;
+      sm.mv_b = 0;
     }
-    if (last) {
-      __hip_atomic_store(&tc->top[0], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      __hip_atomic_store(&tc->gen[0], g + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    } else {
+    if (!alone) {
+      if (lane == 0) {
+        tab[b] = s0;
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");  // this die's stores reach the others
+        __hip_atomic_store(&tc->tag[b], g, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
       const unsigned long long t0 = wall_clock64();
-      while (__hip_atomic_load(&tc->gen[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == g) {
-        if (ld_u32(&tc->abort[0])) {
-          ok = 0u;
-          break;
-        }
-        if (wall_clock64() - t0 > limit) {
+      for (;;) {
+        const unsigned x0 = lane < nb ? ld_u32(&tc->tag[lane]) : g;
+        const unsigned x1 = lane + 64 < nb ? ld_u32(&tc->tag[lane + 64]) : g;
+        const unsigned stop = ld_u32(&tc->abort[0]);
+        if (__ballot((int)(x0 - g) < 0 || (int)(x1 - g) < 0) == 0ull) break;
+        const bool late = __ballot(wall_clock64() - t0 > limit) != 0ull;
+        if (late && lane == 0) {
           __hip_atomic_fetch_or(&tc->abort[0], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
           atomicOr(&tot->err, (unsigned)kErrInternal);
-          ok = 0u;
+        }
+        if (late || __ballot(stop != 0u) != 0ull) {
+          ok = false;
           break;
         }
-        __builtin_amdgcn_s_sleep(2);
+        __builtin_amdgcn_s_sleep(1);
       }
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");  // drop stale lines before the next step
+      s0 = lane < nb ? tab[lane] : TailSeg{};
+      s1 = lane + 64 < nb ? tab[lane + 64] : TailSeg{};
     }
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");  // drop stale lines before the next step
-    gen = g + 1u;
-    sm.ok = ok;
+    const int n = alone ? 1 : nb;
+    const int is0 = (int)wave_incl_sum_u32((unsigned)s0.ns), il0 = (int)wave_incl_sum_u32((unsigned)s0.nl);
+    const int is1 = (int)wave_incl_sum_u32((unsigned)s1.ns) + __builtin_amdgcn_readlane(is0, 63);
+    const int il1 = (int)wave_incl_sum_u32((unsigned)s1.nl) + __builtin_amdgcn_readlane(il0, 63);
+    if (lane < n) {
+      sm.pre_s[lane] = is0 - s0.ns;
+      sm.pre_l[lane] = il0 - s0.nl;
+      sm.sbase[lane] = s0.base;
+      sm.scap[lane] = s0.cap;
+    }
+    if (lane + 64 < n) {
+      sm.pre_s[lane + 64] = is1 - s1.ns;
+      sm.pre_l[lane + 64] = il1 - s1.nl;
+      sm.sbase[lane + 64] = s1.base;
+      sm.scap[lane + 64] = s1.cap;
+    }
+    const long long kept = wave_incl_sum<long long>(s0.kept + s1.kept);
+    const long long md = wave_incl_sum<long long>(s0.md + s1.md);
+    const long long mv = wave_incl_sum<long long>((long long)(s0.mv + s1.mv));
+    if (lane == 63) {
+      sm.pre_s[n] = is1;
+      sm.pre_l[n] = il1;
+      sm.kept = kept;
+      sm.md = md;
+      sm.mv = (unsigned long long)mv;
+      sm.ok = ok ? 1u : 0u;
+    }
   }
   __syncthreads();
   return sm.ok != 0u;
-}
-
-// Workgroup sums of three values; every lane gets them.
-__device__ __forceinline__ void block_sum3(long long& x0, long long& x1, long long& x2, TailSmem& sm) {
-  x0 = wave_incl_sum<long long>(x0);
-  x1 = wave_incl_sum<long long>(x1);
-  x2 = wave_incl_sum<long long>(x2);
-  if (lane_id() == 63) {
-    sm.red[0][wave_id()] = x0;
-    sm.red[1][wave_id()] = x1;
-    sm.red[2][wave_id()] = x2;
-  }
-  __syncthreads();
-  if (threadIdx.x < 3) {
-    long long s = 0;
-#pragma unroll
-    for (int i = 0; i < kTW; ++i) s += sm.red[threadIdx.x][i];
-    sm.sum[threadIdx.x] = s;
-  }
-  __syncthreads();
-  x0 = sm.sum[0];
-  x1 = sm.sum[1];
-  x2 = sm.sum[2];
-  __syncthreads();
 }
 
 // Places the rows of the lanes with `es` (short, front of the segment) or `el`
@@ -178,30 +207,45 @@ __device__ __forceinline__ int4 long_row(const TailSmem& sm, int nseg, const int
   return rows[sm.sbase[lo] + sm.scap[lo] - 1 - (j - sm.pre_l[lo])];
 }
 
-// Keeps the live entries of row r (unmatched vertex) in the next entry buffer
-// and returns how many; best gets the largest key among them. One lane.
-__device__ __forceinline__ int keep_row_lane(const Common& c, int4 r, int base, unsigned vloc, unsigned long long S,
-                                             const int* col, const float* w, int* ncol, float* nw, Best& best) {
+// The vertex x of the graph at `base` is matched in this phase: its candidate's
+// candidate. `a` is x's candidate; cur holds the phase's candidates (ids of the
+// graph).
+__device__ __forceinline__ int back(const Common& c, const int* cur, int base, int a) {
+  return a >= 0 && (unsigned)(base + a) < (unsigned)c.n ? cur[base + a] : -1;
+}
+
+// One phase of the row r (v's) by one lane: -1 if v is matched (with cv);
+// otherwise the entries of unmatched neighbours go to the next entry buffer,
+// their number is returned and best gets the largest key among them. The loads
+// of v's own check go with those of the first entries.
+__device__ __forceinline__ int row_lane(const Common& c, int4 r, int base, unsigned vloc, unsigned long long S,
+                                        const int* cur, const int* col, const float* w, int* ncol, float* nw, int& cv,
+                                        Best& best) {
+  constexpr int kW = 8;
   const bool unw = w == nullptr;
   const int off = r.y, len = r.z;
   int kept = 0;
-  for (int k0 = 0; k0 < len; k0 += 4) {
-    int u[4];
-    float x[4];
-    bool ok[4];
+  cv = cur[r.x];
+  for (int k0 = 0; k0 < len; k0 += kW) {
+    int u[kW], a[kW];
+    float x[kW];
+    bool ok[kW];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
+    for (int q = 0; q < kW; ++q) {
       ok[q] = k0 + q < len;
-      u[q] = ok[q] ? col[off + k0 + q] : 0;
+      u[q] = ok[q] ? col[off + k0 + q] : -1;
       x[q] = (ok[q] && !unw) ? w[off + k0 + q] : 1.0f;
       ok[q] = ok[q] && u[q] >= 0 && (unsigned)(base + u[q]) < (unsigned)c.n;
     }
-    unsigned char st[4];
+    const int own = k0 == 0 ? back(c, cur, base, cv) : -1;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) st[q] = ok[q] ? c.state[base + u[q]] : (unsigned char)1;
+    for (int q = 0; q < kW; ++q) a[q] = ok[q] ? cur[base + u[q]] : -1;
+    if (own == (int)vloc) return -1;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      if (st[q] == 0) {
+    for (int q = 0; q < kW; ++q) a[q] = back(c, cur, base, a[q]);
+#pragma unroll
+    for (int q = 0; q < kW; ++q) {
+      if (ok[q] && a[q] != u[q]) {
         ncol[off + kept] = u[q];
         if (!unw) nw[off + kept] = x[q];
         ++kept;
@@ -234,7 +278,6 @@ __global__ __launch_bounds__(kTailBlock) void k_tail(TailArgs a) {
   const Ctl ctl = *a.ctl[si];
   const int nb = (int)gridDim.x;
   const unsigned long long limit = a.spin_ticks;
-  unsigned bgen = 0;
   const bool unw = a.ew[0] == nullptr;
   const bool csr = c0 == 1 && a.csr_rp != nullptr;
   int4* TA = a.rows[c0 & 1];
@@ -244,8 +287,9 @@ __global__ __launch_bounds__(kTailBlock) void k_tail(TailArgs a) {
   const long long P = ctl.pieces;
   const int k0 = (int)(P * b / nb), k1 = (int)(P * (b + 1) / nb);
   if (tid == 0) {
-    sm.cnt_s = 0;
-    sm.cnt_l = 0;
+    sm.cnt_s = sm.cnt_l = 0;
+    sm.kept_b = sm.md_b = 0;
+    sm.mv_b = 0;
   }
   if (!csr) {
     for (int i = tid; i <= ctl.nruns && i < kRunCache; i += kTailBlock) sm.rp[i] = a.rpre[si][i];
@@ -328,241 +372,174 @@ __global__ __launch_bounds__(kTailBlock) void k_tail(TailArgs a) {
           el = !es;
         }
       }
+      if (c.graphs != 1 && (es || el)) c.mate[r.x] = c.C[r.x] - c.gbase[r.w];  // (cur below)
       place_rows(es, el, r, TA, k0, k1 - k0, sm);
     }
   }
-  __syncthreads();
-  if (tid == 0) {
-    TailSeg sg;
-    sg.base = k0;
-    sg.cap = k1 - k0;
-    sg.ns = sm.cnt_s;
-    sg.nl = sm.cnt_l;
-    sg.kept = 0;
-    sg.md = 0;
-    sg.mv = 0;
-    tc->seg[(c0 - 1) & 1][b] = sg;
-  }
-  if (!grid_sync(tc, nb, bgen, limit, tot, sm)) return;
+  unsigned g = 1;
+  if (!exchange(tc, tc->seg[(c0 - 1) & 1], k0, k1 - k0, nb, g, false, limit, tot, sm)) return;
   // ---- phases c, c + 1, ...
+  // Candidates, as ids of their graph: one phase's in C, the next one's in
+  // mate, which a vertex keeps until its row ends.
+  const int* cur = c.graphs == 1 ? c.C : c.mate;
+  int* nxt = c.graphs == 1 ? c.mate : c.C;
   const int4* rows = TA;
   int4* out = TB;
   int nseg = nb;  // segments of the current list
-  bool solo = false;
+  bool solo = false, stall = false;
   int t = c0;
-  long long L = ctl.L, prevL = 0, prevV = 0;
+  long long L = ctl.L, V = 0, prevL = 0, prevV = 0;
   int last_nonempty = 0;
   unsigned long long matched_total = 0;
   if (b == 0 && tid == 0) {
     last_nonempty = tot->last_nonempty;
     matched_total = tot->matched;
   }
+  int lo = 0, hi = 0, S = 0, Lg = 0, nwaves = kTW;
+  const int gw = b * kTW + wv;
   for (;;) {
-    // segment table of the current list (written by phase t - 1, or the conversion)
-    {
-      const TailSeg* tab = tc->seg[(t - 1) & 1];
-      TailSeg sg;
-      sg.ns = sg.nl = 0;
-      sg.base = sg.cap = 0;
-      sg.kept = sg.md = 0;
-      sg.mv = 0;
-      if (tid < nseg) sg = tab[tid];
-      if (tid < nseg) {
-        sm.sbase[tid] = sg.base;
-        sm.scap[tid] = sg.cap;
-      }
-      // exclusive prefix of ns and nl over the segments (nseg <= 128: waves 0 and 1)
-      const int is = (int)wave_incl_sum_u32((unsigned)sg.ns), il = (int)wave_incl_sum_u32((unsigned)sg.nl);
-      if (lane == 63 && wv < 2) {
-        sm.red[0][wv] = is;
-        sm.red[1][wv] = il;
-      }
-      __syncthreads();
-      if (wv < 2 && tid <= kTailMaxBlocks) {
-        const int cs = wv == 1 ? (int)sm.red[0][0] : 0, cl = wv == 1 ? (int)sm.red[1][0] : 0;
-        if (tid < nseg) {
-          sm.pre_s[tid] = cs + is - sg.ns;
-          sm.pre_l[tid] = cl + il - sg.nl;
+    S = sm.pre_s[nseg];
+    Lg = sm.pre_l[nseg];
+    V = (long long)S + Lg - (long long)(sm.mv >> 32);
+    if (t > c0) {
+      const unsigned mv = (unsigned)sm.mv;
+      L = sm.kept;
+      if (b == 0 && tid == 0) {  // the record of phase t - 1
+        if (t - 1 >= 1 && t - 1 <= a.log_cap) {
+          LogRec rec;
+          rec.live_entries = prevL;
+          rec.live_rows = prevV;
+          rec.matched_edges = mv / 2;
+          rec.matched_entries = sm.md;
+          a.log[t - 2] = rec;
         }
-        if (tid == nseg - 1) {
-          sm.pre_s[nseg] = cs + is;
-          sm.pre_l[nseg] = cl + il;
-        }
+        last_nonempty = t - 1;
+        matched_total += mv;
       }
-      __syncthreads();
-      long long kept = sg.kept, md = sg.md, mv = (long long)sg.mv;
-      block_sum3(kept, md, mv, sm);
-      if (t > c0) {
-        L = kept;
-        if (b == 0 && tid == 0) {  // the record of phase t - 1
-          if (t - 1 >= 1 && t - 1 <= a.log_cap) {
-            LogRec rec;
-            rec.live_entries = prevL;
-            rec.live_rows = prevV;
-            rec.matched_edges = mv / 2;
-            rec.matched_entries = md;
-            a.log[t - 2] = rec;
-          }
-          last_nonempty = t - 1;
-          matched_total += (unsigned long long)mv;
-        }
-        if (mv == 0) {  // nothing matched although edges were live: the input is not symmetric
-          if (b == 0 && tid == 0) atomicOr(&tot->err, (unsigned)kErrStall);
-          break;
-        }
-      }
+      stall = mv == 0u;  // nothing matched although edges were live: the input is not symmetric
+      if (stall && b == 0 && tid == 0) atomicOr(&tot->err, (unsigned)kErrStall);
     }
-    const int S = sm.pre_s[nseg], Lg = sm.pre_l[nseg];
-    const long long V = (long long)S + Lg;
-    if (L == 0 || V == 0) break;
-    if (!solo && L <= kTailSolo) {
+    const bool done = stall || L == 0 || V == 0;
+    if (!done && !solo && L <= kTailSolo) {
       solo = true;
       if (b != 0) return;  // workgroup 0 finishes alone
     }
     const int nbe = solo ? 1 : nb;
     // this workgroup's short rows [lo, hi); long row j goes to wave j % (nbe * kTW)
-    const int lo = (int)((long long)S * b / nbe), hi = (int)((long long)S * (b + 1) / nbe);
-    const int nwaves = nbe * kTW, gw = b * kTW + wv;
+    lo = (int)((long long)S * b / nbe);
+    hi = (int)((long long)S * (b + 1) / nbe);
+    nwaves = nbe * kTW;
+    if (done) break;
     const int q = Lg / nwaves, rmd = Lg % nwaves;
     const int longs_mine = kTW * q + min(max(rmd - b * kTW, 0), kTW);
     const int longs_before = b * kTW * q + min(rmd, b * kTW);
-    // ---- mutual check (rows striped over the workgroup's lanes)
-    long long mv_b = 0;
-    {
-      const int nmine = (hi - lo) + longs_mine;
-      for (int x = tid; x < nmine; x += kTailBlock) {
-        int4 r;
-        if (x < hi - lo) {
-          r = short_row(sm, nseg, rows, lo + x);
-        } else {
-          // the y-th long row of this workgroup: wave w's m-th (the first
-          // longs_mine - kTW q waves of the workgroup have q + 1, the rest q)
-          const int y = x - (hi - lo);
-          const int w = y % kTW, m = y / kTW;
-          const int j = (b * kTW + w) + m * nwaves;
-          if (j >= Lg) continue;
-          r = long_row(sm, nseg, rows, j);
-        }
-        const int v = r.x;
-        const int u = c.C[v];
-        if (c.gphase) atomicMax(&c.gphase[r.w], t);
-        if ((unsigned)u < (unsigned)c.n && c.C[u] == v) {
-          int base;
-          unsigned long long Sd;
-          graph_of(c, r.w, base, Sd);
-          c.mate[v] = u - base;
-          c.state[v] = 1;
-          ++mv_b;
-        }
-      }
-    }
-    {
-      long long z0 = 0, z1 = 0;
-      block_sum3(mv_b, z0, z1, sm);
-    }
-    if (solo) {
-      __syncthreads();
-    } else if (!grid_sync(tc, nb, bgen, limit, tot, sm)) {
-      return;
-    }
-    // ---- compaction fused with the next candidates
     const int obase = lo + longs_before, ocap = (hi - lo) + longs_mine;
-    if (tid == 0) {
-      sm.cnt_s = 0;
-      sm.cnt_l = 0;
-    }
-    __syncthreads();
+    const bool in_mate = cur == c.mate;
     long long kept_b = 0, md_b = 0;
+    unsigned long long mv_b = 0;
     int* ncol = a.ecol[ni];
     float* nw = unw ? nullptr : a.ew[ni];
+    // What a row's phase leaves behind: its partner, its next candidate, or
+    // nothing: mate is then -1 again. Where mate holds the candidates of this
+    // phase the others still read it, so the row stays for one more phase, closed
+    // (length 0).
+    auto close = [&](int4& r, int kept, int cv, int u, bool& es, bool& el) {
+      if (kept < 0) {
+        if (!in_mate) c.mate[r.x] = cv;
+        md_b += r.z;
+        ++mv_b;
+      } else if (kept > 0) {
+        nxt[r.x] = u;
+        kept_b += kept;
+        es = kept <= kTailShort;
+        el = !es;
+        r.z = kept;
+      } else if (in_mate) {
+        mv_b += 1ull << 32;
+        es = true;
+        r.z = 0;
+      } else {
+        c.mate[r.x] = -1;
+      }
+    };
     for (int i0 = lo + (tid & ~63); i0 < hi; i0 += kTailBlock) {
       const int i = i0 + lane;
       int4 r = make_int4(0, 0, 0, 0);
       bool es = false, el = false;
       if (i < hi) {
         r = short_row(sm, nseg, rows, i);
-        if (c.state[r.x]) {
-          md_b += r.z;
+        if (r.z == 0) {
+          c.mate[r.x] = -1;
         } else {
+          if (c.gphase) atomicMax(&c.gphase[r.w], t);
           int base;
           unsigned long long Sd;
           graph_of(c, r.w, base, Sd);
           Sd = cand_seed(Sd, c.renew, t + 1);  // the candidates of phase t + 1
-          const unsigned vloc = (unsigned)(r.x - base);
           Best best = best_ident();
-          const int kept = keep_row_lane(c, r, base, vloc, Sd, cur_col, cur_w, ncol, nw, best);
-          if (kept > 0) {
-            c.C[r.x] = base + best.u;
-            kept_b += kept;
-            r.z = kept;
-            es = kept <= kTailShort;
-            el = !es;
-          }
+          int cv;
+          const int kept = row_lane(c, r, base, (unsigned)(r.x - base), Sd, cur, cur_col, cur_w, ncol, nw, cv, best);
+          close(r, kept, cv, best.u, es, el);
         }
       }
       place_rows(es, el, r, out, obase, ocap, sm);
     }
     for (int j = gw; j < Lg; j += nwaves) {  // long rows, a wave each
-      const int4 r = long_row(sm, nseg, rows, j);
+      int4 r = long_row(sm, nseg, rows, j);
       const int v = r.x, off = r.y, len = r.z;
-      if (c.state[v]) {
-        if (lane == 0) md_b += len;
-        continue;
-      }
+      if (c.gphase && lane == 0) atomicMax(&c.gphase[r.w], t);
       int base;
       unsigned long long Sd;
       graph_of(c, r.w, base, Sd);
       Sd = cand_seed(Sd, c.renew, t + 1);  // the candidates of phase t + 1
       const unsigned vloc = (unsigned)(v - base);
+      const int cv = cur[v];
       Best best = best_ident();
-      int kept = 0;
+      int kept = back(c, cur, base, cv) == (int)vloc ? -1 : 0;
       const unsigned long long lt = lanemask_lt();
-      for (int e0 = 0; e0 < len; e0 += 64) {
-        const int e = e0 + lane;
-        bool ok = e < len;
-        const int u = ok ? cur_col[off + e] : 0;
-        const float x = (ok && !unw) ? cur_w[off + e] : 1.0f;
-        ok = ok && u >= 0 && (unsigned)(base + u) < (unsigned)c.n;
-        const bool keep = ok && c.state[base + u] == 0;
-        const unsigned long long bal = __ballot(keep);
-        if (keep) {
-          const int at = off + kept + (int)__popcll(bal & lt);
-          ncol[at] = u;
-          if (!unw) nw[at] = x;
-          best_update(best, ord_weight_bits(__float_as_uint(x)), u, vloc, Sd);
+      for (int e0 = 0; kept >= 0 && e0 < len; e0 += 64 * kLongStep) {
+        int u[kLongStep], x[kLongStep];
+        float w[kLongStep];
+        bool ok[kLongStep];
+#pragma unroll
+        for (int h = 0; h < kLongStep; ++h) {
+          const int e = e0 + 64 * h + lane;
+          ok[h] = e < len;
+          u[h] = ok[h] ? cur_col[off + e] : -1;
+          w[h] = (ok[h] && !unw) ? cur_w[off + e] : 1.0f;
+          ok[h] = ok[h] && u[h] >= 0 && (unsigned)(base + u[h]) < (unsigned)c.n;
         }
-        kept += (int)__popcll(bal);
+#pragma unroll
+        for (int h = 0; h < kLongStep; ++h) x[h] = ok[h] ? cur[base + u[h]] : -1;
+#pragma unroll
+        for (int h = 0; h < kLongStep; ++h) x[h] = back(c, cur, base, x[h]);
+#pragma unroll
+        for (int h = 0; h < kLongStep; ++h) {
+          const bool keep = ok[h] && x[h] != u[h];
+          const unsigned long long bal = __ballot(keep);
+          if (keep) {
+            const int at = off + kept + (int)__popcll(bal & lt);
+            ncol[at] = u[h];
+            if (!unw) nw[at] = w[h];
+            best_update(best, ord_weight_bits(__float_as_uint(w[h])), u[h], vloc, Sd);
+          }
+          kept += (int)__popcll(bal);
+        }
       }
       const Key kb = wave_max_key(best_key(best, vloc, Sd));
-      int4 rr = r;
-      rr.z = kept;
-      if (lane == 0 && kept > 0) {
-        c.C[v] = base + kb.u;
-        kept_b += kept;
-      }
-      const bool live = kept > 0 && lane == 0;
-      place_rows(live && kept <= kTailShort, live && kept > kTailShort, rr, out, obase, ocap, sm);
+      bool es = false, el = false;
+      if (lane == 0) close(r, kept, cv, kb.u, es, el);
+      place_rows(es, el, r, out, obase, ocap, sm);
     }
-    {
-      long long z = 0;
-      block_sum3(kept_b, md_b, z, sm);
+    kept_b = wave_incl_sum<long long>(kept_b);
+    md_b = wave_incl_sum<long long>(md_b);
+    mv_b = (unsigned long long)wave_incl_sum<long long>((long long)mv_b);
+    if (lane == 63) {
+      atomicAdd(reinterpret_cast<unsigned long long*>(&sm.kept_b), (unsigned long long)kept_b);
+      atomicAdd(reinterpret_cast<unsigned long long*>(&sm.md_b), (unsigned long long)md_b);
+      atomicAdd(&sm.mv_b, mv_b);
     }
-    if (tid == 0) {
-      TailSeg sg;
-      sg.base = obase;
-      sg.cap = ocap;
-      sg.ns = sm.cnt_s;
-      sg.nl = sm.cnt_l;
-      sg.kept = kept_b;
-      sg.md = md_b;
-      sg.mv = (unsigned long long)mv_b;
-      tc->seg[t & 1][b] = sg;
-    }
-    if (solo) {
-      __syncthreads();
-    } else if (!grid_sync(tc, nb, bgen, limit, tot, sm)) {
-      return;
-    }
+    if (!exchange(tc, tc->seg[t & 1], obase, ocap, nb, ++g, solo, limit, tot, sm)) return;
     // next live set
     prevL = L;
     prevV = V;
@@ -573,8 +550,18 @@ __global__ __launch_bounds__(kTailBlock) void k_tail(TailArgs a) {
     cur_col = ncol;
     cur_w = nw;
     ni ^= 1;
+    int* held = const_cast<int*>(cur);
+    cur = nxt;
+    nxt = held;
     ++t;
   }
+  // rows that were closed in the last phase, or all of them after a stall
+  for (int i = lo + tid; i < hi; i += kTailBlock) {
+    const int4 r = short_row(sm, nseg, rows, i);
+    if (stall || r.z == 0) c.mate[r.x] = -1;
+  }
+  if (stall && lane == 0)
+    for (int j = gw; j < Lg; j += nwaves) c.mate[long_row(sm, nseg, rows, j).x] = -1;
   if (b == 0 && tid == 0) {
     tot->last_nonempty = last_nonempty;
     tot->matched = matched_total;
