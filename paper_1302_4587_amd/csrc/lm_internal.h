@@ -309,7 +309,10 @@ struct TailArgs {
   int row_cap;         // records per row buffer
   int* ecol[2];
   float* ew[2];        // nullptr: unweighted
-  const long long* csr_rp;  // R_1 of one graph read from the input CSR, else nullptr
+  // the tail is the whole solve of one graph: it starts from the input CSR (rows
+  // checked and first candidates found here), else nullptr
+  const long long* csr_rp;
+  long long n, nnz;         // of that graph
   const int* in_col;        // the input entries (R_1's)
   const float* in_w;
   LogRec* log;
@@ -321,17 +324,18 @@ struct TailArgs {
 
 // Whole graphs solved by one workgroup each (k_solo).
 constexpr long long kSoloMaxN = 65536;     // vertices: candidates are 16-bit local ids in LDS
-// Entries up to which a single graph is solved by one workgroup: beyond them
-// the phase kernels and the tail kernel, spread over the chip, are faster.
-// Measured (us a call, one workgroup / spread): weighted ER of average degree
-// 16 with 131 K entries 156 / 243, with 262 K 279 / 276; weighted R-MAT with
-// 97 K 220 / 222, with 204 K 434 / 270; unweighted (every entry hashed) RGG
-// with 40 K 109 / 168, with 81 K 198 / 189; unweighted R-MAT with 46 K
-// 186 / 211, with 97 K 277 / 223. A batch has a workgroup for every graph
-// and is faster this way throughout (2 graphs of 2^15 to 2^16 vertices 874 /
-// 2313, 256 of them 2251 / 4821).
-constexpr long long kSoloEntries = 3 << 15;
-constexpr long long kSoloEntriesUnw = 1 << 16;
+// Entries up to which a single graph is solved by one workgroup; beyond them the
+// tail kernel takes it, spread over the chip. Measured (us a call, one workgroup /
+// spread): weighted ER of average degree 16 with 33 K entries 82 / 122, with 66 K
+// 103 / 120, with 99 K 141 / 128; RGG with 32 K 69 / 79, with 64 K 109 / 89, with
+// 98 K 149 / 90; R-MAT, which has more phases, with 10 K 102 / 97, with 46 K
+// 235 / 125. Unweighted (every entry hashed) ER with 50 K 104 / 122, with 66 K
+// 120 / 126; RGG with 32 K 100 / 93, with 48 K 130 / 93; R-MAT with 21 K
+// 117 / 124, with 46 K 182 / 124. A batch has a workgroup for every graph and is
+// faster this way throughout (2 graphs of 2^15 to 2^16 vertices 874 / 2313, 256
+// of them 2251 / 4821).
+constexpr long long kSoloEntries = 1 << 16;
+constexpr long long kSoloEntriesUnw = 1 << 15;
 constexpr int kSoloClasses = 3;            // size classes of a batch's graphs
 
 struct SoloArgs {

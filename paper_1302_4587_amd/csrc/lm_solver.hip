@@ -400,6 +400,12 @@ lm_status Solver::run(const Problem& p, const Work& wk, hipStream_t s, uint32_t 
     if (_e != hipSuccess) return _e;  \
   } while (0)
   // live set R_1 from the input and the first argmax over it
+  // One graph that the tail kernel takes from the first phase on needs nothing
+  // before it: it reads R_1 and finds the first candidates itself (with k_init,
+  // k_plan, the first argmax and its listed rows, and a row list behind them:
+  // RGG with 60 K vertices 130 us a call, now 120; ER with 20 K vertices of degree
+  // 16 200 -> 152; R-MAT 14 221 -> 148).
+  const bool direct = csr1 && (dev_ctl ? p.nnz <= tail_at : tun.tail_entries > 0 && p.nnz <= tun.tail_entries);
   auto enqueue_prologue = [&]() -> hipError_t {
     ENQ(launch_zero(dctl, 2, dtot, s, wk.tail));
     if (p.gphase) ENQ(launch_fill_i32(p.gphase, p.G, 0, s));
@@ -408,6 +414,7 @@ lm_status Solver::run(const Problem& p, const Work& wk, hipStream_t s, uint32_t 
       const int grid = (int)std::min<int64_t>(pmcap, (p.N + kBlock - 1) / kBlock + 1);
       ENQ(launch_check(ca, grid, s));
     }
+    if (direct) return hipSuccess;
     // (a workgroup per 16384 vertices took 30 us for 60 K and 36 for 1 M
     // vertices, one per round of kCap 5 and 10)
     const int pi = (int)std::max<int64_t>(1, std::min<int64_t>(pcap, (p.N + kCap - 1) / kCap));
@@ -547,7 +554,9 @@ lm_status Solver::run(const Problem& p, const Work& wk, hipStream_t s, uint32_t 
       ta.ew[i] = unweighted ? nullptr : wk.ew[i];
     }
     ta.row_cap = (int)(p.N + 2 * kMaxBlocks + 16);
-    ta.csr_rp = csr1 ? p.row_ptr : nullptr;
+    ta.csr_rp = direct ? p.row_ptr : nullptr;
+    ta.n = p.N;
+    ta.nnz = p.nnz;
     ta.in_col = p.col;
     ta.in_w = p.w;
     ta.log = d_log;
@@ -558,6 +567,7 @@ lm_status Solver::run(const Problem& p, const Work& wk, hipStream_t s, uint32_t 
     // workgroups (1024 lanes each): about one per 4096 live entries (per 16384:
     // the first phase of 600 K entries 23 us; 320 K unweighted ER entries solved
     // in 237 us against 211)
+    if (direct) L_hint = p.nnz;
     const long long want = L_hint < 0 ? tail_cap : (L_hint + 4095) / 4096;
     const int grid = (int)std::max<long long>(1, std::min<long long>(tail_cap, want));
     ENQ(launch_tail(ta, grid, s, timing(LM_K_TAIL)));
@@ -753,21 +763,27 @@ lm_status Solver::run(const Problem& p, const Work& wk, hipStream_t s, uint32_t 
     st->k_bytes[LM_K_INIT] = 8.0 * (N + 1.0) + (csr1 ? 9.0 * N : 5.0 * N + 16.0 * V1);
     const double eb = unweighted ? 4.0 : 8.0;  // bytes of one entry: col (+ w)
     st->k_bytes[LM_K_ARGMAX] = (csr1 ? 8.0 * (N + 1.0) : 16.0 * V1) + eb * L1 + 4.0 * V1;
+    if (direct) {
+      st->k_bytes[LM_K_INIT] = st->k_bytes[LM_K_ARGMAX] = 0.0;
+      st->k_bytes[LM_K_TAIL] = 16.0 * N + eb * L1 + 16.0 * V1;
+    }
     // Phases from tail_from on ran in the tail kernel: per phase a 16-byte row
-    // record read twice (mutual check, compaction), C[v] and the C[C[v]]
-    // gather, 5 bytes per matched vertex, the live entries of unmatched rows
-    // with their neighbour's state, the survivors, and a 16-byte record plus
-    // C[v] per next live row; starting from R_c with c >= 2 it first copies
-    // the L_c entries to their virtual positions (a read and a write each) and
-    // reads R_c's piece records.
+    // record, C[v] and the C[C[v]] gather, 4 bytes per matched vertex, the live
+    // entries of unmatched rows with their neighbour's candidate and its
+    // candidate, the survivors, and a 16-byte record plus C[v] per next live
+    // row; starting from R_c with c >= 2 it first copies the L_c entries to
+    // their virtual positions (a read and a write each), reads R_c's piece
+    // records and writes its row list. Where the tail is the whole solve it does
+    // the first argmax itself: 8 bytes of row_ptr, C and mate per vertex, the
+    // entries, and a 16-byte record per row.
     for (int i = 0; i < nrec; ++i) {
       const double L = (double)recs(i).live_entries, V = (double)recs(i).live_rows;
       const double mv = 2.0 * (double)recs(i).matched_edges, md = (double)recs(i).matched_entries;
       const double L2 = (double)recs(i + 1).live_entries, V2 = (double)recs(i + 1).live_rows;
       const bool from_csr = csr1 && i == 0;
       if (tail_from > 0 && i + 1 >= tail_from) {
-        double b = 24.0 * V + 5.0 * mv + 16.0 * V + (eb + 1.0) * (L - md) + eb * L2 + 20.0 * V2;
-        if (i + 1 == tail_from) b += (tail_from >= 2 ? 2.0 * eb * L : 0.0) + (from_csr ? 16.0 * N : 32.0 * V);
+        double b = 24.0 * V + 4.0 * mv + (eb + 8.0) * (L - md) + eb * L2 + 20.0 * V2;
+        if (i + 1 == tail_from) b += (tail_from >= 2 ? 2.0 * eb * L : 0.0) + (direct ? 0.0 : 32.0 * V);
         st->k_bytes[LM_K_TAIL] += b;
         continue;
       }

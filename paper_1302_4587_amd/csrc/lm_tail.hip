@@ -47,6 +47,7 @@ namespace {
 // hundred 4.
 constexpr long long kTailSolo = 2048;
 constexpr int kTW = kTailBlock / 64;    // waves per workgroup
+constexpr int kChunk = 8;               // vertices dealt to a workgroup at a time
 constexpr int kLongStep = 4;            // entries per lane and step of a long row
 constexpr int kRunCache = kMaxBlocks + 1;
 
@@ -214,6 +215,26 @@ __device__ __forceinline__ int back(const Common& c, const int* cur, int base, i
   return a >= 0 && (unsigned)(base + a) < (unsigned)c.n ? cur[base + a] : -1;
 }
 
+// The entry of largest key of the input row r. One lane.
+__device__ __forceinline__ void first_lane(const Common& c, int4 r, unsigned long long S, const int* col,
+                                           const float* w, Best& best) {
+  constexpr int kW = 8;
+  for (int k0 = 0; k0 < r.z; k0 += kW) {
+    int u[kW];
+    float x[kW];
+#pragma unroll
+    for (int q = 0; q < kW; ++q) {
+      const bool in = k0 + q < r.z;
+      u[q] = in ? col[r.y + k0 + q] : -1;
+      x[q] = in && w ? w[r.y + k0 + q] : 1.0f;
+    }
+#pragma unroll
+    for (int q = 0; q < kW; ++q)
+      if ((unsigned)u[q] < (unsigned)c.n)
+        best_update(best, ord_weight_bits(__float_as_uint(x[q])), u[q], (unsigned)r.x, S);
+  }
+}
+
 // One phase of the row r (v's) by one lane: -1 if v is matched (with cv);
 // otherwise the entries of unmatched neighbours go to the next entry buffer,
 // their number is returned and best gets the largest key among them. The loads
@@ -262,7 +283,10 @@ __device__ __forceinline__ int row_lane(const Common& c, int4 r, int base, unsig
 // the phase kernels becomes the tail's first row list: one row per live
 // vertex, its entries at the vertex's virtual position. Rows cut into several
 // pieces are contiguous there, so for c >= 2 every run is copied to its
-// virtual range first. R_1 needs no copy: its entries are the input rows.
+// virtual range first. R_1 needs no copy: its entries are the input rows. Where
+// the tail is the whole solve of one graph (csr_rp) the list is made from the
+// CSR, its offsets checked as k_init does, and the first candidates with it:
+// short rows by a lane each, the others, listed first, by a wave each.
 __global__ __launch_bounds__(kTailBlock) void k_tail(TailArgs a) {
   __shared__ TailSmem sm;
   Common& c = a.c;
@@ -283,9 +307,16 @@ __global__ __launch_bounds__(kTailBlock) void k_tail(TailArgs a) {
   int4* TA = a.rows[c0 & 1];
   int4* TB = a.rows[(c0 + 1) & 1];
   // ---- conversion: workgroup b takes pieces [P b / nb, P (b + 1) / nb), its
-  // segment of the first row list starts at P b / nb
-  const long long P = ctl.pieces;
-  const int k0 = (int)(P * b / nb), k1 = (int)(P * (b + 1) / nb);
+  // segment of the first row list starts at P b / nb. From the CSR it takes
+  // every nb-th kChunk vertices (8 offsets are a line; neighbours in a skewed
+  // graph's order go to other workgroups).
+  const long long P = csr ? a.n : ctl.pieces;
+  int k0 = (int)(P * b / nb), k1 = (int)(P * (b + 1) / nb);
+  if (csr) {
+    const int chunks = (int)((P + kChunk - 1) / kChunk), q = chunks / nb, r = chunks % nb;
+    k0 = kChunk * (q * b + min(b, r));
+    k1 = k0 + kChunk * (q + (b < r ? 1 : 0));
+  }
   if (tid == 0) {
     sm.cnt_s = sm.cnt_l = 0;
     sm.kept_b = sm.md_b = 0;
@@ -307,19 +338,52 @@ __global__ __launch_bounds__(kTailBlock) void k_tail(TailArgs a) {
     cur_w = unw ? nullptr : a.ew[(c0 + 1) & 1];
     ni = c0 & 1;
   }
-  if (csr) {  // piece k is vertex k (empty rows are pieces of length 0)
-    for (int v0 = k0 + (tid & ~63); v0 < k1; v0 += kTailBlock) {
-      const int v = v0 + lane;
+  if (csr) {  // rows and first candidates from the input
+    const unsigned long long Sd = cand_seed(c.gseed[0], c.renew, 1);
+    unsigned err = b == 0 && tid == 0 && (a.csr_rp[0] != 0 || a.csr_rp[c.n] != a.nnz) ? (unsigned)kErrRowPtr : 0u;
+    for (int x0 = k0 + (tid & ~63); x0 < k1; x0 += kTailBlock) {
+      const int x = x0 + lane - k0;
+      const long long v = ((long long)(x / kChunk) * nb + b) * kChunk + x % kChunk;
       int4 r = make_int4(0, 0, 0, 0);
       bool es = false, el = false;
-      if (v < k1) {
-        const long long e0 = a.csr_rp[v], e1 = a.csr_rp[v + 1];
-        const int len = (int)(e1 - e0);
-        r = make_int4(v, (int)e0, len, 0);
-        es = len > 0 && len <= kTailShort;
-        el = len > kTailShort;
+      if (x < k1 - k0 && v < P) {
+        const long long e0 = a.csr_rp[v], d = a.csr_rp[v + 1] - e0;
+        if (d < 0 || e0 < 0 || e0 + d > a.nnz) err |= kErrRowPtr;
+        if (d > 0x7fff0000LL) err |= kErrDegree;
+        const bool ok = d > 0 && d <= 0x7fff0000LL && e0 >= 0 && e0 + d <= a.nnz;
+        r = make_int4((int)v, (int)e0, (int)d, 0);
+        es = ok && d <= kTailShort;
+        el = ok && !es;
+        Best best = best_ident();
+        if (es) first_lane(c, r, Sd, cur_col, cur_w, best);
+        c.mate[v] = -1;
+        if (!el) c.C[v] = best.u;
       }
       place_rows(es, el, r, TA, k0, k1 - k0, sm);
+    }
+    if (err) atomicOr(&tot->err, err);
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+    const int nl = sm.cnt_l;
+    for (int j = wv; j < nl; j += kTW) {
+      const int4 r = TA[k1 - 1 - j];
+      Best best = best_ident();
+      for (int e0 = 0; e0 < r.z; e0 += 64 * kLongStep) {
+        int u[kLongStep];
+        float w[kLongStep];
+#pragma unroll
+        for (int h = 0; h < kLongStep; ++h) {
+          const int e = e0 + 64 * h + lane;
+          u[h] = e < r.z ? cur_col[r.y + e] : -1;
+          w[h] = e < r.z && !unw ? cur_w[r.y + e] : 1.0f;
+        }
+#pragma unroll
+        for (int h = 0; h < kLongStep; ++h)
+          if ((unsigned)u[h] < (unsigned)c.n)
+            best_update(best, ord_weight_bits(__float_as_uint(w[h])), u[h], (unsigned)r.x, Sd);
+      }
+      const Key kb = wave_max_key(best_key(best, (unsigned)r.x, Sd));
+      if (lane == 0) c.C[r.x] = kb.u;
     }
   } else {
     const Run* runs = a.runs[si];
@@ -378,6 +442,7 @@ __global__ __launch_bounds__(kTailBlock) void k_tail(TailArgs a) {
   }
   unsigned g = 1;
   if (!exchange(tc, tc->seg[(c0 - 1) & 1], k0, k1 - k0, nb, g, false, limit, tot, sm)) return;
+  if (csr && ld_u32(&tot->err)) return;  // (the same word everywhere: nothing is added before the next exchange)
   // ---- phases c, c + 1, ...
   // Candidates, as ids of their graph: one phase's in C, the next one's in
   // mate, which a vertex keeps until its row ends.
@@ -388,7 +453,7 @@ __global__ __launch_bounds__(kTailBlock) void k_tail(TailArgs a) {
   int nseg = nb;  // segments of the current list
   bool solo = false, stall = false;
   int t = c0;
-  long long L = ctl.L, V = 0, prevL = 0, prevV = 0;
+  long long L = csr ? a.nnz : ctl.L, V = 0, prevL = 0, prevV = 0;
   int last_nonempty = 0;
   unsigned long long matched_total = 0;
   if (b == 0 && tid == 0) {

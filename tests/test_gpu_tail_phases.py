@@ -101,3 +101,22 @@ def test_union(ctx, weights):
             ctx.set_tuning(**saved)
             assert np.array_equal(mate.cpu().numpy(), want)
             assert np.array_equal(np.asarray(gp), phases)
+
+
+@pytest.mark.parametrize("fault", ["end", "start", "falling", "beyond"])
+def test_bad_offsets(ctx, fault):
+    """A solve that starts in the tail reports offsets that are no CSR's, as the others do."""
+    import torch
+    import paper_1302_4587_amd as lm
+    from paper_1302_4587_amd import _lib as L
+    g = _graph(15000, 8, 3, "uniform")
+    rp = g.row_ptr.copy()
+    at, value = {"end": (-1, g.nnz - 1), "start": (0, 1), "falling": (777, rp[776] - 1), "beyond": (9000, g.nnz + 5)}[fault]
+    rp[at] = value
+    col, w = torch.from_numpy(g.col).cuda(), torch.from_numpy(g.w).cuda()
+    print(f"case: bad offsets {fault}", flush=True)
+    with pytest.raises(lm.LMError) as e:
+        ctx.match(torch.from_numpy(rp).cuda(), col, w, seed=1)
+    assert e.value.status == L.LM_EGRAPH
+    mate, _ = ctx.match(torch.from_numpy(g.row_ptr).cuda(), col, w, seed=1)
+    assert np.array_equal(mate.cpu().numpy(), oracle.local_max_graph(g, 1)[0])
