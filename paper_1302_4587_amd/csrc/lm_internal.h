@@ -434,6 +434,11 @@ int first_unw_min_entries();
 hipError_t launch_compact_rows(const StreamArgs& a, int grid, int lg, long long nnz, hipStream_t s,
                                hipEvent_t* ev = nullptr);
 int compact_rows_per_cu();
+// The same of one unweighted graph of at least compact_unw_min_entries()
+// entries, a.in.ctl->P one-wave ranges.
+hipError_t launch_compact_unw(const StreamArgs& a, int grid, hipStream_t s, hipEvent_t* ev = nullptr);
+int compact_unw_per_cu();
+int compact_unw_min_entries();
 hipError_t launch_mutual(const MutualArgs& a, int grid, hipStream_t s, hipEvent_t* ev = nullptr);
 // grid must not exceed tail_blocks_per_cu() * CUs (every workgroup resident)
 hipError_t launch_tail(const TailArgs& a, int grid, hipStream_t s, hipEvent_t* ev = nullptr);

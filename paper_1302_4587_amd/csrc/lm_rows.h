@@ -6,6 +6,7 @@
 #include <hip/hip_runtime.h>
 
 #include "lm_device.h"
+#include "lm_internal.h"
 #include "lm_key.h"
 
 namespace lm {
@@ -200,6 +201,80 @@ __device__ __forceinline__ void row_best(const int* col, const float* wt, int of
     const unsigned long long win = __ballot(group_winner<kKeyWeight>(ok, cv, wv, k < len, 6, ~0ull, v, S, x, m));
     if (m != 0u) best_pair(w, u, uni(m), __shfl(x, __ffsll((long long)win) - 1, 64), v, S);
   }
+}
+
+// ---- ranges of R_1's entries, a wave each (unweighted graphs: lm_first.hip, lm_compact.hip)
+
+// Smallest i in [lo, hi) with pred(i) true (pred monotone), hi if none; every
+// lane gets the answer. 64 points per round, one memory access per lane.
+template <typename Pred>
+__device__ __forceinline__ long long wave_lower_bound(long long lo, long long hi, Pred pred) {
+  const int lane = lane_id();
+  while (hi > lo) {
+    const long long n = hi - lo;
+    const long long step = (n + 63) >> 6;
+    const long long idx = lo + (long long)lane * step;
+    const bool p = idx < hi ? pred(idx) : true;
+    const unsigned long long bal = __ballot(p);
+    if (bal == 0ull) {  // false at every sampled point: the answer lies past the last one
+      lo = lo + 63 * step + 1;
+      continue;
+    }
+    const int f = __ffsll((long long)bal) - 1;
+    if (f == 0) return lo;
+    // false at lo + (f-1) step, true at lo + f step (or that point is past hi)
+    const long long nhi = lo + (long long)f * step < hi ? lo + (long long)f * step : hi;
+    lo = lo + (long long)(f - 1) * step + 1;
+    hi = nhi;
+  }
+  return lo;
+}
+
+// The entry position of cost c over R_1 read from the CSR (kPieceCostFirst units per row, one
+// per entry, as the other first-argmax kernels split it).
+__device__ __forceinline__ long long wave_csr_entry_at(const long long* rp, long long n, long long c) {
+  constexpr long long K = kPieceCostFirst;
+  const long long v1 = wave_lower_bound(0, n + 1, [&](long long v) { return rp[v] + K * v > c; });
+  const long long v = v1 - 1;
+  const long long u = c - (rp[v] + K * v);
+  if (u < K || v >= n) return rp[v];
+  const long long deg = rp[v + 1] - rp[v];
+  return rp[v] + min(u - K, deg);
+}
+
+__device__ __forceinline__ Part unw_part(long long v, int flags, bool any, unsigned long long h,
+                                         unsigned long long S) {
+  Part p;
+  p.v = (int)v;
+  p.flags = flags;
+  p.kept = 0;
+  p.out_row = -1;
+  p.w = any ? kUnitOrd : 0u;
+  p.hhi = any ? (unsigned)(h >> 32) : 0u;
+  p.hlo = any ? (unsigned)h : 0u;
+  p.u = any ? hash_neighbour(h, S, (unsigned)v) : -1;
+  return p;
+}
+
+// The workgroup is one wave: LDS accesses of its lanes are carried out in
+// issue order, so lanes exchange data through LDS with no s_barrier and no
+// wait for the stores; this only keeps the compiler from moving LDS accesses
+// across the point.
+__device__ __forceinline__ void wave_lds_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// One lane to the left across the wave (lane 63 gets ident).
+__device__ __forceinline__ unsigned dpp_wave_shl1(unsigned x, unsigned ident) {
+  return (unsigned)__builtin_amdgcn_update_dpp((int)ident, (int)x, 0x130, 0xf, 0xf, false);
+}
+
+__device__ __forceinline__ long long rdl64(long long x, int l) {
+  const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)x, l);
+  const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)((unsigned long long)x >> 32), l);
+  return (long long)(((unsigned long long)hi << 32) | lo);
 }
 
 }  // namespace lm

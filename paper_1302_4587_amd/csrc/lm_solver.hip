@@ -326,7 +326,8 @@ lm_status Solver::run(const Problem& p, const Work& wk, hipStream_t s, uint32_t 
   // (the weighted first argmax reads R_1 from the CSR for a batch too)
   const int bf = unweighted ? (csr1 ? bpc_first_unw : bpc_first_u) : bpc_first_csr;
   const int bl = unweighted ? bpc_late_u : bpc_late;
-  const int pcap = std::max(1, std::min(kMaxBlocks, num_cus * std::max(1, std::min(tun.grid_per_cu, bs))));
+  const bool unw1 = csr1 && unweighted && p.nnz >= compact_unw_min_entries();  // one-wave ranges
+  const int pcap = std::max(1, std::min(kMaxBlocks, num_cus * std::max(1, std::min(tun.grid_per_cu, unw1 ? compact_unw_per_cu() : bs))));
   // R_1 feeds the first argmax and the first compaction, each split to its
   // own resident count; later live sets feed compactions with the wider piece
   // window, which fit fewer workgroups per CU
@@ -518,7 +519,11 @@ lm_status Solver::run(const Problem& p, const Work& wk, hipStream_t s, uint32_t 
       sa.rows_first = 1;
       ENQ(launch_compact_rows(sa, std::min(gx, num_cus * bpc_compact_rows), first_rows_lg(p.nnz, p.N), p.nnz, s, timing(LM_K_COMPACT)));
     }
-    ENQ(launch_compact(sa, gx, s, late, unweighted, timing(LM_K_COMPACT)));
+    if (t == 1 && unw1) {
+      ENQ(launch_compact_unw(sa, gx, s, timing(LM_K_COMPACT)));
+    } else {
+      ENQ(launch_compact(sa, gx, s, late, unweighted, timing(LM_K_COMPACT)));
+    }
     PlanArgs pa = plan_base();  // sizes the next compaction, a late one
     pa.pcap = pcap_late;
     pa.mode = kPlanFix | kPlanPrefix | kPlanLog | kPlanTick;
