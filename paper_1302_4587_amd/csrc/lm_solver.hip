@@ -594,12 +594,15 @@ lm_status Solver::run(const Problem& p, const Work& wk, hipStream_t s, uint32_t 
   constexpr int kRing = kMirrorSlots - 1;
   bool tail_queued = false;
   if (dev_ctl) {
-    // Guarded phases until the live set is expected below tail_at (it shrinks
-    // to about a third or less per phase), then the tail kernel, which runs
-    // whatever is left. With LM_GRAPH the whole solve is one captured graph.
+    // Guarded phases until the live set is expected about tail_at, then the tail
+    // kernel, which runs whatever is left. With LM_GRAPH the whole solve is one
+    // captured graph. A phase leaves a fifth to a quarter of the entries of ER
+    // and RGG graphs and about 1 / 2.8 of R-MAT's; a quarter is assumed, since a
+    // phase too many costs 10 to 15 us of launches that do nothing, and the tail
+    // is not slower than the phases up to a few tail_at (RGG with 2^20 vertices:
+    // a third and a phase of margin 242 us, a quarter 228 us).
     int K = 0;
-    for (double x = (double)p.nnz; x > (double)tail_at && K < 24; x /= 3.0) ++K;
-    if (K > 0) ++K;  // one phase of margin: guarded phases after the hand-over do nothing
+    for (double x = (double)p.nnz; x > (double)tail_at && K < 24; x /= 4.0) ++K;
     auto enqueue_all = [&]() -> hipError_t {
       hipError_t e = enqueue_prologue();
       c.guard = 1;
