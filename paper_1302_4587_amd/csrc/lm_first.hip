@@ -1,20 +1,19 @@
-// First argmax of a single graph read straight from its CSR (R_1), gfx950:
-// k_first_csr for a weighted graph, k_first_unw (further below) for an
-// unweighted one.
+// First argmax of R_1 read straight from its CSR, gfx950: k_first_csr for a
+// weighted batch (the union of its graphs), k_first_rows for one weighted graph
+// and k_first_unw for an unweighted one (both further below).
 //
 // Every vertex v with a live entry gets C[v] = the neighbour u maximising the
 // key (w, H(seed, lo, hi)) over its row (Section 2, first pass of the
 // sequential model; the keys are those of Section 1's perturbed weights,
-// fixed as a hash). The workgroup of a cost range (entries plus a fixed cost
-// per row, as the plan kernel splits R_1) walks it in tiles of at most
-// kFTile entries and kFRows rows. Each lane takes kFIt consecutive entries
+// fixed as a hash). k_first_csr: the workgroup of a cost range (entries plus a
+// fixed cost per row, as the plan kernel splits R_1) walks it in tiles of at
+// most kFTile entries and kFRows rows. Each lane takes kFIt consecutive entries
 // (two 16-byte loads) and reduces the runs of one row inside them in
 // registers: a row whose entries all fall into one lane is finished there. A
 // row that crosses lanes (or tiles) is combined in LDS in two passes: the
 // largest ordered weight first, then the largest hash among the segments
 // that reach it; the winner is the neighbour whose hash that is (the hash is
-// a bijection of the neighbour for a fixed vertex). An unweighted graph skips
-// the weight pass (k_first_unw is faster for those). Rows cut at range
+// a bijection of the neighbour for a fixed vertex). Rows cut at range
 // boundaries leave a partial result for the plan kernel, as the other stream
 // kernels do.
 #include <hip/hip_ext.h>
@@ -37,7 +36,7 @@ static_assert(kFIt % 4 == 0, "entries are loaded 16 bytes at a time");
 
 struct FirstSmem {
   long long wrp[kFRows + 1];       // row_ptr of the tile's rows vc .. vc + kFRows
-  unsigned sw[kFRows];             // rows crossing lanes: largest ordered weight (unweighted: 1 = touched)
+  unsigned sw[kFRows];             // rows crossing lanes: largest ordered weight
   unsigned long long sh[kFRows];   // largest hash among the segments at that weight
   unsigned c_w;                    // the row open at the tile's end: its partial key
   unsigned long long c_h;
@@ -45,7 +44,7 @@ struct FirstSmem {
   Part pf, pl;                     // the range's cut rows
   int lb[1];
   unsigned err;
-  // several graphs (a batch): the graph of every row of the tile
+  // the graph of every row of the tile
   unsigned long long rseed[kFRows];  // its tie-break seed
   int rbase[kFRows];                 // its first vertex
   int rlim[kFRows];                  // its vertex count (local ids below it)
@@ -53,18 +52,13 @@ struct FirstSmem {
   int g_cur;                         // the graph of row vc
 };
 
-// A lane's running best over one row segment. Weighted: the largest ordered
-// weight with its neighbour, the hash only once a tie needs it (Best).
-// Unweighted: the largest hash and its neighbour.
-template <bool UNW>
-struct Seg;
-template <>
-struct Seg<false> {
+// A lane's running best over one row segment: the largest ordered weight with
+// its neighbour, the hash only once a tie needs it.
+struct Seg {
   Best b;
   __device__ __forceinline__ void reset() { b = best_ident(); }
-  // one entry's ordered weight w (0: no candidate) and neighbour u; the hash
-  // only when w ties the best so far
-  __device__ __forceinline__ void add_key(unsigned w, int u, unsigned v, unsigned long long S, unsigned long long) {
+  // one entry's ordered weight w (0: no candidate) and neighbour u
+  __device__ __forceinline__ void add_key(unsigned w, int u, unsigned v, unsigned long long S) {
     if (w != 0u) best_update(b, w, u, v, S);
   }
   __device__ __forceinline__ int u() const { return b.u; }
@@ -79,27 +73,6 @@ struct Seg<false> {
     b.u = c ? o.b.u : b.u;
     b.h = c ? o.b.h : b.h;
     b.hv = c ? o.b.hv : b.hv;
-  }
-};
-template <>
-struct Seg<true> {
-  unsigned long long hb;
-  int ub;
-  __device__ __forceinline__ void reset() {
-    hb = 0ull;
-    ub = -1;
-  }
-  __device__ __forceinline__ void add_key(unsigned w, int u, unsigned, unsigned long long, unsigned long long h) {
-    const bool gt = w != 0u && (ub < 0 || h > hb);
-    hb = gt ? h : hb;
-    ub = gt ? u : ub;
-  }
-  __device__ __forceinline__ int u() const { return ub; }
-  __device__ __forceinline__ unsigned w() const { return 1u; }
-  __device__ __forceinline__ unsigned long long h(unsigned, unsigned long long) const { return hb; }
-  __device__ __forceinline__ void pick(bool c, const Seg& o) {
-    hb = c ? o.hb : hb;
-    ub = c ? o.ub : ub;
   }
 };
 
@@ -120,7 +93,6 @@ __device__ __forceinline__ Part part_of(int v, int flags, unsigned w, unsigned l
 
 // The lane's kFIt entries from s0 on (two 16-byte loads each when aligned
 // and in bounds; otherwise only the entries in [lo, hi) are read).
-template <bool UNW>
 __device__ __forceinline__ void load_entries(const int* col, const float* wt, long long s0, long long lo, long long hi,
                                              long long nnz, bool vec, int (&cv)[kFIt], float (&wv)[kFIt]) {
   if (vec && s0 >= 0 && s0 + kFIt <= nnz) {
@@ -131,13 +103,11 @@ __device__ __forceinline__ void load_entries(const int* col, const float* wt, lo
       cv[j + 1] = x.y;
       cv[j + 2] = x.z;
       cv[j + 3] = x.w;
-      if (!UNW) {
-        const float4 y = *reinterpret_cast<const float4*>(wt + s0 + j);
-        wv[j] = y.x;
-        wv[j + 1] = y.y;
-        wv[j + 2] = y.z;
-        wv[j + 3] = y.w;
-      }
+      const float4 y = *reinterpret_cast<const float4*>(wt + s0 + j);
+      wv[j] = y.x;
+      wv[j + 1] = y.y;
+      wv[j + 2] = y.z;
+      wv[j + 3] = y.w;
     }
   } else {
 #pragma unroll
@@ -145,19 +115,15 @@ __device__ __forceinline__ void load_entries(const int* col, const float* wt, lo
       const long long q = s0 + j;
       const bool in = q >= lo && q < hi;
       cv[j] = in ? col[q] : 0;
-      wv[j] = (!UNW && in) ? wt[q] : 1.0f;
+      wv[j] = in ? wt[q] : 1.0f;
     }
   }
 }
 
-// MULTI: the CSR is the disjoint union of a batch's graphs (a.c.graphs of
-// them, graph k from vertex gbase[k] on, local neighbour ids, a seed each):
-// every tile looks up the graph of each of its rows, walking on from the
-// graph of its first row.
-template <bool UNW, bool MULTI>
-__device__ void first_range(const StreamArgs& a, const Ctl& ctl, int b, FirstSmem& sm, unsigned long long S,
-                            bool vec) {
-  constexpr unsigned kUnitOrd = 0xBF800000u;  // ordered image of 1.0f
+// The CSR is the disjoint union of a batch's graphs (a.c.graphs of them, graph
+// k from vertex gbase[k] on, local neighbour ids, a seed each): every tile looks
+// up the graph of each of its rows, walking on from the graph of its first row.
+__device__ void first_range(const StreamArgs& a, const Ctl& ctl, int b, FirstSmem& sm, bool vec) {
   const int tid = threadIdx.x;
   const long long* rp = a.in.csr_rp;
   const int* col = a.in.col;
@@ -165,9 +131,9 @@ __device__ void first_range(const StreamArgs& a, const Ctl& ctl, int b, FirstSme
   const long long n = a.c.n;  // rows of the CSR (every vertex of the union)
   const int G = a.c.graphs;
   // per row slot of the current tile: graph seed, first vertex, vertex count
-  auto seed_of = [&](int i) -> unsigned long long { return MULTI ? sm.rseed[i] : S; };
-  auto base_of = [&](int i) -> int { return MULTI ? sm.rbase[i] : 0; };
-  auto lim_of = [&](int i) -> long long { return MULTI ? (long long)sm.rlim[i] : n; };
+  auto seed_of = [&](int i) -> unsigned long long { return sm.rseed[i]; };
+  auto base_of = [&](int i) -> int { return sm.rbase[i]; };
+  auto lim_of = [&](int i) -> int { return sm.rlim[i]; };
   const long long nnz = rp[n];
   const long long cost = ctl.L + (long long)kPieceCostFirst * n;
   const long long E0 = csr_entry_at<kPieceCostFirst>(a.in, n, cost * b / ctl.P, sm.lb);
@@ -185,7 +151,7 @@ __device__ void first_range(const StreamArgs& a, const Ctl& ctl, int b, FirstSme
   const long long v0 = block_lower_bound(0, n, [&](long long v) { return rp[v + 1] > E0; }, sm.lb);
   const bool cut_left = rp[v0] < E0;
   long long vc = v0, e = E0;
-  if (MULTI) {  // the graph of v0: the last graph starting at or before it
+  {  // the graph of v0: the last graph starting at or before it
     const long long g1 = block_lower_bound(0, G, [&](long long g) { return (long long)a.c.gbase[g] > v0; }, sm.lb);
     if (tid == 0) sm.g_cur = (int)g1 - 1;
   }
@@ -202,7 +168,7 @@ __device__ void first_range(const StreamArgs& a, const Ctl& ctl, int b, FirstSme
       sm.sw[i] = 0u;
       sm.sh[i] = 0ull;
     }
-    if (MULTI) {
+    {
       const int g0 = sm.g_cur;
       for (int i = tid; i <= kFRows; i += kBlock) {
         const long long v = min(vc + i, n - 1);
@@ -233,7 +199,7 @@ __device__ void first_range(const StreamArgs& a, const Ctl& ctl, int b, FirstSme
     const long long lo = max(e, s0), hi = min(tend, s0 + kFIt);
     int cv[kFIt];
     float wv[kFIt];
-    load_entries<UNW>(col, wt, s0, lo, hi, nnz, vec, cv, wv);
+    load_entries(col, wt, s0, lo, hi, nnz, vec, cv, wv);
     // ---- stage 1: the row slot of each of the lane's positions (positions
     // outside [lo, hi) keep the slot before them) and whether it is a
     // candidate (the lane's, with an id inside the graph)
@@ -257,26 +223,21 @@ __device__ void first_range(const StreamArgs& a, const Ctl& ctl, int b, FirstSme
         okv[i] = in && cv[i] >= 0 && cv[i] < lim_of(rr);
       }
     }
-    // ---- stage 2: every entry's ordered weight (0: no candidate) and, for an
-    // unweighted graph, its hash (all at once, out of masked branches)
-    unsigned long long hv[kFIt];
+    // ---- stage 2: every entry's ordered weight (0: no candidate)
     unsigned kw[kFIt];
 #pragma unroll
-    for (int i = 0; i < kFIt; ++i) {
-      hv[i] = UNW ? keep(edge_hash(seed_of(rs[i]), (unsigned)(vc + rs[i] - base_of(rs[i])), (unsigned)cv[i])) : 0ull;
-      kw[i] = okv[i] ? (UNW ? kUnitOrd : ord_weight_bits(__float_as_uint(wv[i]))) : 0u;
-    }
+    for (int i = 0; i < kFIt; ++i) kw[i] = okv[i] ? ord_weight_bits(__float_as_uint(wv[i])) : 0u;
     // ---- stage 3: segments. A row inside the lane is finished here; only the
     // lane's first segment (its row began before lo) and its last (its row
     // goes on past hi) can cross into other lanes.
     int rA = -1, rB = -1;  // slots of those two boundary segments
-    Seg<UNW> sA, sB;
+    Seg sA, sB;
     sA.reset();
     sB.reset();
     if (lo < hi) {
-      Seg<UNW> sg;
+      Seg sg;
       sg.reset();
-      Seg<UNW> empty;
+      Seg empty;
       empty.reset();
       int cur = r;
       bool started = wrp[r] >= lo;
@@ -291,7 +252,7 @@ __device__ void first_range(const StreamArgs& a, const Ctl& ctl, int b, FirstSme
         started = started || nw;
         cur = rs[i];
         sg.pick(nw, empty);
-        sg.add_key(kw[i], cv[i], (unsigned)(vc + rs[i] - base_of(rs[i])), seed_of(rs[i]), hv[i]);
+        sg.add_key(kw[i], cv[i], (unsigned)(vc + rs[i] - base_of(rs[i])), seed_of(rs[i]));
       }
       const bool ends = wrp[cur + 1] <= hi;
       if (started && ends) {
@@ -309,41 +270,30 @@ __device__ void first_range(const StreamArgs& a, const Ctl& ctl, int b, FirstSme
     // and one lane updates the slot; otherwise each lane does.
     if (tid == 0) {
       sm.c_valid = 0;  // (read at the top of this tile; set again below)
-      if (carry) {
-        if (UNW) sw[0] = 1u;
-        else atomicMax(&sw[0], cw_in);
-      }
+      if (carry) atomicMax(&sw[0], cw_in);
     }
     const int rB0 = __builtin_amdgcn_readfirstlane(rB);
     const bool waveB = rB0 >= 0 && __ballot(rB != rB0) == 0ull;
     // (a segment without a valid entry leaves its row untouched)
     if (waveB) {
-      const unsigned wB = UNW ? (__ballot(sB.u() >= 0) ? 1u : 0u)
-                              : (unsigned)__builtin_amdgcn_readlane((int)wave_incl_max_u32(sB.w()), 63);
-      if (lane_id() == 0 && wB) {
-        if (UNW) sw[rB0] = 1u;
-        else atomicMax(&sw[rB0], wB);
-      }
+      const unsigned wB = (unsigned)__builtin_amdgcn_readlane((int)wave_incl_max_u32(sB.w()), 63);
+      if (lane_id() == 0 && wB) atomicMax(&sw[rB0], wB);
     } else if (rB >= 0 && sB.u() >= 0) {
-      if (UNW) sw[rB] = 1u;
-      else atomicMax(&sw[rB], sB.w());
+      atomicMax(&sw[rB], sB.w());
     }
     // pass 1: the largest weight
-    if (rA >= 0 && sA.u() >= 0) {
-      if (UNW) sw[rA] = 1u;
-      else atomicMax(&sw[rA], sA.w());
-    }
+    if (rA >= 0 && sA.u() >= 0) atomicMax(&sw[rA], sA.w());
     __syncthreads();
     // pass 2: the largest hash among the segments at that weight
-    if (rA >= 0 && sA.u() >= 0 && (UNW || sA.w() == sw[rA]))
+    if (rA >= 0 && sA.u() >= 0 && sA.w() == sw[rA])
       atomicMax(&sh[rA], sA.h((unsigned)(vc + rA - base_of(rA)), seed_of(rA)));
     if (waveB) {
-      const bool at = sB.u() >= 0 && (UNW || sB.w() == sw[rB0]);
+      const bool at = sB.u() >= 0 && sB.w() == sw[rB0];
       const unsigned long long hm =
           wave_max_u64(at ? sB.h((unsigned)(vc + rB0 - base_of(rB0)), seed_of(rB0)) : 0ull);
       const bool any = __ballot(at) != 0ull;  // (every lane takes part in the ballot)
       if (lane_id() == 0 && any) atomicMax(&sh[rB0], hm);
-    } else if (rB >= 0 && sB.u() >= 0 && (UNW || sB.w() == sw[rB])) {
+    } else if (rB >= 0 && sB.u() >= 0 && sB.w() == sw[rB]) {
       atomicMax(&sh[rB], sB.h((unsigned)(vc + rB - base_of(rB)), seed_of(rB)));
     }
     __syncthreads();
@@ -352,7 +302,7 @@ __device__ void first_range(const StreamArgs& a, const Ctl& ctl, int b, FirstSme
       if (sw[i] == 0u || wrp[i] >= tend) continue;
       const long long v = vc + i;
       const bool cutl = v == v0 && cut_left;
-      const unsigned w = UNW ? kUnitOrd : sw[i];
+      const unsigned w = sw[i];
       unsigned long long hh = sh[i];
       if (i == 0 && carry && sw[0] == cw_in) hh = max(hh, ch_in);
       const int bs = base_of(i);
@@ -373,7 +323,7 @@ __device__ void first_range(const StreamArgs& a, const Ctl& ctl, int b, FirstSme
 #pragma unroll
     for (int step = kFRows; step > 0; step >>= 1)
       if (r2 + step <= kFRows && wrp[r2 + step] <= tend) r2 += step;
-    if (MULTI && tid == 0) sm.g_cur = sm.rgraph[r2];
+    if (tid == 0) sm.g_cur = sm.rgraph[r2];
     __syncthreads();
     vc += r2;
     e = tend;
@@ -660,7 +610,6 @@ __device__ void unw_range(const StreamArgs& a, const Ctl& ctl, int P, int b, Unw
 
 }  // namespace
 
-template <bool UNW, bool MULTI>
 __global__ __launch_bounds__(kBlock) void k_first_csr(StreamArgs a) {
   __shared__ FirstSmem sm;
   if (threadIdx.x == 0) sm.err = a.c.totals->err;
@@ -668,32 +617,23 @@ __global__ __launch_bounds__(kBlock) void k_first_csr(StreamArgs a) {
   if (sm.err) return;
   Ctl ctl = *a.in.ctl;
   if (ctl.Pf > 0) ctl.P = ctl.Pf;  // the first argmax's own split of R_1
-  const unsigned long long S = cand_seed(a.c.gseed[0], a.c.renew, a.cand_phase);
-  const bool vec = (((unsigned long long)a.in.col | (UNW ? 0ull : (unsigned long long)a.in.w)) & 15ull) == 0ull;
-  for (int b = blockIdx.x; b < ctl.P; b += gridDim.x) first_range<UNW, MULTI>(a, ctl, b, sm, S, vec);
+  const bool vec = (((unsigned long long)a.in.col | (unsigned long long)a.in.w) & 15ull) == 0ull;
+  for (int b = blockIdx.x; b < ctl.P; b += gridDim.x) first_range(a, ctl, b, sm, vec);
 }
 
-template <bool UNW, bool MULTI>
-static hipError_t launch_first_csr_t(const StreamArgs& a, int grid, hipStream_t s, hipEvent_t* ev) {
-  const auto kern = k_first_csr<UNW, MULTI>;
-  if (ev) hipExtLaunchKernelGGL(kern, dim3(grid), dim3(kBlock), 0, s, ev[0], ev[1], 0, a);
-  else hipLaunchKernelGGL(kern, dim3(grid), dim3(kBlock), 0, s, a);
+hipError_t launch_first_csr(const StreamArgs& a, int grid, hipStream_t s, hipEvent_t* ev) {
+  if (ev) hipExtLaunchKernelGGL(k_first_csr, dim3(grid), dim3(kBlock), 0, s, ev[0], ev[1], 0, a);
+  else hipLaunchKernelGGL(k_first_csr, dim3(grid), dim3(kBlock), 0, s, a);
   return hipGetLastError();
-}
-
-hipError_t launch_first_csr(const StreamArgs& a, int grid, hipStream_t s, bool unweighted, hipEvent_t* ev) {
-  const bool multi = a.c.graphs > 1;
-  if (unweighted) return multi ? launch_first_csr_t<true, true>(a, grid, s, ev) : launch_first_csr_t<true, false>(a, grid, s, ev);
-  return multi ? launch_first_csr_t<false, true>(a, grid, s, ev) : launch_first_csr_t<false, false>(a, grid, s, ev);
 }
 
 // First argmax of one weighted graph, whole rows: a wave takes 64 consecutive
 // rows, and lane groups hold those of at most kRI << lg entries (two steps'
 // loads in flight); longer ones, where there are more than a few, are listed
-// for k_first_long, which gives each a wave, or a workgroup above kRHub entries (skewed graphs have their
-// long rows next to each other: a wave that took those of its 64 rows one
-// after the other made R-MAT 14 50 us slower). No row is cut, nothing waits on
-// a workgroup barrier. Bound by HBM: RGG 2^24 415 us, 3.6 TB/s (in tiles with
+// for k_first_long, which gives each a wave, or a workgroup above kRHub entries
+// (skewed graphs have their long rows next to each other: a wave that took those
+// of its 64 rows one after the other made R-MAT 14 50 us slower). No row is cut,
+// nothing waits on a workgroup barrier. Bound by HBM: RGG 2^24 415 us, 3.6 TB/s (in tiles with
 // workgroup barriers 487 us), RGG of 1 M vertices 44 us (69).
 constexpr int kRI = 8;
 constexpr int kRHub = 2048;
@@ -884,20 +824,13 @@ int first_unw_ranges_per_cu() {
   return std::max(1, std::min(kUnwPerCu, std::min(n1, n0)));
 }
 
-// (the fewer of the one-graph and the batch instantiations)
-int first_csr_blocks_per_cu(bool unweighted) {
-  int n1 = 0, n2 = 0;
-  const hipError_t e =
-      unweighted ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&n1, (k_first_csr<true, false>), kBlock, 0)
-                 : hipOccupancyMaxActiveBlocksPerMultiprocessor(&n1, (k_first_csr<false, false>), kBlock, 0);
-  const hipError_t e2 =
-      unweighted ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&n2, (k_first_csr<true, true>), kBlock, 0)
-                 : hipOccupancyMaxActiveBlocksPerMultiprocessor(&n2, (k_first_csr<false, true>), kBlock, 0);
-  if (e != hipSuccess || e2 != hipSuccess) {
+int first_csr_blocks_per_cu() {
+  int nb = 0;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_first_csr, kBlock, 0) != hipSuccess) {
     (void)hipGetLastError();
     return 1;
   }
-  return std::max(1, std::min(n1, n2));
+  return std::max(1, nb);
 }
 
 }  // namespace lm

@@ -420,9 +420,9 @@ hipError_t launch_compact(const StreamArgs& a, int grid, hipStream_t s, bool lat
                           hipEvent_t* ev = nullptr);
 hipError_t launch_first_rows(const FirstRowsArgs& a, int num_cus, hipStream_t s, hipEvent_t* ev = nullptr);
 int first_rows_lg(long long nnz, long long n);
-// First argmax of R_1 of one graph read from its CSR (a.in.csr_rp set).
-hipError_t launch_first_csr(const StreamArgs& a, int grid, hipStream_t s, bool unweighted, hipEvent_t* ev = nullptr);
-int first_csr_blocks_per_cu(bool unweighted);
+// First argmax of R_1 of a weighted batch read from its CSR (a.in.csr_rp set).
+hipError_t launch_first_csr(const StreamArgs& a, int grid, hipStream_t s, hipEvent_t* ev = nullptr);
+int first_csr_blocks_per_cu();
 // First argmax of R_1 of one unweighted graph from its CSR: one-wave
 // workgroups, one range each (first_unw_ranges_per_cu() ranges per CU).
 // vec_ok: col is 16-byte aligned and nnz >= first_unw_min_entries().

@@ -793,9 +793,8 @@ __device__ __forceinline__ void close_segment(const StreamArgs& a, Smem& sm, boo
 // skipped and the hash pass decides every piece.
 // VIEW: kViewOne and kViewCsr hold one graph (vertex base 0, seed seed0), so
 // pieces carry no per-graph base or seed and no table is read; kViewCsr reads
-// R_1 from the input CSR, empty rows as pieces of length 0, and splits the
-// ranges by entries plus a fixed cost per piece (kPieceCostFirst for the
-// first argmax, kPieceCost for the compaction).
+// R_1 from the input CSR (compactions only), empty rows as pieces of length 0,
+// and splits the ranges by entries plus a fixed cost per piece (kPieceCost).
 template <bool FIRST, int PPL, bool UNW, int VIEW>
 __device__ void stream_range(const StreamArgs& a, const Ctl& ctl, int b, StreamSmem<kBlock * PPL, stream_items<FIRST, UNW>()>& sm,
                              unsigned long long seed0) {
@@ -812,7 +811,7 @@ __device__ void stream_range(const StreamArgs& a, const Ctl& ctl, int b, StreamS
   constexpr bool csr = VIEW == kViewCsr;
   long long E0, E1;
   if (csr) {
-    constexpr int K = FIRST ? kPieceCostFirst : kPieceCost;
+    constexpr int K = kPieceCost;
     const long long n = ctl.pieces, cost = ctl.L + (long long)K * n;
     E0 = csr_entry_at<K>(a.in, n, cost * b / ctl.P, sm.lb);
     E1 = csr_entry_at<K>(a.in, n, cost * (b + 1) / ctl.P, sm.lb);
@@ -1574,7 +1573,7 @@ hipError_t launch_plan(const PlanArgs& a, hipStream_t s, hipEvent_t* ev) {
 // other live set the ones that read the tables.
 template <bool FIRST, int PPL, bool UNW>
 static hipError_t launch_stream(const StreamArgs& a, int grid, hipStream_t s, hipEvent_t* ev) {
-  if constexpr (PPL == 1) {
+  if constexpr (PPL == 1 && !FIRST) {
     if (a.c.graphs == 1 && a.in.csr_rp)
       return launch_timed(k_stream<FIRST, PPL, UNW, kViewCsr>, dim3(grid), dim3(kBlock), s, ev, a);
   }
@@ -1584,13 +1583,10 @@ static hipError_t launch_stream(const StreamArgs& a, int grid, hipStream_t s, hi
 }
 hipError_t launch_first_argmax(const StreamArgs& a, int grid, hipStream_t s, bool unweighted, hipEvent_t* ev,
                                long long nnz) {
-  if (a.c.graphs > 1 && a.in.csr_rp && !unweighted) return launch_first_csr(a, grid, s, false, ev);  // a batch
-  if (a.c.graphs == 1 && a.in.csr_rp) {
-    if (unweighted) {
-      const bool vec_ok = ((unsigned long long)a.in.col & 15ull) == 0ull && nnz >= first_unw_min_entries();
-      return launch_first_unw(a, grid, s, vec_ok, ev);
-    }
-    return launch_first_csr(a, grid, s, false, ev);
+  if (a.in.csr_rp && !unweighted) return launch_first_csr(a, grid, s, ev);  // a batch
+  if (a.in.csr_rp) {
+    const bool vec_ok = ((unsigned long long)a.in.col & 15ull) == 0ull && nnz >= first_unw_min_entries();
+    return launch_first_unw(a, grid, s, vec_ok, ev);
   }
   if (unweighted) return launch_stream<true, 1, true>(a, grid, s, ev);
   return launch_stream<true, 1, false>(a, grid, s, ev);
@@ -1619,7 +1615,7 @@ template <bool FIRST, int PPL, bool UNW>
 static int stream_blocks_per_cu() {
   int nb = std::min(blocks_per_cu(k_stream<FIRST, PPL, UNW, kViewOne>),
                     blocks_per_cu(k_stream<FIRST, PPL, UNW, kViewTables>));
-  if constexpr (PPL == 1) nb = std::min(nb, blocks_per_cu(k_stream<FIRST, PPL, UNW, kViewCsr>));
+  if constexpr (PPL == 1 && !FIRST) nb = std::min(nb, blocks_per_cu(k_stream<FIRST, PPL, UNW, kViewCsr>));
   return nb;
 }
 

@@ -223,7 +223,7 @@ lm_status Solver::init_device(int device, size_t budget) {
   bpc_first_u = max_blocks_per_cu_stream(StreamKind::kFirst, true);
   bpc_late_u = max_blocks_per_cu_stream(StreamKind::kLateCompact, true);
   bpc_tail = tail_blocks_per_cu();
-  bpc_first_csr = first_csr_blocks_per_cu(false);
+  bpc_first_csr = first_csr_blocks_per_cu();
   bpc_compact_rows = compact_rows_per_cu();
   bpc_first_unw = first_unw_ranges_per_cu();
   tun.block_entries = kCap;  // one batch: small phases still spread over every CU
