@@ -569,11 +569,17 @@ lm_status Solver::run(const Problem& p, const Work& wk, hipStream_t s, uint32_t 
     ta.final_rec = d_mir + kMirrorSlots;
     ta.gen = gen;
     ta.spin_ticks = clock_khz * 2000ull;  // 2 s
-    // workgroups (1024 lanes each): about one per 4096 live entries (per 16384:
+    // Workgroups (1024 lanes each): about one per 4096 live entries (per 16384:
     // the first phase of 600 K entries 23 us; 320 K unweighted ER entries solved
-    // in 237 us against 211)
+    // in 237 us against 211), but at most a quarter of the resident capacity up
+    // to 2^20 entries: solves of several threads run on up to four hardware
+    // queues, and tails that are each resident in part only would wait for each
+    // other. (Half of it: R-MAT 14 150 us against 178, ER with 20 K vertices 154
+    // against 158, RGG with 60 K 119 against 124.)
     if (direct) L_hint = p.nnz;
-    const long long want = L_hint < 0 ? tail_cap : (L_hint + 4095) / 4096;
+    const long long quarter = std::max(1, num_cus * std::max(1, bpc_tail) / 4);
+    const long long want =
+        L_hint < 0 ? tail_cap : std::min((L_hint + 4095) / 4096, std::max(quarter, (L_hint + 16383) / 16384));
     const int grid = (int)std::max<long long>(1, std::min<long long>(tail_cap, want));
     ENQ(launch_tail(ta, grid, s, timing(LM_K_TAIL)));
     return hipSuccess;
