@@ -302,10 +302,12 @@ __device__ __forceinline__ void wg_vertices(const CArgs& a, long long& vb, long 
                                    lb);
 }
 
-// Vertices a wave takes at a time of a range of nv: about `turns` turns a wave,
-// so that the range's rows spread over its waves, however few and long.
+// Vertices a wave takes at a time of a range of nv: at least `turns` turns a wave,
+// of equal size, so that the range's rows spread over its waves, however few and
+// long.
 __device__ __forceinline__ int wave_rows(long long nv, int turns) {
-  return (int)min(64ll, max(4ll, (nv + kWaves * turns - 1) / (kWaves * turns)));
+  const long long t = max((long long)turns, (nv + 64 * kWaves - 1) / (64 * kWaves));
+  return (int)max(4ll, (nv + kWaves * t - 1) / (kWaves * t));
 }
 
 // Last row r of the chunk with st[r] <= pos (rows with no tile entries share
@@ -405,8 +407,8 @@ __device__ __forceinline__ int wrow_of(const int* st, int pos) {
 // (2a) The coarse rows with bound <= kWS, one wave at a time with no
 // workgroup barrier: each wave takes 64 fine vertices of every chunk of its
 // workgroup's range, lays their rows out back to back and groups them in
-// wave tiles of at most kWT entries (the same grouping as k_c_group, in the
-// wave's own LDS); ranks in row order come from the tile's ballots.
+// wave tiles of at most kWT entries (equal coarse neighbours meet in a slot of
+// the wave's LDS table); ranks in row order come from the tile's ballots.
 __global__ __launch_bounds__(kBlock) void k_c_group_wave(CArgs a) {
   __shared__ WaveSmem wsm[kWaves];
   __shared__ int lb[1];
