@@ -40,7 +40,9 @@ HBM_PEAK_GBS = 8000.0  # MI355X HBM3E, published
 
 KERNEL_SOURCES = ["paper_1302_4587_amd/csrc/lm_kernels.hip", "paper_1302_4587_amd/csrc/lm_device.h",
                   "paper_1302_4587_amd/csrc/lm_key.h", "paper_1302_4587_amd/csrc/lm_internal.h",
-                  "paper_1302_4587_amd/csrc/lm_tail.hip", "paper_1302_4587_amd/csrc/lm_first.hip"]
+                  "paper_1302_4587_amd/csrc/lm_tail.hip", "paper_1302_4587_amd/csrc/lm_first.hip",
+                  "paper_1302_4587_amd/csrc/lm_rows.h", "paper_1302_4587_amd/csrc/lm_compact.hip",
+                  "paper_1302_4587_amd/csrc/lm_compact_unw.hip"]
 CONTRACT_SOURCES = ["paper_1302_4587_amd/csrc/lm_contract.hip"]
 
 

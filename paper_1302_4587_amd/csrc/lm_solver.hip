@@ -404,8 +404,8 @@ lm_status Solver::run(const Problem& p, const Work& wk, hipStream_t s, uint32_t 
   // One graph that the tail kernel takes from the first phase on needs nothing
   // before it: it reads R_1 and finds the first candidates itself (with k_init,
   // k_plan, the first argmax and its listed rows, and a row list behind them:
-  // RGG with 60 K vertices 130 us a call, now 120; ER with 20 K vertices of degree
-  // 16 200 -> 152; R-MAT 14 221 -> 148).
+  // RGG with 60 K vertices 130 us a call, now 123; ER with 20 K vertices of degree
+  // 16 200 -> 158; R-MAT 14 221 -> 178).
   const bool direct = csr1 && (dev_ctl ? p.nnz <= tail_at : tun.tail_entries > 0 && p.nnz <= tun.tail_entries);
   auto enqueue_prologue = [&]() -> hipError_t {
     ENQ(launch_zero(dctl, 2, dtot, s, wk.tail));
