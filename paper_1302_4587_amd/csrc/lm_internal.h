@@ -338,6 +338,14 @@ constexpr long long kSoloEntries = 1 << 16;
 constexpr long long kSoloEntriesUnw = 1 << 15;
 constexpr int kSoloClasses = 3;            // size classes of a batch's graphs
 
+// A batch's phase log is summed over its graphs in the buffer of the partial
+// results (Part), which one workgroup per graph leaves unused: records that
+// buffer holds, and records kept for a batch whose largest graph has n vertices.
+// Every phase of a graph without self-loops matches two of its vertices.
+constexpr long long kSoloLogRecs = (long long)kMaxFirstRanges * 2 * sizeof(Part) / sizeof(uint4);
+static_assert(kSoloMaxN / 2 <= kSoloLogRecs, "every phase of the largest graph has a record");
+constexpr long long solo_log_records(long long n) { return n < kSoloLogRecs ? n : kSoloLogRecs; }
+
 struct SoloArgs {
   const long long* rp;  // row_ptr of the graph or the union
   const int* col;

@@ -805,7 +805,7 @@ lm_status Solver::run_solo(const Problem& p, const Work& wk, const int64_t* vtx_
     for (int k = 0; k < kSoloClasses; ++k) o.cls_n[k] = few ? 0 : kSoloClsN[k];
     o.order = wk.C;  // (candidates stay in LDS here)
     o.acc = reinterpret_cast<uint4*>(wk.parts);
-    o.acc_n = (int)(mx / 2 + 1);  // every phase matches two vertices of each live graph
+    o.acc_n = (int)solo_log_records(mx);
     o.gphase = p.gphase;
     o.totals = check ? nullptr : wk.totals;
     hipLaunchKernelGGL(k_solo_order, dim3(1 + (o.acc_n + 8191) / 8192), dim3(1024), 0, s, o);

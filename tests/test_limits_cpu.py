@@ -1,0 +1,30 @@
+"""Sizes of buffers that several kernels share, at the ends of their ranges: host
+constants of the library's internal header, compiled and printed. No kernel runs."""
+import os
+import subprocess
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_1302_4587_amd", "csrc")
+
+
+def _values(tmp_path, *exprs):
+    """The integer values of expressions over lm_internal.h, on the host."""
+    src, exe = tmp_path / "probe.hip", tmp_path / "probe"
+    body = "".join(f'printf("%lld\\n", (long long)({e}));' for e in exprs)
+    src.write_text(f'#include <cstdio>\n#include "lm_internal.h"\nusing namespace lm;\nint main() {{ {body} return 0; }}\n')
+    hipcc = os.environ.get("HIPCC") or "/opt/rocm/bin/hipcc"
+    r = subprocess.run([hipcc, "--offload-host-only", "-std=c++17", f"-I{CSRC}", str(src), "-o", str(exe)],
+                       capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+    return [int(x) for x in subprocess.run([str(exe)], capture_output=True, text=True, check=True).stdout.split()]
+
+
+def test_phase_log_of_a_batch_fits_its_buffer(tmp_path):
+    """The sums of a batch's phase log (16 bytes a phase) stay inside the buffer of the partial results they borrow,
+    and hold every phase of a graph without self-loops (two vertices a phase at least)."""
+    sizes = (1, 2, 3, 4095, 32767, 32768, 32769, 65535, 65536)
+    room, largest, *recs = _values(tmp_path, "kMaxFirstRanges * 2 * sizeof(Part)", "kSoloMaxN",
+                                   *(f"solo_log_records({n})" for n in sizes))
+    assert largest == sizes[-1]
+    for n, k in zip(sizes, recs):
+        assert 16 * k <= room and k >= n // 2, n
