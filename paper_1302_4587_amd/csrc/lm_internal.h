@@ -341,10 +341,14 @@ constexpr int kSoloClasses = 3;            // size classes of a batch's graphs
 // A batch's phase log is summed over its graphs in the buffer of the partial
 // results (Part), which one workgroup per graph leaves unused: records that
 // buffer holds, and records kept for a batch whose largest graph has n vertices.
-// Every phase of a graph without self-loops matches two of its vertices.
+// Every phase of a graph without self-loops matches two of its vertices; a graph
+// with self-loops, which is only refused where the input is checked, can have one
+// vertex a phase: its later phases are counted and have no record.
 constexpr long long kSoloLogRecs = (long long)kMaxFirstRanges * 2 * sizeof(Part) / sizeof(uint4);
 static_assert(kSoloMaxN / 2 <= kSoloLogRecs, "every phase of the largest graph has a record");
 constexpr long long solo_log_records(long long n) { return n < kSoloLogRecs ? n : kSoloLogRecs; }
+// The record of phase t (1-based) of `recs`, -1: none.
+__host__ __device__ constexpr int solo_log_slot(int t, int recs) { return t <= recs ? t - 1 : -1; }
 
 struct SoloArgs {
   const long long* rp;  // row_ptr of the graph or the union
@@ -361,7 +365,8 @@ struct SoloArgs {
   int4* rows[2];        // live-row lists: N records each
   int* ecol[2];         // live entries, each graph in its own input range
   float* ew[2];
-  uint4* acc;           // a batch: the phase log's sums over its graphs
+  uint4* acc;           // a batch: the phase log's sums over its graphs, acc_n records
+  int acc_n;
   Totals* totals;
   int check_err;        // totals->err was written by the input check
   int* gphase;          // optional: phases per graph

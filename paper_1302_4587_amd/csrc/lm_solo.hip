@@ -556,11 +556,14 @@ __global__ __launch_bounds__(LANES, WPS) void k_solo(SoloArgs a) {
       c.mv = uni(c.mv);
       if (tid == 0) {  // the record of phase t
         if (a.acc) {
-          unsigned* rec = reinterpret_cast<unsigned*>(a.acc + (t - 1));
-          atomicAdd(rec + 0, L);
-          atomicAdd(rec + 1, (unsigned)V);
-          atomicAdd(rec + 2, (unsigned)c.mv / 2u);
-          atomicAdd(rec + 3, c.md);
+          const int at = solo_log_slot(t, a.acc_n);
+          if (at >= 0) {
+            unsigned* rec = reinterpret_cast<unsigned*>(a.acc + at);
+            atomicAdd(rec + 0, L);
+            atomicAdd(rec + 1, (unsigned)V);
+            atomicAdd(rec + 2, (unsigned)c.mv / 2u);
+            atomicAdd(rec + 3, c.md);
+          }
         } else if (t <= a.log_cap) {
           a.log[t - 1] = LogRec{(long long)L, (long long)V, (long long)(c.mv / 2), (long long)c.md};
         }
@@ -666,7 +669,8 @@ __global__ __launch_bounds__(1024) void k_solo_order(SoloOrder a) {
 __global__ __launch_bounds__(1024) void k_solo_fin(SoloArgs a) {
   const int phases = a.totals->last_nonempty;
   for (int i = threadIdx.x; i < phases && i < a.log_cap; i += 1024) {
-    const uint4 r = a.acc[i];
+    const int at = solo_log_slot(i + 1, a.acc_n);
+    const uint4 r = at >= 0 ? a.acc[at] : make_uint4(0u, 0u, 0u, 0u);
     a.log[i] = LogRec{(long long)r.x, (long long)r.y, (long long)r.z, (long long)r.w};
   }
   __syncthreads();
@@ -813,6 +817,7 @@ lm_status Solver::run_solo(const Problem& p, const Work& wk, const int64_t* vtx_
     a.vtx_off = p.vtx_off;
     a.gseed = wk.gseed;
     a.acc = o.acc;
+    a.acc_n = o.acc_n;
     // The largest graphs take a CU each and end one by one; the others run
     // beside them on a second stream (the smallest first: their LDS fits next
     // to a large graph's).

@@ -1,0 +1,42 @@
+"""Solves by one workgroup per graph at their limits: a batch whose phase log
+takes every record it has."""
+import numpy as np
+import pytest
+
+import lmgen
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_1302_4587_amd as lm
+    with lm.Context(0) as c:
+        yield c
+
+
+@pytest.mark.parametrize("n", [65535, 65536])
+def test_as_many_phases_as_log_records(ctx, n):
+    """Increasing weights along a path of the largest number of vertices: only the last edge left is matched in a phase,
+    n // 2 phases in all, beside a graph that ends in the first one."""
+    import torch
+    g = lmgen.from_edges(n, np.stack([np.arange(n - 1), np.arange(1, n)], 1), np.arange(1, n).astype(np.float32))
+    e = lmgen.from_edges(2, [(0, 1)], np.ones(1, np.float32))
+    rp = np.concatenate([g.row_ptr, g.nnz + e.row_ptr[1:]]).astype(np.int64)
+    dev = [torch.from_numpy(x).cuda() for x in (rp, np.concatenate([g.col, e.col]), np.concatenate([g.w, e.w]))]
+    print(f"case: path n={n}", flush=True)
+    mate, st, phases = ctx.match_batch([0, n, n + 2], *dev, log_cap=40000)
+    want = np.full(n + 2, -1)
+    top = np.arange(n - 1, 0, -2)
+    want[top], want[top - 1] = top - 1, top
+    want[n:] = [1, 0]
+    assert np.array_equal(mate.cpu().numpy(), want)
+    assert list(phases) == [n // 2, 1] and st.phases == len(st.log) == n // 2 and st.matched_edges == n // 2 + 1
+    left = n - 2 * np.arange(n // 2)  # vertices of the path left in phase t
+    first = np.arange(n // 2) == 0
+    assert np.array_equal(st.log[:, 0], 2 * (left - 1) + 2 * first)
+    assert np.array_equal(st.log[:, 1], left + 2 * first)
+    assert np.array_equal(st.log[:, 2], 1 + first)

@@ -28,3 +28,11 @@ def test_phase_log_of_a_batch_fits_its_buffer(tmp_path):
     assert largest == sizes[-1]
     for n, k in zip(sizes, recs):
         assert 16 * k <= room and k >= n // 2, n
+
+
+def test_phases_past_the_log_have_no_record(tmp_path):
+    """A graph with self-loops (refused only by the input check) can have a phase per vertex, more than a batch's log has
+    records: phase t's record, 1-based, exists exactly for t up to the records."""
+    recs, n = _values(tmp_path, "solo_log_records(kSoloMaxN)", "kSoloMaxN")
+    at = (1, 2, recs - 1, recs, recs + 1, n - 1, n)
+    assert _values(tmp_path, *(f"solo_log_slot({t}, {recs})" for t in at)) == [t - 1 if t <= recs else -1 for t in at]
