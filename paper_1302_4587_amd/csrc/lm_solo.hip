@@ -599,7 +599,12 @@ __global__ __launch_bounds__(LANES, WPS) void k_solo(SoloArgs a) {
       if (a.gphase) a.gphase[gi] = t - 1;
     }
   } else {
-    __syncthreads();  // every lane's mate is written before the record
+    // Every lane's mate is written before the record: a barrier alone does not
+    // wait for the other waves' stores, and lane 0's release of the record only
+    // for its own wave's.
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
     if (tid == 0) {
       if (a.gphase) a.gphase[0] = t - 1;
       solo_record(a, fail, t, matched, wall_clock64() - t0);
@@ -852,8 +857,9 @@ lm_status Solver::run_solo(const Problem& p, const Work& wk, const int64_t* vtx_
     return LM_OK;
   }
   if (one) {
-    // The record is the kernel's last store, after everything else it wrote
-    // was made visible: it is polled, and carries the solve's time. Two events
+    // The record is the kernel's last store: every wave has waited for its
+    // stores, and they were released to the system, before it. It is polled, and
+    // carries the solve's time. Two events
     // and a wait on one of them cost a short solve half its time (er 300:
     // 52 us a call against 32).
     const volatile PhaseMirror* slot = &h_mir[kMirrorSlots];

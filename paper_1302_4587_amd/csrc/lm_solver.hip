@@ -1083,7 +1083,8 @@ static lm_status solve_common(lm_ctx* c, int64_t N, int64_t nnz, int64_t G, cons
     if (hipMemcpyAsync(graph_phases, S.gphase.p, (size_t)G * 4, hipMemcpyDeviceToHost, s) != hipSuccess)
       return LM_EDEVICE;
   }
-  // (a solve by whole workgroups has waited for its last kernel)
+  // (a solve by whole workgroups has waited for its last kernel, or for the
+  // record behind the last store of its only one)
   if (!(solo && !want_w && out_dev && !graph_phases) && hipStreamSynchronize(s) != hipSuccess) return LM_EDEVICE;
   if (want_w) st->matched_weight = wsum;
   return LM_OK;

@@ -1,9 +1,11 @@
 """Solves by one workgroup per graph at their limits: a batch whose phase log
-takes every record it has."""
+takes every record it has, and results read from elsewhere the moment a call
+returns."""
 import numpy as np
 import pytest
 
 import lmgen
+import oracle
 
 pytestmark = pytest.mark.gpu
 
@@ -40,3 +42,28 @@ def test_as_many_phases_as_log_records(ctx, n):
     assert np.array_equal(st.log[:, 0], 2 * (left - 1) + 2 * first)
     assert np.array_equal(st.log[:, 1], left + 2 * first)
     assert np.array_equal(st.log[:, 2], 1 + first)
+
+
+@pytest.mark.parametrize("edges", [0, 20000])
+@pytest.mark.parametrize("noalloc", [False, True])
+def test_result_is_complete_on_return(ctx, noalloc, edges):
+    """The call returns once mate holds the result: another stream, which waits for nothing, reads all of it at once."""
+    import torch
+    n = 60000
+    g = lmgen.er(n, edges, 7)
+    want = torch.from_numpy(oracle.local_max_graph(g, 5)[0].astype(np.int32)).pin_memory()
+    dev = [torch.from_numpy(x).cuda() for x in (g.row_ptr, g.col, g.w)]
+    if not edges:
+        dev[1], dev[2] = torch.empty(0, dtype=torch.int32, device="cuda"), None
+    mate, other = torch.empty(n, dtype=torch.int32, device="cuda"), torch.cuda.Stream()
+    got = torch.empty(n, dtype=torch.int32).pin_memory()
+    solve = ctx.match_noalloc if noalloc else ctx.match
+    print(f"case: on return noalloc={noalloc} edges={edges}", flush=True)
+    for k in range(20):
+        mate.fill_(-7)
+        torch.cuda.synchronize()
+        solve(*dev, seed=5, mate=mate)
+        with torch.cuda.stream(other):
+            got.copy_(mate, non_blocking=True)
+        other.synchronize()
+        assert torch.equal(got, want), k
