@@ -294,9 +294,12 @@ __global__ __launch_bounds__(kTailBlock) void k_tail(TailArgs a) {
   TailCtl* tc = a.tc;
   const int tid = threadIdx.x, lane = lane_id(), wv = wave_id();
   const int b = blockIdx.x;
-  if (tid == 0) sm.ok = tot->err == 0u ? 1u : 0u;
+  // An error found before this launch ends it: every workgroup reads the same
+  // word. Where this launch checks the input itself, the word may change under a
+  // workgroup that starts late: all go to the first exchange and look behind it.
+  if (tid == 0) sm.ok = a.csr_rp || tot->err == 0u ? 1u : 0u;
   __syncthreads();
-  if (!sm.ok) return;  // every workgroup reads the same word: all leave
+  if (!sm.ok) return;
   const int c0 = tot->t;
   const int si = (c0 - 1) & 1;  // R_c's buffer set
   const Ctl ctl = *a.ctl[si];
