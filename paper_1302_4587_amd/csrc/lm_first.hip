@@ -769,11 +769,11 @@ hipError_t launch_first_rows(const FirstRowsArgs& a, int num_cus, hipStream_t s,
   const int grid = (int)std::max<long long>(1, std::min<long long>(blocks, (long long)num_cus * 64));
   if (ev) hipExtLaunchKernelGGL(k_first_rows, dim3(grid), dim3(kBlock), 0, s, ev[0], ev[1], 0, a);
   else hipLaunchKernelGGL(k_first_rows, dim3(grid), dim3(kBlock), 0, s, a);
-  if (hipGetLastError() != hipSuccess) return hipErrorUnknown;
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess || a.nnz == 0) return e;  // (no entry: nothing is listed)
   hipLaunchKernelGGL(k_first_long, dim3((unsigned)std::min<long long>(2 * num_cus, (a.nnz + 8191) / 8192)),
                      dim3(kHubLanes), 0, s, a);
-  if (hipGetLastError() != hipSuccess) return hipErrorUnknown;
-  return hipSuccess;
+  return hipGetLastError();
 }
 
 // A failed solve, or a guarded launch whose phases the device tail took over.
