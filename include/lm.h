@@ -86,9 +86,11 @@ typedef int32_t lm_status;
 #define LM_GRAPH 0x10u       /* run the whole solve as one captured HIP graph launch: set-up,
                                 a fixed number of phases that do nothing once the tail kernel
                                 has taken over, and the tail kernel (no host round trip);
-                                ignored together with LM_PROFILE or LM_ASYNC, and by solves
-                                whose graphs one workgroup each solves (a few launches and no
-                                host round trip as they are); same results */
+                                ignored together with LM_PROFILE or LM_ASYNC, by solves whose
+                                graphs one workgroup each solves (a few launches and no host
+                                round trip as they are), and by batches in device memory of
+                                graphs small enough for that in vertices but not in entries;
+                                same results */
 #define LM_WEIGHT_SUM 0x20u  /* after the solve, set stats->matched_weight (needs stats) */
 #define LM_ASYNC 0x40u       /* stream-ordered: enqueue the whole solve on `stream` and return
                                 at once; mate holds the result when the stream reaches that

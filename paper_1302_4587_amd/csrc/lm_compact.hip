@@ -200,7 +200,7 @@ __global__ __launch_bounds__(kBlock, 4) void k_compact_rows(StreamArgs a, int lg
   __shared__ CompactSmem sm;
   if (threadIdx.x == 0) {
     const Totals* t = a.c.totals;
-    sm.err = t->err | ((a.c.guard && t->tail_from) ? 0x80000000u : 0u) | (compact_by_rows(t, a.c.n) ? 0u : 1u);
+    sm.err = t->err | (handed_over(a.c, t->tail_from) ? 0x80000000u : 0u) | (compact_by_rows(t, a.c.n) ? 0u : 1u);
   }
   __syncthreads();
   if (sm.err) return;

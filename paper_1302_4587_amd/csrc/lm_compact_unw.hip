@@ -339,7 +339,7 @@ __device__ void compact_unw_range(const StreamArgs& a, const Ctl& ctl, int b, Un
 __global__ __launch_bounds__(64, 4) void k_compact_unw(StreamArgs a) {
   __shared__ UnwCompactSmem sm;
   const Totals* t = a.c.totals;
-  if (uni((int)(t->err | ((a.c.guard && t->tail_from) ? 0x80000000u : 0u))) != 0) return;
+  if (uni((int)(t->err | (handed_over(a.c, t->tail_from) ? 0x80000000u : 0u))) != 0) return;
   const Ctl ctl = *a.in.ctl;
   const int lane = lane_id();
   const unsigned long long S = cand_seed(a.c.gseed[0], a.c.renew, a.cand_phase);

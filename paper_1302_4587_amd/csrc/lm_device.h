@@ -18,6 +18,11 @@ __device__ __forceinline__ unsigned long long keep(unsigned long long x) {
   asm volatile("" : "+v"(x));
   return x;
 }
+// Whether a guarded launch has nothing left to do.
+__device__ __forceinline__ bool handed_over(const Common& c, int tail_from) {
+  return ((c.guard & kGuardTail) && tail_from > 0) || ((c.guard & kGuardSolo) && tail_from == kSoloTook);
+}
+
 __device__ __forceinline__ int wave_id() { return threadIdx.x >> 6; }
 __device__ __forceinline__ unsigned long long lanemask_lt() {
   const int l = lane_id();

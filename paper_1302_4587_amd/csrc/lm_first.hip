@@ -612,7 +612,7 @@ __device__ void unw_range(const StreamArgs& a, const Ctl& ctl, int P, int b, Unw
 
 __global__ __launch_bounds__(kBlock) void k_first_csr(StreamArgs a) {
   __shared__ FirstSmem sm;
-  if (threadIdx.x == 0) sm.err = a.c.totals->err;
+  if (threadIdx.x == 0) sm.err = a.c.totals->err | (handed_over(a.c, a.c.totals->tail_from) ? 0x80000000u : 0u);
   __syncthreads();
   if (sm.err) return;
   Ctl ctl = *a.in.ctl;
@@ -776,9 +776,9 @@ hipError_t launch_first_rows(const FirstRowsArgs& a, int num_cus, hipStream_t s,
   return hipGetLastError();
 }
 
-// A failed solve, or a guarded launch whose phases the device tail took over.
+// A failed solve, or a guarded launch that has nothing left to do.
 __device__ __forceinline__ bool wave_failed(const Common& c) {
-  return (c.totals->err | ((c.guard && c.totals->tail_from) ? 0x80000000u : 0u)) != 0u;
+  return c.totals->err != 0u || handed_over(c, c.totals->tail_from);
 }
 
 template <bool VEC>

@@ -91,7 +91,7 @@ struct Totals {
   int last_nonempty;
   unsigned long long matched;
   int t;    // current phase (1-based): read by the mutual check, advanced by the plan kernel
-  int tail_from;  // guarded phases: the live set R_t the tail kernel takes over (0 = none yet)
+  int tail_from;  // guarded phases: the live set R_t the tail kernel takes over (0 = none yet), or kSoloTook
   unsigned long long fp[2];  // LM_CHECK_GRAPH: fingerprints of the entries and of their mirrors
   unsigned hubs, longs;      // rows left to k_first_long
   unsigned far, samp;        // sampled first entries of R_1 whose neighbour id is far from the row's
@@ -150,7 +150,14 @@ enum : unsigned {
   kErrInternal = 32u,
   kErrStall = 64u,  // a phase removed nothing: the input is not symmetric
   kErrAsym = 128u,  // LM_CHECK_GRAPH: the entries and their mirrors differ (fingerprints)
+  kErrDeclined = 256u,  // (in a record only) k_solo leaves the batch to the phase kernels
 };
+
+// Launches of a device-controlled solve that may have nothing left to do: phases
+// once the tail kernel has taken the live set over, and every launch behind
+// k_solo's where those solved the batch.
+enum : int { kGuardTail = 1, kGuardSolo = 2 };
+constexpr int kSoloTook = -1;  // totals->tail_from: k_solo solves the batch
 
 // Inputs common to the phase kernels.
 struct Common {
@@ -163,8 +170,7 @@ struct Common {
   const unsigned long long* gseed;  // premixed tie-break seed per graph
   int* gphase;                      // optional: last phase with a live row per graph
   int graphs;                       // 1: every piece belongs to graph 0 (no table lookups)
-  int guard = 0;                    // phase kernels of a device-controlled solve: do nothing
-                                    // once the tail kernel has taken the live set over
+  int guard = 0;                    // kGuardTail, kGuardSolo: do nothing once totals->tail_from says so
   unsigned* mbits = nullptr;        // matched bits (one graph, N >= kBitsMinN): cleared by k_init,
                                     // set by the mutual check while bits_on(totals)
   int renew = 0;                    // renewed keys: the candidates of phase t break ties with
@@ -338,6 +344,21 @@ constexpr long long kSoloEntries = 1 << 16;
 constexpr long long kSoloEntriesUnw = 1 << 15;
 constexpr int kSoloClasses = 3;            // size classes of a batch's graphs
 
+// A batch is solved this way if its largest graph has at most so many entries (N
+// vertices and T entries in the union). One workgroup takes about 0.9 us per 1000
+// entries of a weighted graph (1.2 unweighted) however few graphs there are; the
+// phase kernels about 250 us, 3 us per square root of N, and 1 us per 128 K entries.
+// Measured (us, one workgroup each / phase kernels; weighted, equal graphs of n
+// vertices and degree d): 2 of n = 60000, d = 16 883 / 1705, d = 64 2813 / 1357,
+// d = 500 22931 / 1501; 4 of n = 4000, d = 250 1020 / 537; 16 of n = 60000, d = 64
+// 3394 / 4938, d = 128 4891 / 4202; 32 of n = 20000, d = 100 1555 / 2530, d = 200
+// 5120 / 2618; 64 of n = 60000, d = 128 5377 / 8143; 64 of n = 4000, d = 1000
+// 3103 / 3309, d = 3000 8625 / 7811; 256 of n = 4000, d = 1000 4308 / 10224.
+inline long long solo_entry_limit(long long N, long long T, bool unweighted) {
+  const long long x = (1ll << 18) + (long long)(3200.0 * __builtin_sqrt((double)N)) + T / 128;
+  return unweighted ? x - x / 5 : x;
+}
+
 // A batch's phase log is summed over its graphs in the buffer of the partial
 // results (Part), which one workgroup per graph leaves unused: records that
 // buffer holds, and records kept for a batch whose largest graph has n vertices.
@@ -368,7 +389,7 @@ struct SoloArgs {
   uint4* acc;           // a batch: the phase log's sums over its graphs, acc_n records
   int acc_n;
   Totals* totals;
-  int check_err;        // totals->err was written by the input check
+  int check_err;        // look at totals first: the input check's errors, a batch that is not solved here
   int* gphase;          // optional: phases per graph
   LogRec* log;
   int log_cap;
@@ -399,7 +420,9 @@ struct SoloOrder {
   uint4* acc;
   int acc_n;
   int* gphase;
-  Totals* totals;  // cleared, or nullptr: the input check has written it
+  Totals* totals;
+  int clear;            // totals are cleared (the input check has not written them)
+  long long limit;      // a graph with more entries leaves the batch to the phase kernels
 };
 
 struct CheckArgs {

@@ -23,10 +23,10 @@
 namespace lm {
 
 // Reads the error word once per workgroup so that every lane takes the same
-// branch. A guarded launch (device-controlled solve) also stops once the tail
-// kernel has taken the live set over.
+// branch. A guarded launch (device-controlled solve) also stops once it has
+// nothing left to do.
 __device__ __forceinline__ bool block_failed(const Common& c, unsigned* s) {
-  if (threadIdx.x == 0) *s = c.totals->err | ((c.guard && c.totals->tail_from) ? 0x80000000u : 0u);
+  if (threadIdx.x == 0) *s = c.totals->err | (handed_over(c, c.totals->tail_from) ? 0x80000000u : 0u);
   __syncthreads();
   const bool f = *s != 0;
   __syncthreads();
@@ -160,6 +160,7 @@ __global__ void k_check_fp(Totals* t) {
 // cleared, and the count of non-empty rows goes to bstat[b].
 __global__ __launch_bounds__(kBlock) void k_init(InitArgs a) {
   __shared__ unsigned s_cnt[kItems * kWaves];
+  if (a.c.guard && handed_over(a.c, a.c.totals->tail_from)) return;
   const int tid = threadIdx.x;
   const int lane = lane_id(), wv = wave_id();
   const int b = blockIdx.x;
@@ -318,7 +319,7 @@ __global__ __launch_bounds__(kPlanThreads) void k_plan(PlanArgs a) {
   Totals tot;  // lane 0: the totals as the kernels before left them
   if (tid == 0) {
     tot = *a.c.totals;
-    s_err = tot.err | ((a.c.guard && tot.tail_from) ? 0x80000000u : 0u);
+    s_err = tot.err | (handed_over(a.c, tot.tail_from) ? 0x80000000u : 0u);
     s_extra = 0;
     s_red[0] = s_red[1] = s_red[2] = 0;
   }

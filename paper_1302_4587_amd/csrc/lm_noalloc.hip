@@ -99,7 +99,7 @@ extern "C" lm_status lm_match_noalloc(lm_ctx* c, const lm_csr* g, uint64_t seed,
   Work wk;
   (void)carve_work(N, nnz, 1, base, &wk);
   hipStream_t s = (hipStream_t)stream;
-  const bool solo = S.solo_fits(N, nnz, 1, nullptr, g->w == nullptr);
+  const bool solo = S.solo_fits(N, nnz, 1, nullptr, nullptr, g->w == nullptr);
   if (!solo)
     hipLaunchKernelGGL(k_single_tables, dim3(1), dim3(64), 0, s, wk.gbase, wk.gseed, wk.vtxoff,
                      (unsigned long long)premix_seed(seed), (long long)N);
@@ -118,5 +118,6 @@ extern "C" lm_status lm_match_noalloc(lm_ctx* c, const lm_csr* g, uint64_t seed,
   lm_stats local;
   std::memset(&local, 0, sizeof(local));
   lm_stats* sp = st ? st : &local;
-  return solo ? S.run_solo(p, wk, nullptr, seed, s, flags, sp) : S.run(p, wk, s, flags, sp);
+  bool declined = false;  // (batches only)
+  return solo ? S.run_solo(p, wk, nullptr, seed, s, flags, sp, &declined) : S.run(p, wk, s, flags, sp);
 }

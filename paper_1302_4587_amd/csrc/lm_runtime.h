@@ -72,6 +72,7 @@ struct Problem {
   int* mate = nullptr;
   int* gphase = nullptr;  // optional per-graph phase counts
   uint64_t seed = 0;      // G = 1: the graph's premixed seed
+  bool after_solo = false;  // (LM_ASYNC) queued behind k_solo's launches: does nothing where they solve the batch
 };
 
 struct ContractState;  // buffers of lm_contract (lm_contract.hip)
@@ -133,9 +134,10 @@ struct Solver {
   Work pool_work() const;  // the pool's buffers, after prepare
   lm_status run(const Problem& p, const Work& wk, hipStream_t s, uint32_t flags, lm_stats* st);
   // One workgroup per graph (lm_solo.hip): whether it takes this solve, and the solve.
-  bool solo_fits(int64_t N, int64_t nnz, int64_t G, const int64_t* vtx_off, bool unweighted) const;
+  // (row_ptr: on the host, or nullptr)
+  bool solo_fits(int64_t N, int64_t nnz, int64_t G, const int64_t* vtx_off, const int64_t* row_ptr, bool unweighted) const;
   lm_status run_solo(const Problem& p, const Work& wk, const int64_t* vtx_off, uint64_t seed, hipStream_t s,
-                     uint32_t flags, lm_stats* st);
+                     uint32_t flags, lm_stats* st, bool* declined);
   hipEvent_t event(size_t i);
 };
 

@@ -34,6 +34,7 @@
 
 #include <algorithm>
 #include <atomic>
+#include <climits>
 #include <cstring>
 #include <type_traits>
 #include <vector>
@@ -339,8 +340,8 @@ __global__ __launch_bounds__(LANES, WPS) void k_solo(SoloArgs a) {
   constexpr int NW = LANES / 64;
   constexpr bool PAIR = SI == 4 || WPS <= 4;  // registers for two steps' loads
   const int tid = threadIdx.x, lane = lane_id(), wv = uni(wave_id());
-  if (a.check_err) {  // the input check found something
-    if (tid == 0) sm.err = a.totals->err;
+  if (a.check_err) {  // the input check found something, or the phase kernels take the batch
+    if (tid == 0) sm.err = a.totals->err | (a.order && a.totals->tail_from != kSoloTook ? (unsigned)kErrDeclined : 0u);
     __syncthreads();
     const unsigned e = sm.err;
     __syncthreads();
@@ -615,7 +616,8 @@ __global__ __launch_bounds__(LANES, WPS) void k_solo(SoloArgs a) {
 // Graphs of a batch by size class (class k: at most cls_n[k] vertices), the
 // ones with the most entries first; the counters and the phase log cleared.
 // One workgroup sorts (a counting sort by four steps per factor of two of
-// the entries), the others clear the log.
+// the entries) and looks for a graph of more than `limit` entries, which leaves
+// the batch to the phase kernels; the others clear the log.
 constexpr int kSoloBins = 128;
 __global__ __launch_bounds__(1024) void k_solo_order(SoloOrder a) {
   if (blockIdx.x > 0) {
@@ -625,11 +627,15 @@ __global__ __launch_bounds__(1024) void k_solo_order(SoloOrder a) {
     return;
   }
   __shared__ int hist[kSoloClasses * kSoloBins];
+  __shared__ int large;
   const int tid = threadIdx.x;
-  if (tid == 0 && a.totals) {
-    a.totals->err = 0;
-    a.totals->last_nonempty = 0;
-    a.totals->matched = 0;
+  if (tid == 0) {
+    large = 0;
+    if (a.clear) {
+      a.totals->err = 0;
+      a.totals->last_nonempty = 0;
+      a.totals->matched = 0;
+    }
   }
   for (int i = tid; i < kSoloClasses * kSoloBins; i += 1024) hist[i] = 0;
   __syncthreads();
@@ -640,6 +646,7 @@ __global__ __launch_bounds__(1024) void k_solo_order(SoloOrder a) {
     int k = 0;
     while (k + 1 < kSoloClasses && vb - va > a.cls_n[k]) ++k;
     const long long e = a.rp[vb] - a.rp[va];
+    if (e > a.limit) large = 1;
     int x = 0;
     if (e >= 4) {
       const int lz = __clzll(e);  // entries may be any value in a malformed row_ptr
@@ -654,6 +661,7 @@ __global__ __launch_bounds__(1024) void k_solo_order(SoloOrder a) {
     else if (a.gphase) a.gphase[i] = 0;
   }
   __syncthreads();
+  if (tid == 0) a.totals->tail_from = large ? 0 : kSoloTook;
   if (tid < 64) {  // exclusive prefix, largest class first
     int carry = 0;
     for (int c = 0; c < kSoloClasses * kSoloBins; c += 64) {
@@ -679,7 +687,10 @@ __global__ __launch_bounds__(1024) void k_solo_fin(SoloArgs a) {
     a.log[i] = LogRec{(long long)r.x, (long long)r.y, (long long)r.z, (long long)r.w};
   }
   __syncthreads();
-  if (threadIdx.x == 0) solo_record(a, a.totals->err, phases + 1, a.totals->matched, 0ull);
+  if (threadIdx.x == 0) {
+    const unsigned declined = a.totals->tail_from != kSoloTook ? (unsigned)kErrDeclined : 0u;
+    solo_record(a, a.totals->err | declined, phases + 1, a.totals->matched, 0ull);
+  }
 }
 
 // ------------------------------------------------------------------ host
@@ -728,18 +739,26 @@ lm_status solo_setup() {
   return LM_OK;
 }
 
-bool Solver::solo_fits(int64_t N, int64_t nnz, int64_t G, const int64_t* vtx_off, bool unweighted) const {
+bool Solver::solo_fits(int64_t N, int64_t nnz, int64_t G, const int64_t* vtx_off, const int64_t* row_ptr,
+                       bool unweighted) const {
   if (tun.tail_entries <= 0) return false;  // phase kernels only
   if (G == 1)
     return N <= kSoloMaxN && nnz <= std::min<int64_t>(unweighted ? kSoloEntriesUnw : kSoloEntries, tun.tail_entries);
-  int64_t mx = 0;
-  for (int64_t g = 0; g < G; ++g) mx = std::max(mx, vtx_off[g + 1] - vtx_off[g]);
-  return mx <= kSoloMaxN;
+  int64_t mx = 0, me = 0;
+  for (int64_t g = 0; g < G; ++g) {
+    mx = std::max(mx, vtx_off[g + 1] - vtx_off[g]);
+    if (row_ptr) me = std::max(me, row_ptr[vtx_off[g + 1]] - row_ptr[vtx_off[g]]);
+  }
+  return mx <= kSoloMaxN && me <= solo_entry_limit(N, nnz, unweighted);
 }
 
-// Runs the solve whose graphs solo_fits accepted.
+// Runs the solve whose graphs solo_fits accepted. The entries of a batch's graphs
+// are on the device: where their number and the graphs' vertices allow one of more
+// than the limit, the device looks, and leaves such a batch to the phase kernels
+// (*declined; a stream-ordered solve has them queued behind, doing nothing
+// otherwise).
 lm_status Solver::run_solo(const Problem& p, const Work& wk, const int64_t* vtx_off, uint64_t seed, hipStream_t s,
-                           uint32_t flags, lm_stats* st) {
+                           uint32_t flags, lm_stats* st, bool* declined) {
 #define HIPCHK(x)                          \
   do {                                     \
     hipError_t _e = (x);                   \
@@ -748,6 +767,7 @@ lm_status Solver::run_solo(const Problem& p, const Work& wk, const int64_t* vtx_
       return dev_status(_e);               \
     }                                      \
   } while (0)
+  *declined = false;
   if (++gen == 0) gen = 1;
   const bool unw = p.w == nullptr;
   const bool check = (flags & LM_CHECK_GRAPH) != 0;
@@ -778,7 +798,7 @@ lm_status Solver::run_solo(const Problem& p, const Work& wk, const int64_t* vtx_
     a.ew[i] = wk.ew[i];
   }
   a.totals = wk.totals;
-  a.check_err = check ? 1 : 0;
+  a.check_err = check || p.G > 1 ? 1 : 0;
   a.gphase = p.gphase;
   a.log = d_log;
   a.log_cap = kLogCap;
@@ -786,6 +806,13 @@ lm_status Solver::run_solo(const Problem& p, const Work& wk, const int64_t* vtx_
   a.gen = gen;
   hipEvent_t ev[2];
   const bool one = p.G == 1 && !check && !prof;  // a single launch
+  // Whether a graph of the batch may have too many entries (n (n - 1) at most).
+  const long long limit = solo_entry_limit(p.N, p.nnz, unw);
+  bool ask = false;
+  for (int64_t g = 0; p.G > 1 && p.nnz > limit && g < p.G && !ask; ++g) {
+    const int64_t n = vtx_off[g + 1] - vtx_off[g];
+    ask = n * (n - 1) > limit;
+  }
   if (!one) HIPCHK(hipEventRecord(e0, s));
   if (check) {
     HIPCHK(launch_zero(wk.ctl, 0, wk.totals, s, nullptr));
@@ -795,6 +822,7 @@ lm_status Solver::run_solo(const Problem& p, const Work& wk, const int64_t* vtx_
   if (p.G == 1) {
     HIPCHK(launch_solo_class(2, unw, a, 1, solo_lds(p.N), s, timing(ev)));
   } else {
+    if (ask && (flags & LM_ASYNC)) HIPCHK(launch_zero(wk.ctl, 2, wk.totals, s, wk.tail));  // (for the phase kernels)
     // With no more graphs than CUs every graph gets the widest workgroup.
     const bool few = p.G <= num_cus;
     int64_t cnt[kSoloClasses] = {}, big[kSoloClasses] = {}, mx = 0;
@@ -816,7 +844,9 @@ lm_status Solver::run_solo(const Problem& p, const Work& wk, const int64_t* vtx_
     o.acc = reinterpret_cast<uint4*>(wk.parts);
     o.acc_n = (int)solo_log_records(mx);
     o.gphase = p.gphase;
-    o.totals = check ? nullptr : wk.totals;
+    o.totals = wk.totals;
+    o.clear = check ? 0 : 1;
+    o.limit = ask ? limit : LLONG_MAX;
     hipLaunchKernelGGL(k_solo_order, dim3(1 + (o.acc_n + 8191) / 8192), dim3(1024), 0, s, o);
     HIPCHK(hipGetLastError());
     a.vtx_off = p.vtx_off;
@@ -852,6 +882,11 @@ lm_status Solver::run_solo(const Problem& p, const Work& wk, const int64_t* vtx_
     HIPCHK(hipGetLastError());
   }
   if (flags & LM_ASYNC) {
+    if (ask) {
+      Problem q = p;
+      q.after_solo = true;
+      return run(q, wk, s, flags, st);
+    }
     HIPCHK(hipEventRecord(e_async, s));
     async_pending = true;
     return LM_OK;
@@ -879,6 +914,10 @@ lm_status Solver::run_solo(const Problem& p, const Work& wk, const int64_t* vtx_
   }
   const PhaseMirror fin = h_mir[kMirrorSlots];
   if ((unsigned)(fin.tag >> 32) != gen) return LM_EDEVICE;
+  if (fin.err == kErrDeclined) {
+    *declined = true;
+    return LM_OK;
+  }
   if (fin.err) {
     if (fin.err & kErrWeight) return LM_EWEIGHT;
     if (fin.err & (kErrRowPtr | kErrColRange | kErrSelfLoop | kErrStall | kErrAsym)) return LM_EGRAPH;

@@ -347,7 +347,7 @@ lm_status Solver::run(const Problem& p, const Work& wk, hipStream_t s, uint32_t 
   c.gseed = wk.gseed;
   c.gphase = p.gphase;
   c.graphs = (int)p.G;
-  c.guard = 0;
+  c.guard = p.after_solo ? kGuardSolo : 0;
   c.renew = (flags & LM_RENEW_KEYS) ? 1 : 0;
   // one large graph: the compactions may read the matched state from bits,
   // if k_init's sample finds its neighbour ids scattered
@@ -408,7 +408,7 @@ lm_status Solver::run(const Problem& p, const Work& wk, hipStream_t s, uint32_t 
   // 16 200 -> 158; R-MAT 14 221 -> 178).
   const bool direct = csr1 && (dev_ctl ? p.nnz <= tail_at : tun.tail_entries > 0 && p.nnz <= tun.tail_entries);
   auto enqueue_prologue = [&]() -> hipError_t {
-    ENQ(launch_zero(dctl, 2, dtot, s, wk.tail));
+    if (!p.after_solo) ENQ(launch_zero(dctl, 2, dtot, s, wk.tail));
     if (p.gphase) ENQ(launch_fill_i32(p.gphase, p.G, 0, s));
     if (flags & LM_CHECK_GRAPH) {
       CheckArgs ca{dtot, p.nnz, p.row_ptr, p.col, p.w, (int)p.N, (int)p.G, p.vtx_off};
@@ -547,7 +547,6 @@ lm_status Solver::run(const Problem& p, const Work& wk, hipStream_t s, uint32_t 
     TailArgs ta;
     std::memset(&ta, 0, sizeof(ta));
     ta.c = c;
-    ta.c.guard = 0;
     ta.tc = wk.tail;
     for (int i = 0; i < 2; ++i) {
       ta.ctl[i] = dctl + i;
@@ -611,9 +610,9 @@ lm_status Solver::run(const Problem& p, const Work& wk, hipStream_t s, uint32_t 
     for (double x = (double)p.nnz; x > (double)tail_at && K < 24; x /= 4.0) ++K;
     auto enqueue_all = [&]() -> hipError_t {
       hipError_t e = enqueue_prologue();
-      c.guard = 1;
+      c.guard |= kGuardTail;
       for (int j = 0; j < K && e == hipSuccess; ++j) e = enqueue_phase();
-      c.guard = 0;
+      c.guard &= ~kGuardTail;
       if (e == hipSuccess) e = enqueue_tail(-1);
       return e;
     };
@@ -934,8 +933,10 @@ static lm_status solve_common(lm_ctx* c, int64_t N, int64_t nnz, int64_t G, cons
   // produced device inputs). A captured graph needs a stream of its own, which
   // then waits for the default stream.
   // Graphs that one workgroup each solves take a few launches and no host
-  // round trip: nothing is captured.
-  const bool solo = N > 0 && S.solo_fits(N, nnz, G, h_vtx_off, w == nullptr);
+  // round trip: nothing is captured (nor where they leave a batch to the phases: a
+  // capture costs such a solve more than the host's polling, 1605 us against 1381).
+  const int64_t* h_rp = (flags & LM_IN_DEVICE) ? nullptr : row_ptr;
+  const bool solo = N > 0 && S.solo_fits(N, nnz, G, h_vtx_off, h_rp, w == nullptr);
   const bool own_stream = !stream && (flags & LM_GRAPH) && !(flags & LM_PROFILE) && !solo;
   hipStream_t s = stream ? (hipStream_t)stream : (own_stream ? S.own : nullptr);
   if (own_stream) {
@@ -1061,8 +1062,10 @@ static lm_status solve_common(lm_ctx* c, int64_t N, int64_t nnz, int64_t G, cons
     rs = check_row_duplicates(S, N, nnz, p.row_ptr, p.col, s);
     if (rs != LM_OK) return rs;
   }
-  rs = solo ? S.run_solo(p, S.pool_work(), h_vtx_off, seeds ? seeds[0] : seed0, s, flags, sp)
-            : S.run(p, S.pool_work(), s, flags, sp);
+  bool declined = false;
+  if (solo) rs = S.run_solo(p, S.pool_work(), h_vtx_off, seeds ? seeds[0] : seed0, s, flags, sp, &declined);
+  if (solo && rs != LM_OK) return rs;
+  if (!solo || declined) rs = S.run(p, S.pool_work(), s, declined ? flags & ~LM_GRAPH : flags, sp);
   if (rs != LM_OK) return rs;
   if (flags & LM_ASYNC) return LM_OK;  // enqueued; the result lands in order on the stream
   double wsum = 0.0;
@@ -1085,7 +1088,7 @@ static lm_status solve_common(lm_ctx* c, int64_t N, int64_t nnz, int64_t G, cons
   }
   // (a solve by whole workgroups has waited for its last kernel, or for the
   // record behind the last store of its only one)
-  if (!(solo && !want_w && out_dev && !graph_phases) && hipStreamSynchronize(s) != hipSuccess) return LM_EDEVICE;
+  if (!(solo && !declined && !want_w && out_dev && !graph_phases) && hipStreamSynchronize(s) != hipSuccess) return LM_EDEVICE;
   if (want_w) st->matched_weight = wsum;
   return LM_OK;
 }

@@ -297,7 +297,7 @@ __global__ __launch_bounds__(kTailBlock) void k_tail(TailArgs a) {
   // An error found before this launch ends it: every workgroup reads the same
   // word. Where this launch checks the input itself, the word may change under a
   // workgroup that starts late: all go to the first exchange and look behind it.
-  if (tid == 0) sm.ok = a.csr_rp || tot->err == 0u ? 1u : 0u;
+  if (tid == 0) sm.ok = (a.csr_rp || tot->err == 0u) && !(c.guard && handed_over(c, tot->tail_from)) ? 1u : 0u;
   __syncthreads();
   if (!sm.ok) return;
   const int c0 = tot->t;
