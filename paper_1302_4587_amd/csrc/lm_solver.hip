@@ -575,10 +575,13 @@ lm_status Solver::run(const Problem& p, const Work& wk, hipStream_t s, uint32_t 
     // queues, and tails that are each resident in part only would wait for each
     // other. (Half of it: R-MAT 14 150 us against 178, ER with 20 K vertices 154
     // against 158, RGG with 60 K 119 against 124.)
+    // From the CSR the tail also walks every vertex: a workgroup per 1024 of them
+    // at least (2^22 vertices with 8 K entries by 2 workgroups 1461 us, by 64 88; 2^20
+    // 525 and 60).
     if (direct) L_hint = p.nnz;
     const long long quarter = std::max(1, num_cus * std::max(1, bpc_tail) / 4);
-    const long long want =
-        L_hint < 0 ? tail_cap : std::min((L_hint + 4095) / 4096, std::max(quarter, (L_hint + 16383) / 16384));
+    const long long by_work = std::max<long long>((L_hint + 4095) / 4096, direct ? (p.N + 1023) / 1024 : 0);
+    const long long want = L_hint < 0 ? tail_cap : std::min(by_work, std::max(quarter, (L_hint + 16383) / 16384));
     const int grid = (int)std::max<long long>(1, std::min<long long>(tail_cap, want));
     ENQ(launch_tail(ta, grid, s, timing(LM_K_TAIL)));
     return hipSuccess;
