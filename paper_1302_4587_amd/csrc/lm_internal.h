@@ -332,16 +332,18 @@ struct TailArgs {
 constexpr long long kSoloMaxN = 65536;     // vertices: candidates are 16-bit local ids in LDS
 // Entries up to which a single graph is solved by one workgroup; beyond them the
 // tail kernel takes it, spread over the chip. Measured (us a call, one workgroup /
-// spread): weighted ER of average degree 16 with 33 K entries 82 / 122, with 66 K
-// 103 / 120, with 99 K 141 / 128; RGG with 32 K 69 / 79, with 64 K 109 / 89, with
-// 98 K 149 / 90; R-MAT, which has more phases, with 10 K 102 / 97, with 46 K
-// 235 / 125. Unweighted (every entry hashed) ER with 50 K 104 / 122, with 66 K
-// 120 / 126; RGG with 32 K 100 / 93, with 48 K 130 / 93; R-MAT with 21 K
-// 117 / 124, with 46 K 182 / 124. A batch has a workgroup for every graph and is
-// faster this way throughout (2 graphs of 2^15 to 2^16 vertices 874 / 2313, 256
-// of them 2251 / 4821).
-constexpr long long kSoloEntries = 1 << 16;
-constexpr long long kSoloEntriesUnw = 1 << 15;
+// spread): weighted ER of average degree 16 with 24 K entries 60 / 89, with 48 K
+// 79 / 93, with 65 K 99 / 102; RGG with 24 K 57 / 70, with 48 K 83 / 82, with 98 K
+// 141 / 84; R-MAT, whose live sets shrink more slowly, with 21 K 100 / 92, with 46 K
+// 136 / 98. Unweighted (every entry hashed) ER with 24 K 68 / 95, with 48 K 93 / 100;
+// RGG with 24 K 83 / 79, with 48 K 120 / 85; R-MAT with 21 K 109 / 104, with 46 K
+// 178 / 113. A graph with a phase for every few vertices costs one workgroup its
+// whole live set each time: a grid with weights that rise across it, 16 K entries
+// 906 / 690, 36 K 2433 / 1150, 65 K 5560 / 1730. The line is in the middle of where
+// the families cross; at it none loses more than a third on either side, but for
+// those with very many phases.
+// A batch has a workgroup for every graph and gains this way far beyond it.
+constexpr long long kSoloEntries = 1 << 15;
 constexpr int kSoloClasses = 3;            // size classes of a batch's graphs
 
 // A batch is solved this way if its largest graph has at most so many entries (N

@@ -577,12 +577,18 @@ lm_status Solver::run(const Problem& p, const Work& wk, hipStream_t s, uint32_t 
     // against 158, RGG with 60 K 119 against 124.)
     // From the CSR the tail also walks every vertex: a workgroup per 1024 of them
     // at least (2^22 vertices with 8 K entries by 2 workgroups 1461 us, by 64 88; 2^20
-    // 525 and 60).
+    // 525 and 60), and one per 1024 entries, since all phases are its own (per 4096: ER
+    // with 48 K entries 111 us against 93, R-MAT with 46 K 107 and 98). An odd number:
+    // vertices are dealt in chunks, and a skewed graph whose degrees follow the bits of
+    // its vertex numbers puts them unevenly on a power of two (R-MAT 14 by 64
+    // workgroups 175 us, by 63 145; R-MAT 15 284 and 210; unweighted 199 and 160, 277
+    // and 194).
     if (direct) L_hint = p.nnz;
     const long long quarter = std::max(1, num_cus * std::max(1, bpc_tail) / 4);
-    const long long by_work = std::max<long long>((L_hint + 4095) / 4096, direct ? (p.N + 1023) / 1024 : 0);
+    const long long by_work = direct ? (std::max<long long>(L_hint, p.N) + 1023) / 1024 : (L_hint + 4095) / 4096;
     const long long want = L_hint < 0 ? tail_cap : std::min(by_work, std::max(quarter, (L_hint + 16383) / 16384));
-    const int grid = (int)std::max<long long>(1, std::min<long long>(tail_cap, want));
+    int grid = (int)std::max<long long>(1, std::min<long long>(tail_cap, want));
+    if (direct && grid % 2 == 0) --grid;
     ENQ(launch_tail(ta, grid, s, timing(LM_K_TAIL)));
     return hipSuccess;
   };

@@ -1,5 +1,5 @@
 """Solves by one workgroup per graph at their limits: a batch whose phase log
-takes every record it has, and results read from elsewhere the moment a call
+takes every record it has, entries up to which one graph is solved that way, and results read from elsewhere the moment a call
 returns."""
 import numpy as np
 import pytest
@@ -67,3 +67,27 @@ def test_result_is_complete_on_return(ctx, noalloc, edges):
             got.copy_(mate, non_blocking=True)
         other.synchronize()
         assert torch.equal(got, want), k
+
+
+@pytest.mark.parametrize("renew", [False, True])
+@pytest.mark.parametrize("weighted", [True, False])
+@pytest.mark.parametrize("shape", ["er", "star", "path"])
+def test_both_sides_of_the_entry_limit(ctx, shape, weighted, renew):
+    """One graph of 2^15 entries (one workgroup) and of two more (the tail kernel)."""
+    import torch
+    for m in (1 << 14, (1 << 14) + 1):
+        if shape == "er":
+            g = lmgen.er(5000, m, 5)
+        else:
+            a = np.arange(m)
+            e = np.stack([np.zeros(m, int) if shape == "star" else a, a + 1], 1)
+            g = lmgen.from_edges(m + 1, e, np.random.default_rng(m).integers(1, 60, m).astype(np.float32))
+        assert g.nnz == 2 * m
+        w = g.w if weighted else np.ones_like(g.w)
+        want, log = oracle.local_max(g.n, g.row_ptr, g.col, w, 3, renew=renew)
+        dev = [torch.from_numpy(g.row_ptr).cuda(), torch.from_numpy(g.col).cuda(), torch.from_numpy(w).cuda() if weighted else None]
+        print(f"case: entry limit {shape} m={m} weighted={weighted} renew={renew}", flush=True)
+        for kw in ({}, {"hip_graph": True}, {"check_graph": True}):
+            mate, st = ctx.match(*dev, seed=3, renew_keys=renew, **kw)
+            assert np.array_equal(mate.cpu().numpy(), want)
+            assert np.array_equal(st.log[:, :3], log * [2, 1, 1])
