@@ -288,6 +288,7 @@ struct InitArgs {
 constexpr int kTailBlock = 1024;
 constexpr int kTailMaxBlocks = 128;
 constexpr int kTailShort = 16;
+constexpr int kTailHubs = 64;
 
 struct TailSeg {
   int base, cap;             // the segment: rows [base, base + cap) of the row buffer
@@ -300,7 +301,9 @@ struct TailSeg {
 struct TailCtl {
   unsigned tag[kTailMaxBlocks];      // exchanges workgroup b has reached
   unsigned abort[32];
-  TailSeg seg[2][kTailMaxBlocks];    // segment table of the list phase t writes: seg[t & 1]
+  unsigned hubs;                     // rows of the CSR left to the whole grid (the first kTailHubs of them), in hub[]
+  int hub[kTailHubs];
+  TailSeg seg[2][kTailMaxBlocks];    // segment table of exchange g: seg[g & 1]
 };
 
 struct TailArgs {

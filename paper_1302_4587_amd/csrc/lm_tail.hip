@@ -49,6 +49,10 @@ constexpr long long kTailSolo = 2048;
 constexpr int kTW = kTailBlock / 64;    // waves per workgroup
 constexpr int kChunk = 8;               // vertices dealt to a workgroup at a time
 constexpr int kLongStep = 4;            // entries per lane and step of a long row
+// The first candidate of a longer row is found by the whole grid, behind an exchange
+// of its own (8 us; one wave reads 8 K entries in 30). A star of 500 K leaves by one
+// wave 1690 us a call, by its workgroup 205, by the grid 89.
+constexpr int kHubRow = 8192;
 constexpr int kRunCache = kMaxBlocks + 1;
 
 __device__ __forceinline__ unsigned ld_u32(const unsigned* p) {
@@ -66,6 +70,7 @@ struct TailSmem {
   int cnt_s, cnt_l;  // rows this workgroup has placed in its segment
   unsigned ok;
   int rp[kRunCache];  // conversion: piece prefix of R_c's runs
+  Key hub[kTW];       // each wave's best of a row of the whole grid
 };
 
 // Ends a phase: this workgroup's segment of the next list (base, cap, and the
@@ -235,6 +240,30 @@ __device__ __forceinline__ void first_lane(const Common& c, int4 r, unsigned lon
   }
 }
 
+// The entry of largest key among the entries e0, e0 + step, ... (kStep each) of
+// the row r of a graph of n vertices, on every lane of the wave.
+constexpr int kStep = 64 * kLongStep;
+__device__ __forceinline__ Key best_of_row(int4 r, int e0, int step, const int* col, const float* w, int n,
+                                           unsigned long long S) {
+  const int lane = lane_id();
+  Best best = best_ident();
+  for (; e0 < r.z; e0 += step) {
+    int u[kLongStep];
+    float x[kLongStep];
+#pragma unroll
+    for (int h = 0; h < kLongStep; ++h) {
+      const int e = e0 + 64 * h + lane;
+      u[h] = e < r.z ? col[r.y + e] : -1;
+      x[h] = e < r.z && w ? w[r.y + e] : 1.0f;
+    }
+#pragma unroll
+    for (int h = 0; h < kLongStep; ++h)
+      if ((unsigned)u[h] < (unsigned)n)
+        best_update(best, ord_weight_bits(__float_as_uint(x[h])), u[h], (unsigned)r.x, S);
+  }
+  return wave_max_key(best_key(best, (unsigned)r.x, S));
+}
+
 // One phase of the row r (v's) by one lane: -1 if v is matched (with cv);
 // otherwise the entries of unmatched neighbours go to the next entry buffer,
 // their number is returned and best gets the largest key among them. The loads
@@ -286,7 +315,8 @@ __device__ __forceinline__ int row_lane(const Common& c, int4 r, int base, unsig
 // virtual range first. R_1 needs no copy: its entries are the input rows. Where
 // the tail is the whole solve of one graph (csr_rp) the list is made from the
 // CSR, its offsets checked as k_init does, and the first candidates with it:
-// short rows by a lane each, the others, listed first, by a wave each.
+// short rows by a lane each, the others, listed first, by a wave each, and up to
+// kTailHubs rows of more than kHubRow entries by the whole grid.
 __global__ __launch_bounds__(kTailBlock) void k_tail(TailArgs a) {
   __shared__ TailSmem sm;
   Common& c = a.c;
@@ -370,22 +400,16 @@ __global__ __launch_bounds__(kTailBlock) void k_tail(TailArgs a) {
     const int nl = sm.cnt_l;
     for (int j = wv; j < nl; j += kTW) {
       const int4 r = TA[k1 - 1 - j];
-      Best best = best_ident();
-      for (int e0 = 0; e0 < r.z; e0 += 64 * kLongStep) {
-        int u[kLongStep];
-        float w[kLongStep];
-#pragma unroll
-        for (int h = 0; h < kLongStep; ++h) {
-          const int e = e0 + 64 * h + lane;
-          u[h] = e < r.z ? cur_col[r.y + e] : -1;
-          w[h] = e < r.z && !unw ? cur_w[r.y + e] : 1.0f;
+      if (r.z > kHubRow) {  // left to the grid
+        unsigned h = 0;
+        if (lane == 0) h = atomicAdd(&tc->hubs, 1u);
+        h = __builtin_amdgcn_readfirstlane(h);
+        if (h < (unsigned)kTailHubs) {
+          if (lane == 0) tc->hub[h] = r.x;
+          continue;
         }
-#pragma unroll
-        for (int h = 0; h < kLongStep; ++h)
-          if ((unsigned)u[h] < (unsigned)c.n)
-            best_update(best, ord_weight_bits(__float_as_uint(w[h])), u[h], (unsigned)r.x, Sd);
       }
-      const Key kb = wave_max_key(best_key(best, (unsigned)r.x, Sd));
+      const Key kb = best_of_row(r, 0, kStep, cur_col, cur_w, c.n, Sd);
       if (lane == 0) c.C[r.x] = kb.u;
     }
   } else {
@@ -444,8 +468,42 @@ __global__ __launch_bounds__(kTailBlock) void k_tail(TailArgs a) {
     }
   }
   unsigned g = 1;
-  if (!exchange(tc, tc->seg[(c0 - 1) & 1], k0, k1 - k0, nb, g, false, limit, tot, sm)) return;
+  const int cnt_s = sm.cnt_s, cnt_l = sm.cnt_l;
+  if (!exchange(tc, tc->seg[g & 1], k0, k1 - k0, nb, g, false, limit, tot, sm)) return;
   if (csr && ld_u32(&tot->err)) return;  // (the same word everywhere: nothing is added before the next exchange)
+  const int nhub = csr ? min((int)ld_u32(&tc->hubs), kTailHubs) : 0;
+  if (nhub > 0) {  // every workgroup a slice of each, then, behind an exchange, the best of the slices
+    const unsigned long long Sd = cand_seed(c.gseed[0], c.renew, 1);
+    Key* part = reinterpret_cast<Key*>(a.ecol[0]);  // (the buffer that phase 2 writes: more than kHubRow entries)
+    for (int h = 0; h < nhub; ++h) {
+      const int v = tc->hub[h];
+      const int e0 = (int)a.csr_rp[v];
+      const long long len = a.csr_rp[v + 1] - e0;
+      const int s0 = (int)(len * b / nb), s1 = (int)(len * (b + 1) / nb);
+      const Key kb = best_of_row(make_int4(v, e0 + s0, s1 - s0, 0), kStep * wv, kStep * kTW, cur_col, cur_w, c.n, Sd);
+      if (lane == 0) sm.hub[wv] = kb;
+      __syncthreads();
+      if (wv == 0) {
+        const Key best = wave_max_key(lane < kTW ? sm.hub[lane] : key_ident());
+        if (lane == 0) part[h * kTailMaxBlocks + b] = best;
+      }
+      __syncthreads();
+    }
+    if (tid == 0) {
+      sm.cnt_s = cnt_s;
+      sm.cnt_l = cnt_l;
+    }
+    ++g;
+    if (!exchange(tc, tc->seg[g & 1], k0, k1 - k0, nb, g, false, limit, tot, sm)) return;
+    for (int h = wv; h < nhub; h += kTW) {  // (every workgroup stores the same)
+      const Key* p = part + h * kTailMaxBlocks;
+      const Key x0 = lane < nb ? p[lane] : key_ident(), x1 = lane + 64 < nb ? p[lane + 64] : key_ident();
+      const Key best = wave_max_key(key_max(x0, x1));
+      if (lane == 0) c.C[tc->hub[h]] = best.u;
+    }
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+  }
   // ---- phases c, c + 1, ...
   // Candidates, as ids of their graph: one phase's in C, the next one's in
   // mate, which a vertex keeps until its row ends.
@@ -607,7 +665,8 @@ __global__ __launch_bounds__(kTailBlock) void k_tail(TailArgs a) {
       atomicAdd(reinterpret_cast<unsigned long long*>(&sm.md_b), (unsigned long long)md_b);
       atomicAdd(&sm.mv_b, mv_b);
     }
-    if (!exchange(tc, tc->seg[t & 1], obase, ocap, nb, ++g, solo, limit, tot, sm)) return;
+    ++g;
+    if (!exchange(tc, tc->seg[g & 1], obase, ocap, nb, g, solo, limit, tot, sm)) return;
     // next live set
     prevL = L;
     prevV = V;
