@@ -660,8 +660,9 @@ __global__ __launch_bounds__(kBlock, 5) void k_first_rows(FirstRowsArgs a) {
     if (b + nw < nblk) offs(b + nw, n0, n1);  // the next block's rows
     unsigned long long lng = __ballot(len > thr);
     if (lng) {
-      const unsigned long long hub = __ballot(len > kRHub);
-      if (!hub && __popcll(lng) <= kRFew) {
+      const bool huge = len > kRSeg;
+      const unsigned long long hub = __ballot(len > kRHub && !huge);
+      if (__ballot(len > kRHub) == 0ull && __popcll(lng) <= kRFew) {
         while (lng) {
           const int src = __ffsll((long long)lng) - 1;
           lng &= lng - 1;
@@ -673,7 +674,12 @@ __global__ __launch_bounds__(kBlock, 5) void k_first_rows(FirstRowsArgs a) {
           if (lane == 0 && bw != 0u) a.C[rv] = bu;
         }
       } else {  // waves' rows from the list's front, hubs from its back
-        lng &= ~hub;
+        if (huge) {
+          const unsigned ns = ((unsigned)len + kRSeg - 1u) / kRSeg;
+          const unsigned s0 = atomicAdd(&a.totals->segs, ns);
+          for (unsigned i = 0; i < ns; ++i) a.seg[s0 + i] = make_int4(v, (int)s0, 0, 0);
+        }
+        lng &= ~(hub | __ballot(huge));
         unsigned al = 0u, ah = 0u;
         if (lane == 0) {
           if (lng) al = atomicAdd(&a.totals->longs, (unsigned)__popcll(lng));
@@ -682,8 +688,8 @@ __global__ __launch_bounds__(kBlock, 5) void k_first_rows(FirstRowsArgs a) {
         al = uni(al);
         ah = uni(ah);
         const unsigned long long lt = lanemask_lt();
-        if (len > kRHub) a.list[a.n - 1 - (int)(ah + (unsigned)__popcll(hub & lt))] = v;
-        else if (len > thr) a.list[al + (unsigned)__popcll(lng & lt)] = v;
+        if (len > kRHub && !huge) a.list[a.n - 1 - (int)(ah + (unsigned)__popcll(hub & lt))] = v;
+        else if (len > thr && !huge) a.list[al + (unsigned)__popcll(lng & lt)] = v;
       }
     }
     if (len > thr) len = 0;
@@ -721,13 +727,51 @@ __global__ __launch_bounds__(kBlock, 5) void k_first_rows(FirstRowsArgs a) {
   }
 }
 
-// The listed rows: hubs a workgroup each, then the others a wave each.
+// The listed rows: slices of the longest, then hubs, a workgroup each, then the
+// others a wave each. The workgroup that ends a row's last slice takes the best of
+// them; C[v], -1 until then, counts the slices done. (A row by one workgroup: a star
+// of 1 M leaves 357 us a call, one of 20 M 4160; in slices 243 and 1000.)
 constexpr int kHubLanes = 1024;
 __global__ __launch_bounds__(kHubLanes) void k_first_long(FirstRowsArgs a) {
   __shared__ unsigned sw[kHubLanes / 64];
   __shared__ int su[kHubLanes / 64];
+  __shared__ int last;
   if (a.totals->err) return;
   const int tid = threadIdx.x, wv = uni(wave_id());
+  const int segs = (int)a.totals->segs;
+  for (int q = blockIdx.x; q < segs; q += gridDim.x) {
+    const int v = uni(a.seg[q].x), first = uni(a.seg[q].y);
+    const int off = uni((int)a.rp[v]), len = uni((int)a.rp[v + 1]) - off, s0 = (q - first) * kRSeg;
+    const int ns = (int)(((unsigned)len + kRSeg - 1u) / kRSeg);
+    unsigned bw = 0u;
+    int bu = 0;
+    row_best<kRI, kHubLanes>(a.col, a.w, off + s0, min(kRSeg, len - s0), tid, (int)a.nnz, a.n, (unsigned)v, a.S, bw, bu);
+    if (lane_id() == 0) {
+      sw[wv] = bw;
+      su[wv] = bu;
+    }
+    __syncthreads();
+    if (tid == 0) {
+      for (int i = 1; i < kHubLanes / 64; ++i) best_pair(bw, bu, sw[i], su[i], (unsigned)v, a.S);
+      a.seg[q].z = (int)bw;
+      a.seg[q].w = bu;
+      __threadfence();  // the slice's best before its count
+      last = atomicSub(&a.C[v], 1) == -ns;
+      __threadfence();
+    }
+    __syncthreads();
+    if (last && wv == 0) {
+      bw = 0u;
+      for (int i = lane_id(); i < ns; i += 64) {
+        const int4 r = a.seg[first + i];
+        best_pair(bw, bu, (unsigned)r.z, r.w, (unsigned)v, a.S);
+      }
+      const unsigned long long h = bw ? edge_hash(a.S, (unsigned)v, (unsigned)bu) : 0ull;
+      const Key best = wave_max_key(Key{bw, (unsigned)(h >> 32), (unsigned)h, bw ? bu : -1});
+      if (lane_id() == 0) a.C[v] = best.u;
+    }
+    __syncthreads();
+  }
   const int hubs = (int)a.totals->hubs, longs = (int)a.totals->longs;
   for (int h = blockIdx.x; h < hubs; h += gridDim.x) {
     const int v = uni(a.list[a.n - 1 - h]);

@@ -94,6 +94,7 @@ struct Totals {
   int tail_from;  // guarded phases: the live set R_t the tail kernel takes over (0 = none yet), or kSoloTook
   unsigned long long fp[2];  // LM_CHECK_GRAPH: fingerprints of the entries and of their mirrors
   unsigned hubs, longs;      // rows left to k_first_long
+  unsigned segs;             // slices of rows too long for one workgroup, left to it as well
   unsigned far, samp;        // sampled first entries of R_1 whose neighbour id is far from the row's
 };
 
@@ -108,13 +109,13 @@ __host__ __device__ __forceinline__ bool bits_on(const Totals* t) {
 }
 
 // The first compaction of one weighted graph takes whole rows (k_compact_rows)
-// when the first argmax listed no row for a whole workgroup and at most one for a
+// when the first argmax listed no row for whole workgroups and at most one for a
 // wave in 64 vertices: a wave takes such a row alone, two times over. ER with
 // 2^20 vertices of degree 10 beside rows of 1000 (2000) entries, whole solve by
 // piece windows -> by rows: none 386 -> 339 us, one in 100 vertices 577 -> 533,
 // one in 70 677 -> 659 (920 -> 917): the line is where the gain ends.
 __host__ __device__ __forceinline__ bool compact_by_rows(const Totals* t, int n) {
-  return t->hubs == 0u && 64ull * t->longs <= (unsigned long long)(unsigned)n;
+  return t->hubs == 0u && t->segs == 0u && 64ull * t->longs <= (unsigned long long)(unsigned)n;
 }
 
 // What the host loop needs after each plan, written by the plan kernel into
@@ -402,7 +403,12 @@ struct SoloArgs {
   unsigned gen;
 };
 
-// First argmax of one weighted graph by whole rows (k_first_rows).
+// First argmax of one weighted graph by whole rows (k_first_rows). Rows of more
+// than kRSeg entries are read in slices of at most that many; their records fit the
+// buffer of the partial results.
+constexpr int kRSeg = 1 << 17;
+constexpr long long kFirstSegs = 2ll * (((1ll << 31) - 65536) / kRSeg);
+static_assert(kFirstSegs * sizeof(int4) <= (size_t)kMaxFirstRanges * 2 * sizeof(Part), "slices of the longest rows");
 struct FirstRowsArgs {
   const long long* rp;
   const int* col;
@@ -413,6 +419,7 @@ struct FirstRowsArgs {
   unsigned long long S;  // the seed of the candidates of phase 1
   int lg;                // lanes per row (log2)
   int* list;             // n words: the rows left to k_first_long
+  int4* seg;             // kFirstSegs records: {v, the row's first slice, w and u of the slice's best}
   Totals* totals;
 };
 

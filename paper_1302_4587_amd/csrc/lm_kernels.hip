@@ -53,6 +53,7 @@ __global__ void k_zero(Ctl* ctl, int nctl, Totals* totals, TailCtl* tc) {
     totals->fp[1] = 0;
     totals->hubs = 0;
     totals->longs = 0;
+    totals->segs = 0;
     totals->far = 0;
     totals->samp = 0;
   }

@@ -462,6 +462,7 @@ lm_status Solver::run(const Problem& p, const Work& wk, hipStream_t s, uint32_t 
       fa.S = cand_seed(p.seed, c.renew != 0, 1);
       fa.lg = first_rows_lg(p.nnz, p.N);
       fa.list = reinterpret_cast<int*>(wk.rows[0]);  // (R_1 has no piece records)
+      fa.seg = reinterpret_cast<int4*>(wk.parts);  // (no row is cut here)
       fa.totals = dtot;
       ENQ(launch_first_rows(fa, num_cus, s, timing(LM_K_ARGMAX)));
       return hipSuccess;

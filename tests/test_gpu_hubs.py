@@ -67,6 +67,17 @@ def test_tail_from_the_csr(ctx, degrees, shared, weights):
     _check(ctx, g, f"hub rows {len(degrees)} {degrees[:4]} {weights}", [{"tail_entries": 1 << 22}])
 
 
+SEG = 1 << 17  # entries of a slice of a row that several workgroups read
+
+
+@pytest.mark.parametrize("weights", ["uniform", "tied", "signed"])
+@pytest.mark.parametrize("degrees,shared", [((SEG - 1, SEG, SEG + 1, 2 * SEG, 2 * SEG + 1), False), ((5 * SEG + 77, 2049, 300), True), ((150000, 140000, 3000), True)])
+def test_first_argmax_of_phases(ctx, degrees, shared, weights):
+    g = _stars(degrees, weights, 9, shared)
+    assert g.nnz > 500000
+    _check(ctx, g, f"slices {degrees} {weights}", [{"tail_entries": 5000}])
+
+
 def test_time_of_a_large_star(ctx):
     """A row of half a million entries: 0.09 ms, 1.7 ms where one wave reads it."""
     import time
