@@ -262,7 +262,8 @@ typedef struct {
                            LDS buckets of about 512 entries by a hash of the coarse neighbour */
   int64_t long_entries; /* the fine entries of those rows */
   int64_t table_rows;   /* long rows merged through per-row hash tables in device memory
-                           instead (all of them, when a bucket outgrew LDS; normally 0) */
+                           instead: those of more than 2^19 entries, where the budget has
+                           room for the tables, and all of them when a bucket outgrew LDS */
 } lm_contract_stats;
 
 /* Contracts a graph by a matching: the coarsening step of multilevel graph

@@ -24,6 +24,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <climits>
 #include <cstring>
 #include <mutex>
 
@@ -49,6 +50,11 @@ constexpr int kLSmall = 4;    // buckets of a long row that a workgroup of kBloc
 constexpr int kLPart = 8;     // buckets a workgroup of kLBig lanes merges at once
 constexpr int kLBig = 1024;
 constexpr int kLC = 8192;     // entries of a long row per chunk of the mapping and the output
+// A row of more entries than this is merged through a table in device memory: its
+// parts would each read all of it, 4 bytes an entry and part, which grows with the
+// square of its length. A star of 600 K leaves 423 us (parts) / 339 (table), of 3 M
+// 1936 / 1046, of 30 M 100 ms / 9.4.
+constexpr int kLTable = 1 << 19;
 constexpr int kLDrop = 512;   // chunks of a row whose dropped entries a part counts in LDS
 
 constexpr unsigned kCErrMate = 1u;    // mate is not an involution with -1 for free vertices
@@ -61,11 +67,12 @@ struct CTot {
   unsigned pad;
   long long nc;            // coarse vertices
   long long nnz_c;         // coarse entries
-  long long nlong;         // coarse rows merged through device-memory tables
+  long long nlong;         // long rows
   long long long_entries;  // the sum of their bounds
-  long long long_slots;    // hash slots their tables take
-  long long long_items;    // low word: long rows of at most kLSmall buckets; high word: parts of kLPart buckets of the others
-  long long long_chunks;   // row-aligned chunks of kLC entries
+  long long tab_entries;   // the same of those merged through device-memory tables
+  long long long_slots;    // hash slots these tables take
+  long long long_items;    // of the others, low word: rows of at most kLSmall buckets; high word: parts of kLPart buckets
+  long long long_chunks;   // row-aligned chunks of kLC entries; from bit 40 on the rows merged through tables
   unsigned overflow;       // a bucket outgrew LDS: the long rows take the table path
   unsigned pad2;
 };
@@ -75,8 +82,8 @@ struct LongRow {
   int ub;     // deg(a) + deg(b)
   int tbits;  // table of 2^tbits slots
   int nb;     // buckets of the row (about kLB entries each)
-  int np;     // parts of kLPart buckets; 0: at most kLSmall buckets
-  long long eoff;  // first flat index of the row's entries among all long rows
+  int np;     // parts of kLPart buckets; 0: at most kLSmall buckets; -1: merged through a table
+  long long eoff;  // first flat index of the row's entries among those of the rows with a table
   long long toff;  // first slot of its table
   int soff, boff;  // its place among the rows of at most kLSmall buckets; its first part
   long long coff;  // first chunk of the row (kLC entries each)
@@ -109,7 +116,8 @@ struct CArgs {
   int* next;  // per fine entry of a long row: the previous entry of its table slot's list (table path)
   LongRow* lrows;
   long long lrow_cap;
-  int2* table;  // (key, list head) per slot of the long rows' tables
+  long long table_from;  // long rows of more entries are merged through tables
+  int2* table;  // (key, list head) per slot of the tables
   int* srow;   // long row of each row of at most kLSmall buckets
   int* prow;   // long row of each part
   int* crow;   // long row of each chunk
@@ -886,39 +894,44 @@ __global__ __launch_bounds__(kBlock) void k_c_copy(CArgs a) {
   }
 }
 
-// (3a') Sizes of the long rows: entries (their bound), table slots (the
-// power of two at least twice the bound), whether one small workgroup merges
-// the row, parts and chunks, and the offsets of each in row order. Workgroup
+// (3a') Sizes of the long rows: entries (their bound) and table slots (the
+// power of two at least twice the bound) of those merged through tables, whether
+// one small workgroup merges the row, parts and chunks, and the offsets of each in
+// row order. Workgroup
 // g sums kLPRows rows (k_c_long_sums), one scan over the workgroup sums per
 // quantity gives the totals (k_c_scan_top), and each workgroup writes its
 // rows' offsets from its prefix (k_c_long_offs). The grid covers the row
 // capacity; workgroups past the long rows counted write zero sums.
 constexpr int kLP = 4;                 // long rows per lane in the prep kernels
 constexpr int kLPRows = kBlock * kLP;  // long rows per workgroup
-constexpr int kLQ = 4;                 // quantities
+constexpr int kLQ = 5;                 // quantities
+constexpr long long kLTabBit = 1ll << 40;
 
-__device__ __forceinline__ void long_row_sizes(long long ub, int& bits, int& nb, int& np, long long v[kLQ]) {
+__device__ __forceinline__ void long_row_sizes(long long ub, long long table_from, int& bits, int& nb, int& np,
+                                               long long v[kLQ]) {
+  const bool tab = ub > table_from;
   const long long t = 2 * ub;
   bits = t <= 2 ? 1 : 64 - __clzll((unsigned long long)(t - 1));  // smallest bits >= 1 with 2^bits >= 2 ub
   nb = (int)((ub + kLB - 1) / kLB);
-  np = nb <= kLSmall ? 0 : (nb + kLPart - 1) / kLPart;
-  v[0] = ub;
-  v[1] = 1ll << bits;
-  v[2] = np == 0 ? 1 : (long long)np << 32;  // (each sum is below 2^31)
-  v[3] = (ub + kLC - 1) / kLC;
+  np = tab ? -1 : nb <= kLSmall ? 0 : (nb + kLPart - 1) / kLPart;
+  v[0] = tab ? ub : 0;
+  v[1] = tab ? 1ll << bits : 0;
+  v[2] = tab ? 0 : np == 0 ? 1 : (long long)np << 32;  // (each sum is below 2^31)
+  v[3] = (ub + kLC - 1) / kLC + (tab ? kLTabBit : 0);
+  v[4] = ub;
 }
 
 __global__ __launch_bounds__(kBlock) void k_c_long_sums(CArgs a, long long* lsum, long long nblk) {
   __shared__ long long sm[kWaves];
   const long long nl = a.tot->err ? 0 : (a.tot->nlong < a.lrow_cap ? a.tot->nlong : a.lrow_cap);
-  long long su[kLQ] = {0, 0, 0, 0};
+  long long su[kLQ] = {};
   const long long i0 = (long long)blockIdx.x * kLPRows + (long long)threadIdx.x * kLP;
 #pragma unroll
   for (int j = 0; j < kLP; ++j) {
     if (i0 + j >= nl) continue;
     int bits, nb, np;
     long long v[kLQ];
-    long_row_sizes(a.lrows[i0 + j].ub, bits, nb, np, v);
+    long_row_sizes(a.lrows[i0 + j].ub, a.table_from, bits, nb, np, v);
 #pragma unroll
     for (int q = 0; q < kLQ; ++q) su[q] += v[q];
   }
@@ -943,7 +956,7 @@ __global__ __launch_bounds__(kCTopThreads) void k_c_long_top(long long* lsum, lo
     if (i < nblk) v[i] = carry + e;
     carry += t;
   }
-  long long* total[kLQ] = {&tot->long_entries, &tot->long_slots, &tot->long_items, &tot->long_chunks};
+  long long* total[kLQ] = {&tot->tab_entries, &tot->long_slots, &tot->long_items, &tot->long_chunks, &tot->long_entries};
 #pragma unroll
   for (int q = 0; q < kLQ; ++q)
     if (threadIdx.x == 0 && blockIdx.x == q) *total[q] = carry;
@@ -957,14 +970,14 @@ __global__ __launch_bounds__(kBlock) void k_c_long_offs(CArgs a, const long long
   const long long i0 = (long long)blockIdx.x * kLPRows + (long long)threadIdx.x * kLP;
   int bits[kLP], nb[kLP], np[kLP];
   long long v[kLP][kLQ];
-  long long su[kLQ] = {0, 0, 0, 0};
+  long long su[kLQ] = {};
 #pragma unroll
   for (int j = 0; j < kLP; ++j) {
     bits[j] = 1;
     nb[j] = np[j] = 0;
 #pragma unroll
     for (int q = 0; q < kLQ; ++q) v[j][q] = 0;
-    if (i0 + j < nl) long_row_sizes(a.lrows[i0 + j].ub, bits[j], nb[j], np[j], v[j]);
+    if (i0 + j < nl) long_row_sizes(a.lrows[i0 + j].ub, a.table_from, bits[j], nb[j], np[j], v[j]);
 #pragma unroll
     for (int q = 0; q < kLQ; ++q) su[q] += v[j][q];
   }
@@ -985,21 +998,43 @@ __global__ __launch_bounds__(kBlock) void k_c_long_offs(CArgs a, const long long
       L.np = np[j];
       L.soff = (int)(off[2] & 0x7fffffffll);
       L.boff = (int)(off[2] >> 32);
-      L.coff = off[3];
+      L.coff = off[3] & (kLTabBit - 1);
     }
 #pragma unroll
     for (int q = 0; q < kLQ; ++q) off[q] += v[j][q];
   }
 }
 
-// The long row of every small row, part and chunk.
+// The long row of every small row, part and chunk; the chunk counts of the rows
+// with a table are cleared. A lane a row, a wave the longest ones.
 __global__ __launch_bounds__(kBlock) void k_c_long_tables(CArgs a, long long nl) {
-  for (long long r = (long long)blockIdx.x * kBlock + threadIdx.x; r < nl; r += (long long)gridDim.x * kBlock) {
-    const LongRow L = a.lrows[r];
-    if (L.np == 0) a.srow[L.soff] = (int)r;
-    for (int p = 0; p < L.np; ++p) a.prow[L.boff + p] = (int)r;
-    const int nc = (L.ub + kLC - 1) / kLC;
-    for (int j = 0; j < nc; ++j) a.crow[L.coff + j] = (int)r;
+  const long long step = (long long)gridDim.x * kBlock;
+  for (long long r0 = (long long)blockIdx.x * kBlock + (threadIdx.x & ~63u); r0 < nl; r0 += step) {
+    const long long r = r0 + lane_id();
+    int np = 0, nc = 0, boff = 0;
+    long long coff = 0;
+    if (r < nl) {
+      const LongRow L = a.lrows[r];
+      np = L.np;
+      nc = (L.ub + kLC - 1) / kLC;
+      boff = L.boff;
+      coff = L.coff;
+      if (np == 0) a.srow[L.soff] = (int)r;
+    }
+    auto put = [&](int row, int p, int pe, int bo, int c, int ce, long long co, bool tab, int by) {
+      for (; p < pe; p += by) a.prow[bo + p] = row;
+      for (; c < ce; c += by) {
+        a.crow[co + c] = row;
+        if (tab) a.ccnt[co + c] = 0;
+      }
+    };
+    const bool big = nc > 64;
+    if (!big) put((int)r, 0, np, boff, 0, nc, coff, np < 0, 1);
+    for (unsigned long long m = __ballot(big); m; m &= m - 1) {
+      const int src = __ffsll((long long)m) - 1, l = lane_id();
+      const int n1 = __shfl(np, src, 64);
+      put((int)(r0 + src), l, n1, __shfl(boff, src, 64), l, __shfl(nc, src, 64), __shfl(coff, src, 64), n1 < 0, 64);
+    }
   }
 }
 
@@ -1022,11 +1057,11 @@ __device__ __forceinline__ long long long_row_of(const LongRow* L, long long nl,
 }
 
 // The long row of flat index i, searched forward from r0 (the row of the
-// chunk's first index; rows are longer than a chunk's lane stride).
+// chunk's first index), which mostly holds it; rows without a table lie between.
 __device__ __forceinline__ long long long_row_from(const LongRow* L, long long nl, long long r0, long long i) {
-  long long r = r0;
-  while (r + 1 < nl && L[r + 1].eoff <= i) ++r;
-  return r;
+  if (r0 + 1 >= nl || L[r0 + 1].eoff > i) return r0;
+  if (r0 + 2 >= nl || L[r0 + 2].eoff > i) return r0 + 1;
+  return long_row_of(L, nl, i);
 }
 
 constexpr int kLI = 4;  // long-row entries per lane per round (their loads are in flight together)
@@ -1137,8 +1172,10 @@ __global__ __launch_bounds__(kBlock) void k_c_long_keep(CArgs a, long long nl, l
     int nxt[kLI];
 #pragma unroll
     for (int j = 0; j < kLI; ++j) nxt[j] = D[j] >= 0 ? a.next[slot[j].y] : -1;
+    long long ch[kLI];  // the chunk of a kept entry
 #pragma unroll
     for (int j = 0; j < kLI; ++j) {
+      ch[j] = -1;
       if (at[j].k < 0) continue;
       if (D[j] < 0) {
         if (a.dmap) a.dmap[at[j].k] = -1;
@@ -1190,11 +1227,35 @@ __global__ __launch_bounds__(kBlock) void k_c_long_keep(CArgs a, long long nl, l
       }
       a.dmap[at[j].k] = nlst > 1 ? D[j] | kMerged : D[j];
       if (nlst > 1) a.aux[at[j].k] = sum;
-      atomicAdd(&a.cnt[L.a], 1);
-      atomicAdd(&a.ccnt[L.coff + at[j].off / kLC], 1);
+      ch[j] = L.coff + at[j].off / kLC;
+    }
+    // (the lanes of a wave are mostly in one chunk)
+#pragma unroll
+    for (int j = 0; j < kLI; ++j) {
+      const unsigned long long m = __ballot(ch[j] >= 0);
+      if (m == 0ull) continue;
+      const int lead = __ffsll((long long)m) - 1;
+      const long long c0 = __shfl(ch[j], lead, 64);
+      const unsigned long long same = __ballot(ch[j] == c0);
+      if (lane_id() == lead) atomicAdd(&a.ccnt[c0], (int)__popcll(same));
+      else if (ch[j] >= 0 && ch[j] != c0) atomicAdd(&a.ccnt[ch[j]], 1);
     }
   }
   if (err) atomicOr(&a.tot->err, err);
+}
+
+// The kept entries of the rows with a table, from their chunks' counts; a wave a
+// row.
+__global__ __launch_bounds__(kBlock) void k_c_long_cnt(CArgs a, long long nl) {
+  for (long long r = (long long)blockIdx.x * kWaves + wave_id(); r < nl; r += (long long)gridDim.x * kWaves) {
+    const LongRow L = a.lrows[r];
+    if (L.np >= 0) continue;
+    int kept = 0;
+    const int nc = (L.ub + kLC - 1) / kLC;
+    for (int i = lane_id(); i < nc; i += 64) kept += a.ccnt[L.coff + i];
+    kept = wave_incl_sum<int>(kept);
+    if (lane_id() == 63) a.cnt[L.a] = kept;
+  }
 }
 
 // ---- long rows: the coarse neighbours of a row are split into buckets by a
@@ -1408,15 +1469,6 @@ __global__ __launch_bounds__(LANES, LANES == kLBig ? 8 : 4) void k_c_long_group(
   if (err) atomicOr(&a.tot->err, err);
 }
 
-// Clears the kept counts of the long rows and their chunks (before the table
-// path redoes them after a bucket overflow).
-__global__ __launch_bounds__(kBlock) void k_c_long_clear_cnt(CArgs a, long long nl, long long nchunks) {
-  for (long long r = (long long)blockIdx.x * kBlock + threadIdx.x; r < nl; r += (long long)gridDim.x * kBlock)
-    a.cnt[a.lrows[r].a] = 0;
-  for (long long c = (long long)blockIdx.x * kBlock + threadIdx.x; c < nchunks; c += (long long)gridDim.x * kBlock)
-    a.ccnt[c] = 0;
-}
-
 // Lengths of the coarse rows base + i * kBlock + lane, all loads of a step in
 // flight together.
 __device__ __forceinline__ void coarse_degs(const CArgs& a, long long base, long long nc, int (&deg)[kCV]) {
@@ -1611,6 +1663,7 @@ lm_status check_row_duplicates(Solver& S, int64_t n, int64_t nnz, const long lon
   a.lrow_cap = lrow_cap;
   a.dup_limit = 1;
   a.identity = 1;
+  a.table_from = 0;
   if (hipMemsetAsync(a.tot, 0, sizeof(CTot), s) != hipSuccess) return LM_EDEVICE;
   set_ranges(a, P, cs.ranges, S.num_cus);
   hipLaunchKernelGGL(k_c_count, dim3((unsigned)nb_v), dim3(kBlock), 0, s, a);
@@ -1631,9 +1684,9 @@ lm_status check_row_duplicates(Solver& S, int64_t n, int64_t nnz, const long lon
     a.table = (int2*)cs.table.p;
     const long long fill_grid = std::min<long long>((t1.long_slots + kBlock - 1) / kBlock, 8192);
     hipLaunchKernelGGL(k_c_fill, dim3((unsigned)fill_grid), dim3(kBlock), 0, s, a.table, t1.long_slots);
-    const long long lg = std::min<long long>((t1.long_entries + kBlock * kLI - 1) / (kBlock * kLI), 16384);
-    hipLaunchKernelGGL(k_c_long_insert, dim3((unsigned)lg), dim3(kBlock), 0, s, a, t1.nlong, t1.long_entries);
-    hipLaunchKernelGGL(k_c_long_keep, dim3((unsigned)lg), dim3(kBlock), 0, s, a, t1.nlong, t1.long_entries);
+    const long long lg = std::min<long long>((t1.tab_entries + kBlock * kLI - 1) / (kBlock * kLI), 16384);
+    hipLaunchKernelGGL(k_c_long_insert, dim3((unsigned)lg), dim3(kBlock), 0, s, a, t1.nlong, t1.tab_entries);
+    hipLaunchKernelGGL(k_c_long_keep, dim3((unsigned)lg), dim3(kBlock), 0, s, a, t1.nlong, t1.tab_entries);
     if (hipGetLastError() != hipSuccess) return LM_EDEVICE;
     if (hipMemcpyAsync(cs.h_tot, a.tot, sizeof(CTot), hipMemcpyDeviceToHost, s) != hipSuccess ||
         hipStreamSynchronize(s) != hipSuccess)
@@ -1771,6 +1824,7 @@ lm_status lm_contract(lm_ctx* ctx, const lm_csr* g, const int32_t* mate, const i
   a.lrow_cap = lrow_cap;
   a.dup_limit = kCMaxDup;
   a.identity = 0;
+  a.table_from = kLTable;
   set_ranges(a, P, cs.ranges, S.num_cus);
 
   LMC_HIP(hipEventRecord(S.e0, s));
@@ -1790,16 +1844,56 @@ lm_status lm_contract(lm_ctx* ctx, const lm_csr* g, const int32_t* mate, const i
   const long long nc = t1.nc;
   const long long nl = t1.nlong;
   if (nl > lrow_cap) return LM_EDEVICE;  // cannot happen: the bounds of the rows sum to nnz
-  long long overflow_rows = 0;
+  // sizes and offsets again, with other rows merged through tables
+  auto prep_again = [&](long long table_from) -> lm_status {
+    a.table_from = table_from;
+    launch_long_prep(a, (long long*)cs.lsum.p, s);
+    LMC_HIP(hipGetLastError());
+    LMC_HIP(hipMemcpyAsync(cs.h_tot, a.tot, sizeof(CTot), hipMemcpyDeviceToHost, s));
+    LMC_HIP(hipStreamSynchronize(s));
+    t1 = *cs.h_tot;
+    return LM_OK;
+  };
+  auto reserve_tables = [&]() -> lm_status {
+    LMC_TRY(P.reserve(cs.next, a256(sizeof(int) * (size_t)nnz)));
+    LMC_TRY(P.reserve(cs.table, a256(sizeof(int2) * (size_t)t1.long_slots)));
+    a.next = (int*)cs.next.p;
+    a.table = (int2*)cs.table.p;
+    return LM_OK;
+  };
+  auto launch_tables = [&]() {  // merges the rows with a table
+    const long long lg = std::min<long long>((t1.tab_entries + kBlock * kLI - 1) / (kBlock * kLI), 16384);
+    const long long fill_grid = std::min<long long>((t1.long_slots + kBlock - 1) / kBlock, 8192);
+    hipLaunchKernelGGL(k_c_fill, dim3((unsigned)fill_grid), dim3(kBlock), 0, s, a.table, t1.long_slots);
+    hipLaunchKernelGGL(k_c_long_insert, dim3((unsigned)lg), dim3(kBlock), 0, s, a, nl, t1.tab_entries);
+    hipLaunchKernelGGL(k_c_long_keep, dim3((unsigned)lg), dim3(kBlock), 0, s, a, nl, t1.tab_entries);
+    hipLaunchKernelGGL(k_c_long_cnt, dim3((unsigned)std::min<long long>((nl + kWaves - 1) / kWaves, 4096)), dim3(kBlock),
+                       0, s, a, nl);
+  };
+  auto launch_index = [&]() {
+    hipLaunchKernelGGL(k_c_long_tables, dim3((unsigned)std::min<long long>((nl + kBlock - 1) / kBlock, 4096)),
+                       dim3(kBlock), 0, s, a, nl);
+  };
   if (nl > 0) {
-    const long long np = t1.long_items >> 32, nsm = t1.long_items & 0x7fffffffll, nch = t1.long_chunks;
-    LMC_TRY(P.reserve(cs.ltab, a256(sizeof(int) * (size_t)(nsm + np + 2 * nch))));
+    long long np, nsm, nch;
+    auto reserve_index = [&]() -> lm_status {
+      np = t1.long_items >> 32;
+      nsm = t1.long_items & 0x7fffffffll;
+      nch = t1.long_chunks & (kLTabBit - 1);
+      return P.reserve(cs.ltab, a256(sizeof(int) * (size_t)(nsm + np + 2 * nch)));
+    };
+    if (t1.tab_entries > 0 && (reserve_tables() != LM_OK || reserve_index() != LM_OK)) {
+      // no room for the tables: the parts need none
+      P.release(cs.next);
+      P.release(cs.table);
+      LMC_TRY(prep_again(LLONG_MAX));
+    }
+    LMC_TRY(reserve_index());
     a.srow = (int*)cs.ltab.p;
     a.prow = a.srow + nsm;
     a.crow = a.prow + np;
     a.ccnt = a.crow + nch;
-    hipLaunchKernelGGL(k_c_long_tables, dim3((unsigned)std::min<long long>((nl + kBlock - 1) / kBlock, 4096)),
-                       dim3(kBlock), 0, s, a, nl);
+    launch_index();
     // a workgroup per chunk, part and row: they differ in work, and are
     // handed out as workgroups end
     if (np > 0) hipLaunchKernelGGL(k_c_long_map, dim3((unsigned)nch), dim3(kBlock), 0, s, a);
@@ -1809,26 +1903,20 @@ lm_status lm_contract(lm_ctx* ctx, const lm_csr* g, const int32_t* mate, const i
                          (int)np);
     if (nsm > 0 && !one)
       hipLaunchKernelGGL((k_c_long_group<kBlock, kLSmall>), dim3((unsigned)nsm), dim3(kBlock), 0, s, a, 0);
+    if (t1.tab_entries > 0) launch_tables();
     LMC_HIP(hipGetLastError());
     LMC_HIP(hipMemcpyAsync(cs.h_tot, a.tot, sizeof(CTot), hipMemcpyDeviceToHost, s));
     LMC_HIP(hipStreamSynchronize(s));
     if (cs.h_tot->err & kCErrMate) return LM_EINVAL;
     if (cs.h_tot->err) return LM_EGRAPH;
     if (cs.h_tot->overflow) {  // a bucket outgrew LDS: every long row through per-row tables
-      overflow_rows = nl;
-      LMC_TRY(P.reserve(cs.next, a256(sizeof(int) * (size_t)nnz)));
-      LMC_TRY(P.reserve(cs.table, a256(sizeof(int2) * (size_t)t1.long_slots)));
-      a.next = (int*)cs.next.p;
-      a.table = (int2*)cs.table.p;
-      const long long lg = std::min<long long>((t1.long_entries + kBlock * kLI - 1) / (kBlock * kLI), 16384);
-      const long long cg = std::min<long long>((nl + kBlock - 1) / kBlock, 4096);
-      hipLaunchKernelGGL(k_c_long_clear_cnt, dim3((unsigned)cg), dim3(kBlock), 0, s, a, nl, nch);
-      const long long fill_grid = std::min<long long>((t1.long_slots + kBlock - 1) / kBlock, 8192);
-      hipLaunchKernelGGL(k_c_fill, dim3((unsigned)fill_grid), dim3(kBlock), 0, s, a.table, t1.long_slots);
-      hipLaunchKernelGGL(k_c_long_insert, dim3((unsigned)lg), dim3(kBlock), 0, s, a, nl, t1.long_entries);
-      hipLaunchKernelGGL(k_c_long_keep, dim3((unsigned)lg), dim3(kBlock), 0, s, a, nl, t1.long_entries);
+      LMC_TRY(prep_again(0));
+      LMC_TRY(reserve_tables());
+      launch_index();
+      launch_tables();
     }
   }
+  const long long table_rows = t1.long_chunks / kLTabBit;
   const long long nb_c = (nc + kCBlockV - 1) / kCBlockV;
   if (nb_c > 0) {
     hipLaunchKernelGGL(k_c_deg_count, dim3((unsigned)nb_c), dim3(kBlock), 0, s, a, nc);
@@ -1836,7 +1924,7 @@ lm_status lm_contract(lm_ctx* ctx, const lm_csr* g, const int32_t* mate, const i
     hipLaunchKernelGGL(k_c_deg_write, dim3((unsigned)nb_c), dim3(kBlock), 0, s, a, nc);
   }
   hipLaunchKernelGGL(k_c_copy, dim3((unsigned)a.ranges), dim3(kBlock), 0, s, a);
-  if (nl > 0) hipLaunchKernelGGL(k_c_long_out, dim3((unsigned)t1.long_chunks), dim3(kBlock), 0, s, a);
+  if (nl > 0) hipLaunchKernelGGL(k_c_long_out, dim3((unsigned)(t1.long_chunks & (kLTabBit - 1))), dim3(kBlock), 0, s, a);
   LMC_HIP(hipGetLastError());
   LMC_HIP(hipEventRecord(S.e1, s));
   LMC_HIP(hipMemcpyAsync(cs.h_tot, a.tot, sizeof(CTot), hipMemcpyDeviceToHost, s));
@@ -1864,7 +1952,7 @@ lm_status lm_contract(lm_ctx* ctx, const lm_csr* g, const int32_t* mate, const i
                     (vwgt ? 8.0 * n : 0.0) + (out->vwgt ? 8.0 * nc : 0.0);
     st->long_rows = nl;
     st->long_entries = t1.long_entries;
-    st->table_rows = overflow_rows;
+    st->table_rows = table_rows;
   }
   return LM_OK;
 }
