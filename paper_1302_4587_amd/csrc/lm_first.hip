@@ -808,15 +808,22 @@ int first_rows_lg(long long nnz, long long n) {
   return lg;
 }
 
+// The timing events span both kernels (one first argmax).
 hipError_t launch_first_rows(const FirstRowsArgs& a, int num_cus, hipStream_t s, hipEvent_t* ev) {
   const long long blocks = (((long long)a.n + 63) / 64 + kWaves - 1) / kWaves;
   const int grid = (int)std::max<long long>(1, std::min<long long>(blocks, (long long)num_cus * 64));
-  if (ev) hipExtLaunchKernelGGL(k_first_rows, dim3(grid), dim3(kBlock), 0, s, ev[0], ev[1], 0, a);
-  else hipLaunchKernelGGL(k_first_rows, dim3(grid), dim3(kBlock), 0, s, a);
+  const bool more = a.nnz > 0;  // (no entry: nothing is listed)
+  if (ev)
+    hipExtLaunchKernelGGL(k_first_rows, dim3(grid), dim3(kBlock), 0, s, ev[0], more ? (hipEvent_t) nullptr : ev[1], 0, a);
+  else
+    hipLaunchKernelGGL(k_first_rows, dim3(grid), dim3(kBlock), 0, s, a);
   const hipError_t e = hipGetLastError();
-  if (e != hipSuccess || a.nnz == 0) return e;  // (no entry: nothing is listed)
-  hipLaunchKernelGGL(k_first_long, dim3((unsigned)std::min<long long>(2 * num_cus, (a.nnz + 8191) / 8192)),
-                     dim3(kHubLanes), 0, s, a);
+  if (e != hipSuccess || !more) return e;
+  const unsigned gl = (unsigned)std::min<long long>(2 * num_cus, (a.nnz + 8191) / 8192);
+  if (ev)
+    hipExtLaunchKernelGGL(k_first_long, dim3(gl), dim3(kHubLanes), 0, s, (hipEvent_t) nullptr, ev[1], 0, a);
+  else
+    hipLaunchKernelGGL(k_first_long, dim3(gl), dim3(kHubLanes), 0, s, a);
   return hipGetLastError();
 }
 
