@@ -222,24 +222,25 @@ __global__ __launch_bounds__(kBlock, 4) void k_compact_rows(StreamArgs a, int lg
     }
     __syncthreads();
     unsigned md = 0u, loaded = 0u;
-    auto offs = [&](int v0, int& o0, int& o1, unsigned& st) {
-      const int v = v0 + lane;
-      o0 = v < ve ? (int)a.in.csr_rp[v] : 0;
-      o1 = v < ve ? (int)a.in.csr_rp[v + 1] : 0;
-      st = v < ve ? a.c.state[v] : 1u;
+    auto offs = [&](unsigned v0, int& o0, int& o1, unsigned& st) {
+      const unsigned v = v0 + (unsigned)lane;
+      const bool in = v < (unsigned)ve;
+      o0 = in ? (int)a.in.csr_rp[v] : 0;
+      o1 = in ? (int)a.in.csr_rp[v + 1u] : 0;
+      st = in ? a.c.state[v] : 1u;
     };
     int n0 = 0, n1 = 0;
     unsigned ns = 1u;
-    if (vb + wv * 64 < ve) offs(vb + wv * 64, n0, n1, ns);
-    int v0 = vb + wv * 64;
+    unsigned v0 = (unsigned)vb + (unsigned)wv * 64u;  // (may pass 2^31)
+    if (v0 < (unsigned)ve) offs(v0, n0, n1, ns);
     unsigned head = 0u, tail = 0u;
     for (;;) {
-      while (tail - head < (unsigned)cnt && v0 < ve) {
-        const int v = v0 + lane, off = n0;
+      while (tail - head < (unsigned)cnt && v0 < (unsigned)ve) {
+        const int v = (int)(v0 + (unsigned)lane), off = n0;
         int len = n1 - n0;
         const bool matched = ns != 0u;
         v0 += kBlock;
-        if (v0 < ve) offs(v0, n0, n1, ns);  // the wave's next rows
+        if (v0 < (unsigned)ve) offs(v0, n0, n1, ns);  // the wave's next rows
         md += matched ? (unsigned)len : 0u;
         loaded += matched ? 0u : (unsigned)len;
         if (matched) len = 0;

@@ -92,10 +92,14 @@ __device__ void compact_unw_range(const StreamArgs& a, const Ctl& ctl, int b, Un
     const bool cut_left = uni((int)rp[v0]) < E0;
     row0 = v0 + b;
     int R0 = v0 & ~63;  // the window: lane i holds row R0 + i
-    auto end_of = [&](int r) { return (int)rp[min(r + lane + 1, n)]; };
-    auto state_of = [&](int r) { return r + lane < n ? (unsigned)a.c.state[r + lane] : 1u; };
-    int ce = end_of(R0), cs;
-    unsigned st = state_of(R0);
+    // (of the window i rows on)
+    auto end_of = [&](int r, unsigned i) { return (int)rp[row_or_end(r, i + (unsigned)lane + 1u, n)]; };
+    auto state_of = [&](int r, unsigned i) {
+      const unsigned v = row_or_end(r, i + (unsigned)lane, n);
+      return v < (unsigned)n ? (unsigned)a.c.state[v] : 1u;
+    };
+    int ce = end_of(R0, 0u), cs;
+    unsigned st = state_of(R0, 0u);
     unsigned long long live;
     auto enter = [&](int first) {  // (first: where the window's first row starts)
       cs = (int)dpp_wave_shr1((unsigned)ce, (unsigned)first);
@@ -104,8 +108,8 @@ __device__ void compact_unw_range(const StreamArgs& a, const Ctl& ctl, int b, Un
       loaded += lv ? (unsigned)max(min(ce, E1) - max(cs, E0), 0) : 0u;
     };
     enter(uni((int)rp[R0]));
-    int ne = end_of(R0 + 64);  // the next window
-    unsigned ns = state_of(R0 + 64);
+    int ne = end_of(R0, 64u);  // the next window
+    unsigned ns = state_of(R0, 64u);
     int pos = E0;
     // pos to the first entry of a live row from pos on; false: none in the range
     auto seek = [&]() -> bool {
@@ -116,13 +120,13 @@ __device__ void compact_unw_range(const StreamArgs& a, const Ctl& ctl, int b, Un
           return pos < E1;
         }
         const int last = __builtin_amdgcn_readlane(ce, 63);
-        if (R0 + 64 >= n || last >= E1) return false;
+        if (row_or_end(R0, 64u, n) == (unsigned)n || last >= E1) return false;
         R0 += 64;
         ce = ne;
         st = ns;
         enter(last);
-        ne = end_of(R0 + 64);
-        ns = state_of(R0 + 64);
+        ne = end_of(R0, 64u);
+        ns = state_of(R0, 64u);
       }
     };
     int orow = -1, ostart = E0;   // the row open at the end of the previous step, its first kept entry

@@ -43,6 +43,11 @@ constexpr int kHeadBit = (int)0x80000000u;
 constexpr int kMatchedBit = 0x40000000;
 constexpr int kGraphMask = 0x3fffffff;
 
+// Row r + i of n rows (n < 2^31), n past the last: r + i may pass 2^31.
+__host__ __device__ constexpr unsigned row_or_end(int r, unsigned i, int n) {
+  return (unsigned)r + i < (unsigned)n ? (unsigned)r + i : (unsigned)n;
+}
+
 struct Run {
   int row_begin;   // first piece of the run in the piece buffer
   int row_count;   // pieces

@@ -344,11 +344,11 @@ __global__ __launch_bounds__(kTailBlock) void k_tail(TailArgs a) {
   // every nb-th kChunk vertices (8 offsets are a line; neighbours in a skewed
   // graph's order go to other workgroups).
   const long long P = csr ? a.n : ctl.pieces;
-  int k0 = (int)(P * b / nb), k1 = (int)(P * (b + 1) / nb);
+  int k0 = (int)(P * b / nb), kc = (int)(P * (b + 1) / nb) - k0;  // (k0 + kc may be 2^31)
   if (csr) {
     const int chunks = (int)((P + kChunk - 1) / kChunk), q = chunks / nb, r = chunks % nb;
     k0 = kChunk * (q * b + min(b, r));
-    k1 = k0 + kChunk * (q + (b < r ? 1 : 0));
+    kc = kChunk * (q + (b < r ? 1 : 0));
   }
   if (tid == 0) {
     sm.cnt_s = sm.cnt_l = 0;
@@ -374,12 +374,12 @@ __global__ __launch_bounds__(kTailBlock) void k_tail(TailArgs a) {
   if (csr) {  // rows and first candidates from the input
     const unsigned long long Sd = cand_seed(c.gseed[0], c.renew, 1);
     unsigned err = b == 0 && tid == 0 && (a.csr_rp[0] != 0 || a.csr_rp[c.n] != a.nnz) ? (unsigned)kErrRowPtr : 0u;
-    for (int x0 = k0 + (tid & ~63); x0 < k1; x0 += kTailBlock) {
-      const int x = x0 + lane - k0;
+    for (int x0 = tid & ~63; x0 < kc; x0 += kTailBlock) {
+      const int x = x0 + lane;
       const long long v = ((long long)(x / kChunk) * nb + b) * kChunk + x % kChunk;
       int4 r = make_int4(0, 0, 0, 0);
       bool es = false, el = false;
-      if (x < k1 - k0 && v < P) {
+      if (x < kc && v < P) {
         const long long e0 = a.csr_rp[v], d = a.csr_rp[v + 1] - e0;
         if (d < 0 || e0 < 0 || e0 + d > a.nnz) err |= kErrRowPtr;
         if (d > 0x7fff0000LL) err |= kErrDegree;
@@ -392,14 +392,14 @@ __global__ __launch_bounds__(kTailBlock) void k_tail(TailArgs a) {
         c.mate[v] = -1;
         if (!el) c.C[v] = best.u;
       }
-      place_rows(es, el, r, TA, k0, k1 - k0, sm);
+      place_rows(es, el, r, TA, k0, kc, sm);
     }
     if (err) atomicOr(&tot->err, err);
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
     const int nl = sm.cnt_l;
     for (int j = wv; j < nl; j += kTW) {
-      const int4 r = TA[k1 - 1 - j];
+      const int4 r = TA[k0 + (kc - 1 - j)];
       if (r.z > kHubRow) {  // left to the grid
         unsigned h = 0;
         if (lane == 0) h = atomicAdd(&tc->hubs, 1u);
@@ -430,11 +430,11 @@ __global__ __launch_bounds__(kTailBlock) void k_tail(TailArgs a) {
         }
       }
     }
-    for (int q0 = k0 + (tid & ~63); q0 < k1; q0 += kTailBlock) {
-      const int k = q0 + lane;
+    for (int x0 = tid & ~63; x0 < kc; x0 += kTailBlock) {
+      const int k = k0 + min(x0 + lane, kc - 1);
       int4 r = make_int4(0, 0, 0, 0);
       bool es = false, el = false;
-      if (k < k1) {
+      if (x0 + lane < kc) {
         int lo = 0, hi = ctl.nruns;  // run of piece k: largest lo with rp[lo] <= k
         while (hi - lo > 1) {
           const int mid = (lo + hi) >> 1;
@@ -464,12 +464,12 @@ __global__ __launch_bounds__(kTailBlock) void k_tail(TailArgs a) {
         }
       }
       if (c.graphs != 1 && (es || el)) c.mate[r.x] = c.C[r.x] - c.gbase[r.w];  // (cur below)
-      place_rows(es, el, r, TA, k0, k1 - k0, sm);
+      place_rows(es, el, r, TA, k0, kc, sm);
     }
   }
   unsigned g = 1;
   const int cnt_s = sm.cnt_s, cnt_l = sm.cnt_l;
-  if (!exchange(tc, tc->seg[g & 1], k0, k1 - k0, nb, g, false, limit, tot, sm)) return;
+  if (!exchange(tc, tc->seg[g & 1], k0, kc, nb, g, false, limit, tot, sm)) return;
   if (csr && ld_u32(&tot->err)) return;  // (the same word everywhere: nothing is added before the next exchange)
   const int nhub = csr ? min((int)ld_u32(&tc->hubs), kTailHubs) : 0;
   if (nhub > 0) {  // every workgroup a slice of each, then, behind an exchange, the best of the slices
@@ -494,7 +494,7 @@ __global__ __launch_bounds__(kTailBlock) void k_tail(TailArgs a) {
       sm.cnt_l = cnt_l;
     }
     ++g;
-    if (!exchange(tc, tc->seg[g & 1], k0, k1 - k0, nb, g, false, limit, tot, sm)) return;
+    if (!exchange(tc, tc->seg[g & 1], k0, kc, nb, g, false, limit, tot, sm)) return;
     for (int h = wv; h < nhub; h += kTW) {  // (every workgroup stores the same)
       const Key* p = part + h * kTailMaxBlocks;
       const Key x0 = lane < nb ? p[lane] : key_ident(), x1 = lane + 64 < nb ? p[lane + 64] : key_ident();

@@ -36,3 +36,11 @@ def test_phases_past_the_log_have_no_record(tmp_path):
     recs, n = _values(tmp_path, "solo_log_records(kSoloMaxN)", "kSoloMaxN")
     at = (1, 2, recs - 1, recs, recs + 1, n - 1, n)
     assert _values(tmp_path, *(f"solo_log_slot({t}, {recs})" for t in at)) == [t - 1 if t <= recs else -1 for t in at]
+
+
+def test_row_numbers_near_the_limit(tmp_path):
+    """Rows past the last one, of up to 2^31 - 1, are the end and never wrap below zero."""
+    n = 2**31 - 1
+    at = [(0, 0, n), (0, 64, 64), (0, 63, 64), (n - 63, 62, n), (n - 63, 63, n), (n - 63, 64, n), (n - 63, 192, n), (n - 1, 64, n), (5, 700, 6)]
+    got = _values(tmp_path, *(f"row_or_end({r}, {i}u, {m})" for r, i, m in at))
+    assert got == [min(r + i, m) for r, i, m in at]
