@@ -223,7 +223,7 @@ typedef struct {
   int32_t tail_entries;    /* 0..2^30: the phases from the first live set of at most this many
                               entries on run in one persistent launch (device-controlled
                               solves: LM_GRAPH, LM_ASYNC); a host-polled solve hands over one
-                              phase after a live set of at most 4x this many (it keeps one phase
+                              phase after a live set of at most 2x this many (it keeps one phase
                               queued ahead). 0: host-polled solves never hand over (default
                               2^20), and no graph is solved by one workgroup */
 } lm_tuning;

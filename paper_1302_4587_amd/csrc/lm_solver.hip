@@ -660,7 +660,11 @@ lm_status Solver::run(const Problem& p, const Work& wk, hipStream_t s, uint32_t 
   // Once R_rc is small the phases already queued run and the tail kernel
   // takes the rest.
   const int ahead = std::max(1, std::min(tun.phases_per_sync, kMirrorSlots / 2));
-  const long long host_tail = tun.tail_entries > 0 ? 4ll * tun.tail_entries : -1;
+  // Twice tail_entries: the tail looks two candidates up per entry where the phases
+  // read one matched flag, and over 4 M entries its phases take longer (a grid of 1 M
+  // vertices whose weights rise across it, a phase for every few vertices: handed over
+  // at four times 184 ms, at twice 102; R-MAT 20 and 24 and RGG 2^24 the same).
+  const long long host_tail = tun.tail_entries > 0 ? 2ll * tun.tail_entries : -1;
   // Reads a record tagged for this solve and live set `idx` (idx < 0: the tail
   // kernel's final record, any live set). The tag is read before and after the
   // copy, so a record being rewritten is never taken.
