@@ -137,7 +137,8 @@ typedef struct {
 #define LM_K_MUTUAL 2   /* mutual-candidate check and matched marking */
 #define LM_K_COMPACT 3  /* edge compaction fused with the next argmax */
 #define LM_K_PLAN 4     /* single-workgroup stitching of cut rows and run-table scan */
-#define LM_K_TAIL 5     /* persistent launch running every phase from a small live set on */
+#define LM_K_TAIL 5     /* persistent launch running every phase from a small live set on, or of
+                           whole graphs, a workgroup each */
 #define LM_K_KINDS 6
 
 typedef struct {

@@ -270,10 +270,11 @@ class Context:
     def match_batch(self, vtx_off, row_ptr, col, w, seeds=None, seed0: int = 1, mate=None, *, check_graph=False,
                     profile=False, stream=None, log_cap: int = 4096, want_graph_phases=True, hip_graph=True,
                     weight_sum=False, asynchronous=False, renew_keys=False):
-        """Solves a batch (disjoint union, local ids) in one captured HIP graph
-        launch unless hip_graph=False or profile=True. Returns (mate, MatchStats,
-        graph_phases); with asynchronous=True (LM_ASYNC) (mate, None, None) at
-        once."""
+        """Solves a batch (disjoint union, local ids): one workgroup per graph where
+        every graph has at most 65536 vertices and none very many entries, else by
+        the phase kernels, in one captured HIP graph launch unless hip_graph=False
+        or profile=True. Returns (mate, MatchStats, graph_phases); with
+        asynchronous=True (LM_ASYNC) (mate, None, None) at once."""
         vo = np.ascontiguousarray(np.asarray(vtx_off, dtype=np.int64))
         G = len(vo) - 1
         N = int(vo[-1])

@@ -14,10 +14,10 @@
 // vertices into ranges of equal cost. (2) Coarse rows by their bound deg(a) +
 // deg(b): up to kWS entries, several rows at once in a wave's tile; up to kCS,
 // a wave each; longer ones, a workgroup each or several (3). All find the
-// entries of one coarse neighbour in a hash set in LDS; the first of them in
-// row order keeps it with the sum, and the kept entries are written compacted
-// at the start of their fine row part (longer rows: in place, the others
-// marked as dropped). (4) A scan over the coarse rows gives their offsets and
+// entries of one coarse neighbour in a hash set in LDS (rows of more than kLTable
+// entries in device memory); the first of them in row order keeps it with the sum,
+// and the kept entries are written compacted at the start of their fine row part
+// (longer rows: in place, the others marked as dropped). (4) A scan over the coarse rows gives their offsets and
 // the kept entries are copied out in order. The fine graph's entries are read
 // once; cmap is gathered once per entry, which is what bounds the skewed
 // graphs (R-MAT scale 24: about 100 G gathers a second).
@@ -385,7 +385,6 @@ struct WaveSmem {
   int shead[2 * kWT];  // last tile position inserted into the slot's list
   short enext[kWT];
   short eslot[kWT];
-  unsigned char erow[kWT];
   int st[65];  // wave-local start of each lane's row; st[64] = the wave's total
   int ra[64], rb[64], rc[64], rdega[64], rut[64];
   int rrk[64][2];  // kept entries of the tile before the row's a part and b part
@@ -492,7 +491,6 @@ __global__ __launch_bounds__(kBlock) void k_c_group_wave(CArgs a) {
           const bool side = off >= sm.rdega[r];
           rr[i] = r;
           kr[i] = side ? sm.rkb[r] + (off - sm.rdega[r]) : sm.rka[r] + off;
-          sm.erow[q] = (unsigned char)r;
         }
       }
 #pragma unroll

@@ -633,8 +633,8 @@ hipError_t launch_first_csr(const StreamArgs& a, int grid, hipStream_t s, hipEve
 // for k_first_long, which gives each a wave, or a workgroup above kRHub entries
 // (skewed graphs have their long rows next to each other: a wave that took those
 // of its 64 rows one after the other made R-MAT 14 50 us slower). No row is cut,
-// nothing waits on a workgroup barrier. Bound by HBM: RGG 2^24 415 us, 3.6 TB/s (in tiles with
-// workgroup barriers 487 us), RGG of 1 M vertices 44 us (69).
+// nothing waits on a workgroup barrier. Bound by HBM: RGG 2^24 347 us, 4.5 TB/s (in tiles with
+// workgroup barriers 487 us), RGG of 1 M vertices 22 us (69).
 constexpr int kRI = 8;
 constexpr int kRHub = 2048;
 constexpr int kRFew = 2;  // long rows a wave takes itself rather than list them (two atomics on shared words)

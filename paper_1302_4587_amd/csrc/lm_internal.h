@@ -282,13 +282,13 @@ struct InitArgs {
 };
 
 // Device-side tail of the phase loop (k_tail): one persistent launch runs
-// every phase from the current live set R_c on, with software grid barriers
-// between the mutual check and the compaction of each phase. Its live rows are
-// records {v, entry offset, live length, graph}. Workgroup b writes the rows it
-// keeps into a segment of its own of the next row list (rows of at most
-// kTailShort live entries from the segment's front, one lane each next phase;
-// longer ones from its back, one wave each), and its counts into a table that
-// every workgroup reads after the barrier: no counter is shared. A row keeps
+// every phase from the current live set R_c on, a pass over the live rows and one
+// exchange between the workgroups each. Its live rows are records {v, entry
+// offset, live length, graph}. Workgroup b writes the rows it keeps into a segment
+// of its own of the next row list (rows of at most kTailShort live entries from
+// the segment's front, one lane each next phase; longer ones from its back, one
+// wave each), and its counts into a table that every workgroup reads in the
+// exchange: no counter is shared. A row keeps
 // its entry offset for the rest of the solve: phase t reads its entries from
 // one entry buffer and writes the survivors to the same offset of the other.
 constexpr int kTailBlock = 1024;
@@ -321,7 +321,6 @@ struct TailArgs {
   const long long* epre[2];
   const int* rpre[2];
   int4* rows[2];       // R_c's piece records; afterwards the tail's row lists
-  int row_cap;         // records per row buffer
   int* ecol[2];
   float* ew[2];        // nullptr: unweighted
   // the tail is the whole solve of one graph: it starts from the input CSR (rows

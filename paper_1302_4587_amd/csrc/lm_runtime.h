@@ -17,7 +17,6 @@
 namespace lm {
 
 constexpr int kLogCap = 1 << 16;  // device phase records kept per solve
-constexpr int kGraphPhases = 12;  // phases in the captured graph (LM_GRAPH)
 constexpr int kWeightSumMaxGrid = 1024;  // workgroups of the matched-weight sum (LM_WEIGHT_SUM)
 
 struct DevBuf {

@@ -25,7 +25,7 @@
 // CU; a batch, HBM: the first argmax of a large graph reads 4.1 TB/s over the
 // chip, the first compaction, whose writes and LDS lookups come on top, 3 TB/s.
 // Measured against the phase kernels with the grid-wide tail (whole calls):
-// ER 300 / 1200 122 -> 47 us, ER 4096 / 32768 235 -> 104 us, 64 unweighted
+// ER 300 / 1200 122 -> 47 us, ER 2000 / 16000 203 -> 70 us, 64 unweighted
 // graphs of 2^8 to 2^12 vertices 0.79 -> 0.21 ms, 4096 weighted graphs of 2^8
 // to 2^16 vertices 12.9 -> 5.2 ms. Entries a lane takes per step and waves per
 // SIMD: 8 and 4 for the largest graphs (LDS holds one) and for one graph (4 and

@@ -404,8 +404,8 @@ lm_status Solver::run(const Problem& p, const Work& wk, hipStream_t s, uint32_t 
   // One graph that the tail kernel takes from the first phase on needs nothing
   // before it: it reads R_1 and finds the first candidates itself (with k_init,
   // k_plan, the first argmax and its listed rows, and a row list behind them:
-  // RGG with 60 K vertices 130 us a call, now 123; ER with 20 K vertices of degree
-  // 16 200 -> 158; R-MAT 14 221 -> 178).
+  // RGG with 60 K vertices 130 us a call, now 124; ER with 20 K vertices of degree
+  // 16 200 -> 153; R-MAT 14 221 -> 145).
   const bool direct = csr1 && (dev_ctl ? p.nnz <= tail_at : tun.tail_entries > 0 && p.nnz <= tun.tail_entries);
   auto enqueue_prologue = [&]() -> hipError_t {
     if (!p.after_solo) ENQ(launch_zero(dctl, 2, dtot, s, wk.tail));
@@ -558,7 +558,6 @@ lm_status Solver::run(const Problem& p, const Work& wk, hipStream_t s, uint32_t 
       ta.ecol[i] = wk.ecol[i];
       ta.ew[i] = unweighted ? nullptr : wk.ew[i];
     }
-    ta.row_cap = (int)(p.N + 2 * kMaxBlocks + 16);
     ta.csr_rp = direct ? p.row_ptr : nullptr;
     ta.n = p.N;
     ta.nnz = p.nnz;
@@ -574,8 +573,9 @@ lm_status Solver::run(const Problem& p, const Work& wk, hipStream_t s, uint32_t 
     // in 237 us against 211), but at most a quarter of the resident capacity up
     // to 2^20 entries: solves of several threads run on up to four hardware
     // queues, and tails that are each resident in part only would wait for each
-    // other. (Half of it: R-MAT 14 150 us against 178, ER with 20 K vertices 154
-    // against 158, RGG with 60 K 119 against 124.)
+    // other. (What that costs, 127 workgroups against 63: ER with 60 K vertices and 960 K
+    // entries 195 us against 255, with 20 K 145 against 153; R-MAT 15 200 and 209, R-MAT 14
+    // 145 and 143; RGG with 60 K 112 and 116.)
     // From the CSR the tail also walks every vertex: a workgroup per 1024 of them
     // at least (2^22 vertices with 8 K entries by 2 workgroups 1461 us, by 64 88; 2^20
     // 525 and 60), and one per 1024 entries, since all phases are its own (per 4096: ER
