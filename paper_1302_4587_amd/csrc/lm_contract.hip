@@ -113,11 +113,11 @@ struct CArgs {
   // (While a long row is merged, aux links the fine edges of one coarse edge.)
   int* dmap;
   float* aux;
-  int* next;  // per fine entry of a long row: the previous entry of its table slot's list (table path)
+  int* next;  // per flat entry of the rows with a table: the previous one of its slot's list
   LongRow* lrows;
   long long lrow_cap;
   long long table_from;  // long rows of more entries are merged through tables
-  int2* table;  // (key, list head) per slot of the tables
+  int2* table;  // (key, list head: a flat entry) per slot of the tables
   int* srow;   // long row of each row of at most kLSmall buckets
   int* prow;   // long row of each part
   int* crow;   // long row of each chunk
@@ -1130,7 +1130,8 @@ __global__ __launch_bounds__(kBlock) void k_c_long_insert(CArgs a, long long nl,
         if (old == -1 || old == D[j]) break;
         h = (h + 1) & mask;
       }
-      a.next[at[j].k] = atomicExch(&tb[h].y, (int)at[j].k);
+      const int i = (int)(L.eoff + at[j].off);
+      a.next[i] = atomicExch(&tb[h].y, i);
     }
   }
   if (err) atomicOr(&a.tot->err, err);
@@ -1194,7 +1195,7 @@ __global__ __launch_bounds__(kBlock) void k_c_long_keep(CArgs a, long long nl, l
       const LongRow& L = a.lrows[at[j].r];
       const long long ka = a.rp[L.a];
       const long long kb = L.b >= 0 ? a.rp[L.b] : 0;
-      // the group's entries; row order is a's part, then b's part
+      // the row positions of the group's entries
       int lst[kCMaxDup + 1];
       int nlst = 0;
       int p = slot[j].y;
@@ -1203,11 +1204,9 @@ __global__ __launch_bounds__(kBlock) void k_c_long_keep(CArgs a, long long nl, l
 #pragma unroll
       for (int t = 0; t <= kCMaxDup; ++t) {  // static indices: at most five nodes matter
         if (p < 0) continue;
-        lst[t] = p;
+        lst[t] = (int)(p - L.eoff);
         nlst = t + 1;
-        const bool pa = (long long)p >= ka && (long long)p < ka + L.dega;
-        const long long pos_p = pa ? p - ka : L.dega + (p - kb);
-        first = first && pos_p >= at[j].off;
+        first = first && lst[t] >= at[j].off;
         p = pn;
         if (p >= 0 && t < kCMaxDup) pn = a.next[p];
       }
@@ -1226,12 +1225,11 @@ __global__ __launch_bounds__(kBlock) void k_c_long_keep(CArgs a, long long nl, l
           ord[t] = ~0ull;
           wv[t] = 0.f;
           if (t >= nlst) continue;
-          const int pp = lst[t];
-          const bool pa = (long long)pp >= ka && (long long)pp < ka + L.dega;
-          const int sp = pa ? L.a : L.b;
-          const int xp = pp == at[j].k ? x[j] : a.col[pp];
-          ord[t] = edge_order(sp, xp);
-          wv[t] = pp == at[j].k ? wself[j] : (a.w ? a.w[pp] : 1.0f);
+          const bool pa = lst[t] < L.dega, self = lst[t] == at[j].off;
+          const long long pp = pa ? ka + lst[t] : kb + (lst[t] - L.dega);
+          const int xp = self ? x[j] : a.col[pp];
+          ord[t] = edge_order(pa ? L.a : L.b, xp);
+          wv[t] = self ? wself[j] : (a.w ? a.w[pp] : 1.0f);
         }
         sum = group_sum(ord, wv, nlst);
       }
@@ -1691,7 +1689,7 @@ lm_status check_row_duplicates(Solver& S, int64_t n, int64_t nnz, const long lon
   if (t1.err) return LM_EGRAPH;
   if (t1.nlong > 0) {
     if (t1.nlong > lrow_cap) return LM_EDEVICE;
-    if ((rs = P.reserve(cs.next, a256(sizeof(int) * (size_t)nnz))) != LM_OK) return rs;
+    if ((rs = P.reserve(cs.next, a256(sizeof(int) * (size_t)t1.tab_entries))) != LM_OK) return rs;
     if ((rs = P.reserve(cs.table, a256(sizeof(int2) * (size_t)t1.long_slots))) != LM_OK) return rs;
     a.next = (int*)cs.next.p;
     a.table = (int2*)cs.table.p;
@@ -1868,7 +1866,7 @@ lm_status lm_contract(lm_ctx* ctx, const lm_csr* g, const int32_t* mate, const i
     return LM_OK;
   };
   auto reserve_tables = [&]() -> lm_status {
-    LMC_TRY(P.reserve(cs.next, a256(sizeof(int) * (size_t)nnz)));
+    LMC_TRY(P.reserve(cs.next, a256(sizeof(int) * (size_t)t1.tab_entries)));
     LMC_TRY(P.reserve(cs.table, a256(sizeof(int2) * (size_t)t1.long_slots)));
     a.next = (int*)cs.next.p;
     a.table = (int2*)cs.table.p;
