@@ -441,7 +441,7 @@ def main():
 
 def bench_batch(ctx, dev, replays, with_cpu):
     """4096 random graphs, n log-uniform in [2^8, 2^16], avg degree U[4,32],
-    uniform weights: one batched solve (one captured HIP graph) timed over
+    uniform weights: one batched solve timed over
     `replays` replays, against a loop of single solves over the same graphs
     on the same GPU. Every graph's mate is compared with the oracle (which is
     timed on one core, summed over the graphs, and on all host cores)."""
