@@ -559,7 +559,8 @@ __global__ __launch_bounds__(LANES, WPS) void k_solo(SoloArgs a) {
         if (a.acc) {
           const int at = solo_log_slot(t, a.acc_n);
           if (at >= 0) {
-            unsigned* rec = reinterpret_cast<unsigned*>(a.acc + at);
+            unsigned* rec =
+                reinterpret_cast<unsigned*>(t < kSoloHot ? a.hot + (blockIdx.x % kSoloCopies) * kSoloHot + t : a.acc + at);
             atomicAdd(rec + 0, L);
             atomicAdd(rec + 1, (unsigned)V);
             atomicAdd(rec + 2, (unsigned)c.mv / 2u);
@@ -595,8 +596,9 @@ __global__ __launch_bounds__(LANES, WPS) void k_solo(SoloArgs a) {
   if (a.order) {
     if (tid == 0) {
       if (fail) atomicOr(&a.totals->err, fail);
-      atomicMax(&a.totals->last_nonempty, t - 1);
-      atomicAdd(&a.totals->matched, matched);
+      uint4* head = a.hot + (blockIdx.x % kSoloCopies) * kSoloHot;
+      atomicAdd(reinterpret_cast<unsigned long long*>(head), matched);
+      atomicMax(reinterpret_cast<int*>(head) + 2, t - 1);
       if (a.gphase) a.gphase[gi] = t - 1;
     }
   } else {
@@ -624,6 +626,8 @@ __global__ __launch_bounds__(1024) void k_solo_order(SoloOrder a) {
     const int stride = ((int)gridDim.x - 1) * 1024;
     for (int i = ((int)blockIdx.x - 1) * 1024 + (int)threadIdx.x; i < a.acc_n; i += stride)
       a.acc[i] = make_uint4(0u, 0u, 0u, 0u);
+    for (int i = ((int)blockIdx.x - 1) * 1024 + (int)threadIdx.x; i < kSoloCopies * kSoloHot; i += stride)
+      a.hot[i] = make_uint4(0u, 0u, 0u, 0u);
     return;
   }
   __shared__ int hist[kSoloClasses * kSoloBins];
@@ -631,11 +635,7 @@ __global__ __launch_bounds__(1024) void k_solo_order(SoloOrder a) {
   const int tid = threadIdx.x;
   if (tid == 0) {
     large = 0;
-    if (a.clear) {
-      a.totals->err = 0;
-      a.totals->last_nonempty = 0;
-      a.totals->matched = 0;
-    }
+    if (a.clear) a.totals->err = 0;
   }
   for (int i = tid; i < kSoloClasses * kSoloBins; i += 1024) hist[i] = 0;
   __syncthreads();
@@ -680,16 +680,43 @@ __global__ __launch_bounds__(1024) void k_solo_order(SoloOrder a) {
 
 // The phase log of a batch from its sums, and the final record.
 __global__ __launch_bounds__(1024) void k_solo_fin(SoloArgs a) {
-  const int phases = a.totals->last_nonempty;
-  for (int i = threadIdx.x; i < phases && i < a.log_cap; i += 1024) {
+  __shared__ unsigned sum[4 * kSoloHot];
+  __shared__ unsigned long long matched;
+  __shared__ int phases;
+  const int tid = threadIdx.x;
+  if (tid < 4 * kSoloHot) sum[tid] = 0u;
+  if (tid == 0) {
+    matched = 0ull;
+    phases = 0;
+  }
+  __syncthreads();
+  for (int i = tid; i < kSoloCopies * kSoloHot; i += 1024) {
+    const uint4 r = a.hot[i];
+    unsigned* rec = sum + 4 * (i % kSoloHot);
+    if (i % kSoloHot == 0) {
+      atomicAdd(&matched, ((unsigned long long)r.y << 32) | r.x);
+      atomicMax(&phases, (int)r.z);
+    } else {
+      atomicAdd(rec + 0, r.x);
+      atomicAdd(rec + 1, r.y);
+      atomicAdd(rec + 2, r.z);
+      atomicAdd(rec + 3, r.w);
+    }
+  }
+  __syncthreads();
+  for (int i = tid; i < phases && i < a.log_cap; i += 1024) {
     const int at = solo_log_slot(i + 1, a.acc_n);
-    const uint4 r = at >= 0 ? a.acc[at] : make_uint4(0u, 0u, 0u, 0u);
+    uint4 r = make_uint4(0u, 0u, 0u, 0u);
+    if (at >= 0) {
+      if (i + 1 < kSoloHot) r = make_uint4(sum[4 * i + 4], sum[4 * i + 5], sum[4 * i + 6], sum[4 * i + 7]);
+      else r = a.acc[at];
+    }
     a.log[i] = LogRec{(long long)r.x, (long long)r.y, (long long)r.z, (long long)r.w};
   }
   __syncthreads();
   if (threadIdx.x == 0) {
     const unsigned declined = a.totals->tail_from != kSoloTook ? (unsigned)kErrDeclined : 0u;
-    solo_record(a, a.totals->err | declined, phases + 1, a.totals->matched, 0ull);
+    solo_record(a, a.totals->err | declined, phases + 1, matched, 0ull);
   }
 }
 
@@ -843,6 +870,7 @@ lm_status Solver::run_solo(const Problem& p, const Work& wk, const int64_t* vtx_
     o.order = wk.C;  // (candidates stay in LDS here)
     o.acc = reinterpret_cast<uint4*>(wk.parts);
     o.acc_n = (int)solo_log_records(mx);
+    o.hot = reinterpret_cast<uint4*>(wk.bstat);
     o.gphase = p.gphase;
     o.totals = wk.totals;
     o.clear = check ? 0 : 1;
@@ -853,6 +881,7 @@ lm_status Solver::run_solo(const Problem& p, const Work& wk, const int64_t* vtx_
     a.gseed = wk.gseed;
     a.acc = o.acc;
     a.acc_n = o.acc_n;
+    a.hot = o.hot;
     // The largest graphs take a CU each and end one by one; the others run
     // beside them on a second stream (the smallest first: their LDS fits next
     // to a large graph's).
