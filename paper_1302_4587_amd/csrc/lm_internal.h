@@ -369,6 +369,15 @@ inline long long solo_entry_limit(long long N, long long T, bool unweighted) {
   return unweighted ? x - x / 5 : x;
 }
 
+// Graphs up to which a batch of N vertices is solved this way. A workgroup for a
+// graph of a few vertices costs the chip about 25 ns, one of hundreds 40 ns; the phase
+// kernels know no graphs and take 90 us per million vertices. Measured (us, one workgroup
+// each / phase kernels; weighted): graphs of 2^4 to 2^6 vertices 12000 329 / 443,
+// 16000 423 / 433, 24000 627 / 472, 64000 1626 / 675; of 2^6 to 2^8 16000 558 / 634,
+// 24000 836 / 782, 64000 2294 / 1440; of 2^7 to 2^9 32000 1389 / 1472, 64000
+// 2751 / 2565; of 2^9 to 2^10 64000 3643 / 5538.
+constexpr long long solo_graph_limit(long long N) { return (1 << 14) + N / 512; }
+
 // A batch's phase log is summed over its graphs in the buffer of the partial
 // results (Part), which one workgroup per graph leaves unused: records that
 // buffer holds, and records kept for a batch whose largest graph has n vertices.

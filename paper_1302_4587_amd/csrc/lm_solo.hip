@@ -771,6 +771,7 @@ bool Solver::solo_fits(int64_t N, int64_t nnz, int64_t G, const int64_t* vtx_off
   if (tun.tail_entries <= 0) return false;  // phase kernels only
   if (G == 1)
     return N <= kSoloMaxN && nnz <= std::min<int64_t>(kSoloEntries, tun.tail_entries);
+  if (G > solo_graph_limit(N)) return false;
   int64_t mx = 0, me = 0;
   for (int64_t g = 0; g < G; ++g) {
     mx = std::max(mx, vtx_off[g + 1] - vtx_off[g]);

@@ -59,3 +59,13 @@ def test_many_small_graphs(ctx, weighted):
     print(f"case: many small graphs weighted={weighted}", flush=True)
     _solve(ctx, gs, weighted)
     _solve(ctx, gs, weighted, check_graph=True)
+
+
+@pytest.mark.parametrize("graphs,phase_kernels", [(16000, False), (16500, True)])
+def test_number_of_graphs(ctx, graphs, phase_kernels):
+    """On both sides of the number of graphs (2^14 and one for every 512 vertices) past which the phase kernels solve a
+    batch."""
+    gs = [lmgen.er(2, 1, 0), lmgen.er(3, 2, 1), lmgen.er(1, 0, 2), lmgen.er(4, 4, 3)]
+    print(f"case: {graphs} graphs", flush=True)
+    st, _ = _solve(ctx, [gs[i % 4] for i in range(graphs)], profile=True)
+    assert (st.kernel_launches["init"] > 0) == phase_kernels
