@@ -364,8 +364,15 @@ constexpr int kSoloClasses = 3;            // size classes of a batch's graphs
 // 3394 / 4938, d = 128 4891 / 4202; 32 of n = 20000, d = 100 1555 / 2530, d = 200
 // 5120 / 2618; 64 of n = 60000, d = 128 5377 / 8143; 64 of n = 4000, d = 1000
 // 3103 / 3309, d = 3000 8625 / 7811; 256 of n = 4000, d = 1000 4308 / 10224.
-inline long long solo_entry_limit(long long N, long long T, bool unweighted) {
-  const long long x = (1ll << 18) + (long long)(3200.0 * __builtin_sqrt((double)N)) + T / 128;
+// A stream-ordered solve (LM_ASYNC) goes on by itself from the phase kernels to the
+// tail, which a solve whose phases the host follows does for a single graph only: about
+// 150 us, 13 us per million entries and 60 per million vertices. Measured (the same,
+// stream-ordered): 2 of n = 30000, d = 8 303 / 178; 8 of n = 60000, d = 8 661 / 287; 32
+// of n = 8000, d = 32 294 / 384; 32 of n = 30000, d = 8 377 / 367; 32 of n = 60000,
+// d = 8 671 / 512; 128 of n = 30000, d = 8 462 / 794; 128 of n = 60000, d = 8 869 / 1410.
+inline long long solo_entry_limit(long long N, long long T, bool unweighted, bool async) {
+  const long long x = async ? (1ll << 17) + N / 16 + T / 80
+                            : (1ll << 18) + (long long)(3200.0 * __builtin_sqrt((double)N)) + T / 128;
   return unweighted ? x - x / 5 : x;
 }
 
@@ -375,8 +382,12 @@ inline long long solo_entry_limit(long long N, long long T, bool unweighted) {
 // each / phase kernels; weighted): graphs of 2^4 to 2^6 vertices 12000 329 / 443,
 // 16000 423 / 433, 24000 627 / 472, 64000 1626 / 675; of 2^6 to 2^8 16000 558 / 634,
 // 24000 836 / 782, 64000 2294 / 1440; of 2^7 to 2^9 32000 1389 / 1472, 64000
-// 2751 / 2565; of 2^9 to 2^10 64000 3643 / 5538.
-constexpr long long solo_graph_limit(long long N) { return (1 << 14) + N / 512; }
+// 2751 / 2565; of 2^9 to 2^10 64000 3643 / 5538. Stream-ordered (above): of 2^4 to
+// 2^6 8000 204 / 270, 16000 390 / 307; of 2^6 to 2^8 12000 398 / 427, 16000 527 / 480;
+// of 2^7 to 2^9 16000 662 / 795, 24000 1013 / 1052; of 2^9 to 2^10 64000 3562 / 5379.
+constexpr long long solo_graph_limit(long long N, bool async) {
+  return async ? (3 << 12) + N / 640 : (1 << 14) + N / 512;
+}
 
 // A batch's phase log is summed over its graphs in the buffer of the partial
 // results (Part), which one workgroup per graph leaves unused: records that

@@ -99,7 +99,7 @@ extern "C" lm_status lm_match_noalloc(lm_ctx* c, const lm_csr* g, uint64_t seed,
   Work wk;
   (void)carve_work(N, nnz, 1, base, &wk);
   hipStream_t s = (hipStream_t)stream;
-  const bool solo = S.solo_fits(N, nnz, 1, nullptr, nullptr, g->w == nullptr);
+  const bool solo = S.solo_fits(N, nnz, 1, nullptr, nullptr, g->w == nullptr, false);
   if (!solo)
     hipLaunchKernelGGL(k_single_tables, dim3(1), dim3(64), 0, s, wk.gbase, wk.gseed, wk.vtxoff,
                      (unsigned long long)premix_seed(seed), (long long)N);

@@ -134,7 +134,8 @@ struct Solver {
   lm_status run(const Problem& p, const Work& wk, hipStream_t s, uint32_t flags, lm_stats* st);
   // One workgroup per graph (lm_solo.hip): whether it takes this solve, and the solve.
   // (row_ptr: on the host, or nullptr)
-  bool solo_fits(int64_t N, int64_t nnz, int64_t G, const int64_t* vtx_off, const int64_t* row_ptr, bool unweighted) const;
+  bool solo_fits(int64_t N, int64_t nnz, int64_t G, const int64_t* vtx_off, const int64_t* row_ptr, bool unweighted,
+                 bool async) const;
   lm_status run_solo(const Problem& p, const Work& wk, const int64_t* vtx_off, uint64_t seed, hipStream_t s,
                      uint32_t flags, lm_stats* st, bool* declined);
   hipEvent_t event(size_t i);

@@ -767,17 +767,17 @@ lm_status solo_setup() {
 }
 
 bool Solver::solo_fits(int64_t N, int64_t nnz, int64_t G, const int64_t* vtx_off, const int64_t* row_ptr,
-                       bool unweighted) const {
+                       bool unweighted, bool async) const {
   if (tun.tail_entries <= 0) return false;  // phase kernels only
   if (G == 1)
     return N <= kSoloMaxN && nnz <= std::min<int64_t>(kSoloEntries, tun.tail_entries);
-  if (G > solo_graph_limit(N)) return false;
+  if (G > solo_graph_limit(N, async)) return false;
   int64_t mx = 0, me = 0;
   for (int64_t g = 0; g < G; ++g) {
     mx = std::max(mx, vtx_off[g + 1] - vtx_off[g]);
     if (row_ptr) me = std::max(me, row_ptr[vtx_off[g + 1]] - row_ptr[vtx_off[g]]);
   }
-  return mx <= kSoloMaxN && me <= solo_entry_limit(N, nnz, unweighted);
+  return mx <= kSoloMaxN && me <= solo_entry_limit(N, nnz, unweighted, async);
 }
 
 // Runs the solve whose graphs solo_fits accepted. The entries of a batch's graphs
@@ -835,7 +835,7 @@ lm_status Solver::run_solo(const Problem& p, const Work& wk, const int64_t* vtx_
   hipEvent_t ev[2];
   const bool one = p.G == 1 && !check && !prof;  // a single launch
   // Whether a graph of the batch may have too many entries (n (n - 1) at most).
-  const long long limit = solo_entry_limit(p.N, p.nnz, unw);
+  const long long limit = solo_entry_limit(p.N, p.nnz, unw, (flags & LM_ASYNC) != 0);
   bool ask = false;
   for (int64_t g = 0; p.G > 1 && p.nnz > limit && g < p.G && !ask; ++g) {
     const int64_t n = vtx_off[g + 1] - vtx_off[g];

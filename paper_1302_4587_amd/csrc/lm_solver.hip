@@ -950,7 +950,7 @@ static lm_status solve_common(lm_ctx* c, int64_t N, int64_t nnz, int64_t G, cons
   // round trip: nothing is captured (nor where they leave a batch to the phases: a
   // capture costs such a solve more than the host's polling, 1605 us against 1381).
   const int64_t* h_rp = (flags & LM_IN_DEVICE) ? nullptr : row_ptr;
-  const bool solo = N > 0 && S.solo_fits(N, nnz, G, h_vtx_off, h_rp, w == nullptr);
+  const bool solo = N > 0 && S.solo_fits(N, nnz, G, h_vtx_off, h_rp, w == nullptr, (flags & LM_ASYNC) != 0);
   const bool own_stream = !stream && (flags & LM_GRAPH) && !(flags & (LM_PROFILE | LM_ASYNC)) && !solo;
   hipStream_t s = stream ? (hipStream_t)stream : (own_stream ? S.own : nullptr);
   if (own_stream) {

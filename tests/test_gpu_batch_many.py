@@ -69,3 +69,29 @@ def test_number_of_graphs(ctx, graphs, phase_kernels):
     print(f"case: {graphs} graphs", flush=True)
     st, _ = _solve(ctx, [gs[i % 4] for i in range(graphs)], profile=True)
     assert (st.kernel_launches["init"] > 0) == phase_kernels
+
+
+@pytest.mark.parametrize("n", [300, 400])
+@pytest.mark.parametrize("weighted", [True, False])
+@pytest.mark.parametrize("renew", [False, True])
+def test_stream_ordered_dense(ctx, n, weighted, renew):
+    """On both sides of the entries (2^17 and a few for the batch's size) past which the device leaves a stream-ordered batch
+    to the phase kernels."""
+    import torch
+    a = np.triu_indices(n, 1)
+    g = lmgen.from_edges(n, np.stack(a, 1), (np.arange(len(a[0])) * 7919 % 2003 + 1).astype(np.float32))
+    gs = [lmgen.er(300, 1200, 1), g, lmgen.er(1, 0, 3), g]
+    vo, off = np.cumsum([0] + [g.n for g in gs]), np.cumsum([0] + [g.nnz for g in gs])
+    rp = np.concatenate([g.row_ptr[:-1] + o for g, o in zip(gs, off)] + [off[-1:]])
+    col, w = np.concatenate([g.col for g in gs]), np.concatenate([g.w for g in gs])
+    seeds = np.arange(3, 3 + len(gs), dtype=np.uint64)
+    want, _ = oracle.local_max_batch(vo, rp, col, w if weighted else np.ones_like(w), seeds=seeds, renew=renew)
+    dev = [torch.from_numpy(rp).cuda(), torch.from_numpy(col).cuda(), torch.from_numpy(w).cuda() if weighted else None]
+    mate = torch.full((vo[-1],), -7, dtype=torch.int32, device="cuda")
+    for _ in range(3):
+        print(f"case: stream-ordered n={n} weighted={weighted} renew={renew}", flush=True)
+        ctx.match_batch(vo, *dev, seeds=seeds, renew_keys=renew, asynchronous=True, mate=mate)
+        got = mate.clone()
+        mate.fill_(-7)
+        torch.cuda.synchronize()
+        assert np.array_equal(got.cpu().numpy(), want)

@@ -3,6 +3,8 @@ constants of the library's internal header, compiled and printed. No kernel runs
 import os
 import subprocess
 
+import pytest
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_1302_4587_amd", "csrc")
 
@@ -44,3 +46,21 @@ def test_row_numbers_near_the_limit(tmp_path):
     at = [(0, 0, n), (0, 64, 64), (0, 63, 64), (n - 63, 62, n), (n - 63, 63, n), (n - 63, 64, n), (n - 63, 192, n), (n - 1, 64, n), (5, 700, 6)]
     got = _values(tmp_path, *(f"row_or_end({r}, {i}u, {m})" for r, i, m in at))
     assert got == [min(r + i, m) for r, i, m in at]
+
+
+# (graphs, vertices of each, average degree, stream-ordered, whether one workgroup each is the faster way by a fifth or more)
+SIDES = [
+    (2, 8000, 8, 1, True), (128, 30000, 8, 1, True), (128, 60000, 8, 1, True), (512, 8000, 8, 1, True), (4000, 36, 3, 1, True), (64000, 740, 4, 1, True),
+    (2, 30000, 8, 1, False), (8, 30000, 8, 1, False), (8, 60000, 8, 1, False), (32, 60000, 8, 1, False),
+    (16000, 36, 3, 1, False), (64000, 36, 3, 1, False), (16000, 140, 5, 1, False),
+    (2, 60000, 8, 0, True), (32, 60000, 8, 0, True), (64000, 740, 4, 0, True), (8000, 36, 3, 0, True),
+    (2, 60000, 64, 0, False), (4, 4000, 250, 0, False), (24000, 36, 3, 0, False), (128000, 140, 5, 0, False),
+]
+
+
+@pytest.mark.parametrize("graphs,n,degree,stream_ordered,solo", SIDES)
+def test_batches_one_workgroup_each(tmp_path, graphs, n, degree, stream_ordered, solo):
+    """The rule for a weighted batch of equal graphs falls on the side that measured faster."""
+    N, T, a = graphs * n, graphs * n * degree, stream_ordered
+    most, entries = _values(tmp_path, f"solo_graph_limit({N}, {a})", f"solo_entry_limit({N}, {T}, false, {a})")
+    assert (graphs <= most and n * degree <= entries) == solo
